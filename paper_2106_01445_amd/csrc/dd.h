@@ -138,16 +138,46 @@ __host__ __device__ __forceinline__ dd dd_sqrt(dd x)
     return quick_two_sum(s, r.hi / (2.0 * s));
 }
 
-// 1/sqrt(x) for x > 0, refined by one Newton step y <- y + y (1 - x y^2) / 2.
-__host__ __device__ __forceinline__ dd dd_rsqrt(dd x)
+// 1/sqrt(x) for x > 0: the fp64 value y and the next terms of its series in
+// e = 1 - x y^2 (|e| of the order of 1e-16): y + y e (1/2 + 3 e / 8), with e
+// formed from error-free products (1 - x.hi y^2 cancels exactly).
+__device__ __forceinline__ dd dd_rsqrt(dd x)
 {
 #pragma clang fp contract(off)
-    double y0 = 1.0 / sqrt(x.hi);
-    dd y = dd_make(y0);
-    dd e = dd_sub(dd_make(1.0), dd_mul(x, dd_mul(y, y)));
-    y = dd_add(y, dd_mul_d(dd_mul(y, e), 0.5));
-    e = dd_sub(dd_make(1.0), dd_mul(x, dd_mul(y, y)));
-    return dd_add(y, dd_mul_d(dd_mul(y, e), 0.5));
+    const double y = rsqrt(x.hi);
+    const dd h = two_prod(y, y);
+    const dd q = two_prod(x.hi, h.hi);
+    double e = (1.0 - q.hi) - q.lo;
+    e = fma(-x.hi, h.lo, e);
+    e = fma(-x.lo, h.hi, e);
+    return quick_two_sum(y, y * e * fma(0.375, e, 0.5));
+}
+
+// a - p q and a - p q - r s: error-free leading products and sums, what is
+// below them in one fp64 sum (errors of a few 2^-106 of the largest term, as
+// dd_mul and dd_add leave)
+__device__ __forceinline__ dd dd_fms(dd a, dd p, dd q)
+{
+#pragma clang fp contract(off)
+    const dd t = two_prod(p.hi, q.hi);
+    const dd u = two_sum(a.hi, -t.hi);
+    double lo = fma(-p.hi, q.lo, a.lo);
+    lo = fma(-p.lo, q.hi, lo);
+    lo += u.lo - t.lo;
+    return quick_two_sum(u.hi, lo);
+}
+__device__ __forceinline__ dd dd_fms2(dd a, dd p, dd q, dd r, dd s)
+{
+#pragma clang fp contract(off)
+    const dd f = two_prod(p.hi, q.hi), g = two_prod(r.hi, s.hi);
+    const dd t = two_sum(f.hi, g.hi);
+    const dd u = two_sum(a.hi, -t.hi);
+    double lo = fma(-p.hi, q.lo, a.lo);
+    lo = fma(-p.lo, q.hi, lo);
+    lo = fma(-r.hi, s.lo, lo);
+    lo = fma(-r.lo, s.hi, lo);
+    lo += u.lo - ((f.lo + g.lo) + t.lo);
+    return quick_two_sum(u.hi, lo);
 }
 
 // exp(x) for |x| < 700.  x = k ln2 + r; r' = r / 1024; Taylor to degree 14;

@@ -3,168 +3,252 @@
 //
 //   p(C) = det(Q)^{-1/2} sum_{Z subset C} (-1)^{n-|Z|} det(A_Z)^{-1/2},  A = (Q^{-1})_CC
 //
-// Each determinant is a product of 2x2 Schur-complement determinants taken one
-// mode at a time, so the subsets form a binary include/exclude tree over the
-// clicked modes and every tree edge that includes a mode costs one rank-2
-// update of the remaining matrix.  Work split:
-//   - the first h = max(0, n-9) modes: 2^h included/excluded assignments z0,
-//     dealt to at most 2^EX_LGI work items (one wavefront each) per row, each
-//     item taking a contiguous range of z0 in turn; for each z0 the wave
-//     conditions A on the included prefix modes by successive Schur steps in
-//     LDS;
-//   - the next m = R-3 modes (R = n-h <= 9): breadth-first expansion in LDS,
-//     level by level, ending with 2^m <= 64 nodes, one per lane;
-//   - the last 3 modes: each lane evaluates its node's 8 subsets in registers.
-// All matrices are kept as packed symmetric double-double (hi/lo planes) with
-// the two quadratures of a mode interleaved.  Signed sums are double-double,
-// reduced in a fixed order; kappa = sum|terms| / |sum| is returned.
+// The subsets form a binary include/exclude tree over the clicked modes.
+// Including a mode takes its two quadratures out of the remaining matrix by a
+// 2x2 Cholesky step (l = the factor of the mode's own block, y = l^{-1} times
+// its rows, a_ij -= y_i y_j) and multiplies the subset's term by
+// det(l)^{-1}; excluding it drops its rows.  A matrix is stored with the last
+// mode first, so that what remains after a mode, in either branch, is a
+// prefix of what was there: excluded children need no storage of their own.
+// Work split of a row of n clicks, R = min(n, EX_R) (one wavefront per item):
+//   - the first h = n - R modes: 2^h assignments z0, dealt to at most 2^EX_LGI
+//     items per row in contiguous ranges.  The high bits of z0 are conditioned
+//     on in LDS, from the gathered matrix; the result, of R + EX_IN modes, is
+//     held in registers for the 2^EX_IN assignments that share it;
+//   - the next R - S - 1 modes: breadth first in LDS, each level's included
+//     children in one pass over (node, pair of modes);
+//   - the last S + 1 modes: one lane per node and choice of the first of them
+//     (lanes 0..31 without it, 32..63 with it), which then walks the tree of
+//     the other S modes in registers.
+// Signed sums are double-double, reduced in a fixed order; kappa =
+// sum|terms| / |sum| is returned.
+//
+// What bounds it: the fp64 vector ALUs (about 390 operations per subset, the
+// Schur complements 7 entries of them at 27 each, and as many again for the
+// levels' redundant factors and the lanes that carry an excluded mode).  The
+// breadth-first levels of 64 lanes' nodes take 39 KB of LDS, so that one
+// wavefront sits on each SIMD with 512 registers, and the independent entries
+// of a step keep it busy.  Against levels that end with three modes per node,
+// copy excluded children and pay 122 operations per entry (43 KB, three
+// wavefronts per compute unit): one row of 30 clicks 502 -> 31.6 ms (3.4e10
+// subsets/s), 4096 rows of 6-14 clicks at 20 modes 8.60 -> 0.62 ms.
 #include <algorithm>
 #include <mutex>
 
 #include "internal.h"
 
-#define EX_R 9          // modes handled inside one prefix assignment
-#define EX_BUF 1344     // packed dd entries of the 64 nodes x 21 of the last level
+#define EX_R 10         // modes handled inside one prefix assignment
+#define EX_S 4          // of these, walked in registers by one lane (R = EX_R)
+#define EX_IN 3         // prefix modes whose assignments share one conditioned matrix
 #define EX_LGI 12       // at most 2^12 work items per row
+#define EX_SMALL 8      // rows of at most this many clicks take the small kernel
 
-// packed dd entries per LDS buffer for rows of up to maxn clicks: the last
-// expansion level, or the matrix of all maxn modes
-__host__ __device__ __forceinline__ int ex_buf(int maxn)
+// packed dd entries of a symmetric matrix of k modes
+__host__ __device__ constexpr int ex_e(int k) { return k * (2 * k + 1); }
+// where the levels of R modes sit: level l's included children (l >= 1, 2^{l-1}
+// matrices of R - l modes) follow each other, the root's matrix comes last
+__host__ __device__ constexpr int ex_lev(int R, int l)
 {
-    const int k = maxn * (2 * maxn + 1);
-    return k > EX_BUF ? k : EX_BUF;
+    int o = 0;
+    for (int u = 1; u < l; ++u) o += (1 << (u - 1)) * ex_e(R - u);
+    return o;
 }
-__host__ __device__ __forceinline__ int ex_lds_bytes(int maxn)
-{
-    // two buffers (hi and lo planes) and the packed index tables (two shorts)
-    return 4 * 8 * ex_buf(maxn) + 2 * 2 * ex_buf(maxn);
-}
+// At R = EX_R the last level's two last matrices take the place of those of the
+// root's rows that are no longer read when they are written (the rows of the
+// modes before the level's own): this brings four wavefronts' levels into a
+// compute unit's 160 KB
+#define EX_LMAX (EX_R - EX_S - 1)
+#define EX_TUCK 2
+#define EX_ROOT (ex_lev(EX_R, EX_LMAX + 1) - EX_TUCK * ex_e(EX_S + 1))
+static_assert(ex_e(EX_R - EX_LMAX + 1) + EX_TUCK * ex_e(EX_S + 1) <= ex_e(EX_R), "the tucked matrices lie in the root's dead rows");
+#define EX_CAP (EX_ROOT + ex_e(EX_R))
+static_assert(ex_e(GBS_MAX_N_EXACT) <= EX_CAP, "the prefix's matrix is conditioned in the levels' place");
+static_assert(EX_LMAX == 5, "32 nodes, one lane for each choice of their first mode");
+#define EX_CAP_SMALL (ex_lev(EX_SMALL, 6) + ex_e(EX_SMALL))
 
 namespace {
 
-__device__ __forceinline__ int pk(int r, int c) { return r >= c ? r * (r + 1) / 2 + c : c * (c + 1) / 2 + r; }
+__device__ __forceinline__ dd sel(bool c, dd x) { return dd{c ? x.hi : 0.0, c ? x.lo : 0.0}; }
 
-struct Sym2 {  // symmetric 2x2 dd block
-    dd a, b, c;  // [[a, b], [b, c]]
+// 2x2 Cholesky factor of a mode's block [[a, b], [b, d]]: inverse diagonal and
+// the off-diagonal entry; det^{-1/2} = i0 i1
+struct Piv {
+    dd i0, l, i1;
 };
+__device__ __forceinline__ Piv factor(dd a, dd b, dd d)
+{
+    Piv f;
+    f.i0 = dd_rsqrt(a);
+    f.l = dd_mul(b, f.i0);
+    f.i1 = dd_rsqrt(dd_fms(d, f.l, f.l));
+    return f;
+}
+__device__ __forceinline__ dd rdet(dd a, dd b, dd d) { return dd_rsqrt(dd_fms(dd_mul(a, d), b, b)); }
 
-__device__ __forceinline__ dd det2(const Sym2 &s) { return dd_sub(dd_mul(s.a, s.c), dd_mul(s.b, s.b)); }
-
-__device__ __forceinline__ Sym2 inv2(const Sym2 &s, dd det)
+__device__ __forceinline__ void add_term(dd v, dd &tot, double &ab)
 {
-    dd id = dd_recip(det);
-    return Sym2{dd_mul(s.c, id), dd_neg(dd_mul(s.b, id)), dd_mul(s.a, id)};
-}
-
-struct Gen2 {  // general 2x2 dd block [[p, q], [r, s]]
-    dd p, q, r, s;
-};
-
-// inv (sym) * X (general)
-__device__ __forceinline__ Gen2 mul_sg(const Sym2 &i, const Gen2 &x)
-{
-    return Gen2{dd_add(dd_mul(i.a, x.p), dd_mul(i.b, x.r)), dd_add(dd_mul(i.a, x.q), dd_mul(i.b, x.s)),
-                dd_add(dd_mul(i.b, x.p), dd_mul(i.c, x.r)), dd_add(dd_mul(i.b, x.q), dd_mul(i.c, x.s))};
-}
-// Y^T * G  (general^T * general), symmetric result when G = inv * Y
-__device__ __forceinline__ Sym2 tmul_sym(const Gen2 &y, const Gen2 &g)
-{
-    return Sym2{dd_add(dd_mul(y.p, g.p), dd_mul(y.r, g.r)), dd_add(dd_mul(y.p, g.q), dd_mul(y.r, g.s)),
-                dd_add(dd_mul(y.q, g.q), dd_mul(y.s, g.s))};
-}
-__device__ __forceinline__ Gen2 tmul_gen(const Gen2 &y, const Gen2 &g)
-{
-    return Gen2{dd_add(dd_mul(y.p, g.p), dd_mul(y.r, g.r)), dd_add(dd_mul(y.p, g.q), dd_mul(y.r, g.s)),
-                dd_add(dd_mul(y.q, g.p), dd_mul(y.s, g.r)), dd_add(dd_mul(y.q, g.q), dd_mul(y.s, g.s))};
-}
-__device__ __forceinline__ Sym2 sub_s(const Sym2 &a, const Sym2 &b)
-{
-    return Sym2{dd_sub(a.a, b.a), dd_sub(a.b, b.b), dd_sub(a.c, b.c)};
-}
-__device__ __forceinline__ Gen2 sub_g(const Gen2 &a, const Gen2 &b)
-{
-    return Gen2{dd_sub(a.p, b.p), dd_sub(a.q, b.q), dd_sub(a.r, b.r), dd_sub(a.s, b.s)};
+    const dd s = two_sum(tot.hi, v.hi);
+    tot.lo += s.lo + v.lo;
+    tot.hi = s.hi;
+    ab += fabs(v.hi);
 }
 
-struct Buf {
-    double *hi, *lo;
-    __device__ __forceinline__ dd get(int i) const { return dd{hi[i], lo[i]}; }
-    __device__ __forceinline__ void put(int i, dd v) const
-    {
-        hi[i] = v.hi;
-        lo[i] = v.lo;
+// The first of K modes held in registers (packed, last mode first) taken out of
+// the others' matrix; returns its -det^{-1/2}.
+template <int K>
+__device__ __forceinline__ dd step(const dd (&A)[ex_e(K)], dd (&B)[ex_e(K - 1)])
+{
+    constexpr int Y = ex_e(K - 1), D = Y + 4 * (K - 1);  // the first mode's rows, its own block
+    const Piv f = factor(A[D], A[D + 1], A[D + 2]);
+    dd y[K - 1][4];  // per mode: y0 (x, p), y1 (x, p)
+#pragma unroll
+    for (int j = 0; j < K - 1; ++j)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            y[j][c] = dd_mul(A[Y + 4 * j + c], f.i0);
+            y[j][2 + c] = dd_mul(dd_fms(A[Y + 4 * j + 2 + c], f.l, y[j][c]), f.i1);
+        }
+#pragma unroll
+    for (int i = 0; i < K - 1; ++i) {
+#pragma unroll
+        for (int j = 0; j < i; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int e = ex_e(i) + 4 * j + t, r = t >> 1, c = t & 1;
+                B[e] = dd_fms2(A[e], y[i][r], y[j][c], y[i][2 + r], y[j][2 + c]);
+            }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const int e = ex_e(i) + 4 * i + t, r = t == 2, c = t > 0;
+            B[e] = dd_fms2(A[e], y[i][r], y[i][c], y[i][2 + r], y[i][2 + c]);
+        }
     }
-};
-
-__device__ __forceinline__ Sym2 sblk(const Buf &b, int base, int j)
-{
-    return Sym2{b.get(base + pk(2 * j, 2 * j)), b.get(base + pk(2 * j + 1, 2 * j)),
-                b.get(base + pk(2 * j + 1, 2 * j + 1))};
-}
-// block (rows of mode i, cols of mode j), i < j
-__device__ __forceinline__ Gen2 gblk(const Buf &b, int base, int i, int j)
-{
-    return Gen2{b.get(base + pk(2 * i, 2 * j)), b.get(base + pk(2 * i, 2 * j + 1)),
-                b.get(base + pk(2 * i + 1, 2 * j)), b.get(base + pk(2 * i + 1, 2 * j + 1))};
+    return dd_neg(dd_mul(f.i0, f.i1));
 }
 
-// Leaf: the 2^S subsets of the last S (1..3) modes of one node's matrix.
-// Adds sign * acc * det(S_T)^{-1/2} into tot and acc*|...| into ab, where the
-// sign of subset T is (-1)^(base_par + |T|).
-template <int S>
-__device__ void leaf(const Buf &b, int base, dd acc, int base_par, dd &tot, double &ab)
+// The subsets of K modes held in registers; acc: the product of the inverse
+// roots so far with the subset's sign.
+template <int K>
+__device__ __forceinline__ void walk(const dd (&A)[ex_e(K)], dd acc, dd &tot, double &ab)
 {
-    auto add = [&](dd f, int t) {
-        dd v = dd_mul(acc, f);
-        tot = ((base_par + t) & 1) ? dd_sub(tot, v) : dd_add(tot, v);
-        ab += fabs(v.hi);
-    };
-    add(dd_make(1.0), 0);
-    const Sym2 sx = sblk(b, base, 0);
-    const dd dx = det2(sx);
-    const dd rx = dd_rsqrt(dx);
-    add(rx, 1);
-    if (S == 1) return;
-    const Sym2 sy = sblk(b, base, 1);
-    const dd dy = det2(sy);
-    const dd ry = dd_rsqrt(dy);
-    add(ry, 1);
-    const Sym2 ix = inv2(sx, dx);
-    const Gen2 xy = gblk(b, base, 0, 1);
-    const Gen2 gy = mul_sg(ix, xy);
-    const Sym2 syx = sub_s(sy, tmul_sym(xy, gy));      // S_yy | x
-    const dd dyx = det2(syx);
-    add(dd_mul(rx, dd_rsqrt(dyx)), 2);
-    if (S == 2) return;
-    const Sym2 sz = sblk(b, base, 2);
-    add(dd_rsqrt(det2(sz)), 1);
-    const Gen2 xz = gblk(b, base, 0, 2);
-    const Gen2 yz = gblk(b, base, 1, 2);
-    const Gen2 gz = mul_sg(ix, xz);
-    const Sym2 szx = sub_s(sz, tmul_sym(xz, gz));      // S_zz | x
-    add(dd_mul(rx, dd_rsqrt(det2(szx))), 2);
-    const Sym2 iy = inv2(sy, dy);
-    const Sym2 szy = sub_s(sz, tmul_sym(yz, mul_sg(iy, yz)));  // S_zz | y
-    add(dd_mul(ry, dd_rsqrt(det2(szy))), 2);
-    const Gen2 yzx = sub_g(yz, tmul_gen(xy, gz));     // S_yz | x
-    const Sym2 iyx = inv2(syx, dyx);
-    const Sym2 szxy = sub_s(szx, tmul_sym(yzx, mul_sg(iyx, yzx)));  // S_zz | x,y
-    add(dd_mul(dd_mul(rx, dd_rsqrt(dyx)), dd_rsqrt(det2(szxy))), 3);
+    if constexpr (K == 1) {
+        add_term(acc, tot, ab);
+        add_term(dd_neg(dd_mul(acc, rdet(A[0], A[1], A[2]))), tot, ab);
+    } else {
+        dd B[ex_e(K - 1)];
+        const dd r = step<K>(A, B);
+        walk<K - 1>(B, dd_mul(acc, r), tot, ab);
+#pragma unroll
+        for (int e = 0; e < ex_e(K - 1); ++e) B[e] = A[e];
+        walk<K - 1>(B, acc, tot, ab);
+    }
 }
 
-// One elimination step: Schur complement of the first mode of the k-mode
-// matrix at src+sbase, written (k-1 modes) to dst+dbase; lanes split entries.
-__device__ __forceinline__ void schur_first(const Buf &src, int sbase, const Buf &dst, int dbase, int k,
-                                            const Sym2 &inv, int e, const short *lr, const short *lc)
+__device__ __forceinline__ dd ld(const double2 *p)
 {
-    const int r = lr[e], c = lc[e];
-    const int R = r + 2, Cc = c + 2;
-    const dd a0 = src.get(sbase + pk(R, 0)), a1 = src.get(sbase + pk(R, 1));
-    const dd b0 = src.get(sbase + pk(0, Cc)), b1 = src.get(sbase + pk(1, Cc));
-    const dd t0 = dd_add(dd_mul(inv.a, b0), dd_mul(inv.b, b1));
-    const dd t1 = dd_add(dd_mul(inv.b, b0), dd_mul(inv.c, b1));
-    dst.put(dbase + e, dd_sub(src.get(sbase + pk(R, Cc)), dd_add(dd_mul(a0, t0), dd_mul(a1, t1))));
+    const double2 v = *p;
+    return dd{v.x, v.y};
 }
+__device__ __forceinline__ void st(double2 *p, dd v) { *p = make_double2(v.hi, v.lo); }
+
+// block (i, j), j <= i, of the lower triangle from its index i (i + 1)/2 + j
+__device__ __forceinline__ void tri_ij(int t, int &i, int &j)
+{
+    i = (int)(0.5f * (sqrtf(8.0f * (float)t + 1.0f) - 1.0f));
+    if ((i + 1) * (i + 2) / 2 <= t) ++i;
+    if (i * (i + 1) / 2 > t) --i;
+    j = t - i * (i + 1) / 2;
+}
+
+// y of mode block j in the rows of mode i of the matrix at m, in place
+__device__ __forceinline__ void make_y(double2 *m, int i, int j, const Piv &f)
+{
+    double2 *q = m + ex_e(i) + 4 * j;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const dd y0 = dd_mul(ld(q + c), f.i0);
+        const dd y1 = dd_mul(dd_fms(ld(q + 2 + c), f.l, y0), f.i1);
+        st(q + c, y0);
+        st(q + 2 + c, y1);
+    }
+}
+// the child's block (i, j) from the parent's, yr: the parent's row of y
+__device__ __forceinline__ void update(const double2 *src, const double2 *yr, double2 *dst, int i, int j)
+{
+    const double2 *yi = yr + 4 * i, *yj = yr + 4 * j;
+    const dd i0 = ld(yi), i1 = ld(yi + 1), i2 = ld(yi + 2), i3 = ld(yi + 3);
+    const dd j0 = ld(yj), j1 = ld(yj + 1), j2 = ld(yj + 2), j3 = ld(yj + 3);
+    const int e = ex_e(i) + 4 * j;
+    if (i != j) {
+        const dd a0 = dd_fms2(ld(src + e), i0, j0, i2, j2), a1 = dd_fms2(ld(src + e + 1), i0, j1, i2, j3);
+        const dd a2 = dd_fms2(ld(src + e + 2), i1, j0, i3, j2), a3 = dd_fms2(ld(src + e + 3), i1, j1, i3, j3);
+        st(dst + e, a0);
+        st(dst + e + 1, a1);
+        st(dst + e + 2, a2);
+        st(dst + e + 3, a3);
+    } else {
+        const dd a0 = dd_fms2(ld(src + e), i0, i0, i2, i2), a1 = dd_fms2(ld(src + e + 1), i0, i1, i2, i3);
+        const dd a2 = dd_fms2(ld(src + e + 2), i1, i1, i3, i3);
+        st(dst + e, a0);
+        st(dst + e + 1, a1);
+        st(dst + e + 2, a2);
+    }
+}
+__device__ __forceinline__ Piv factor_at(const double2 *m, int i)
+{
+    const double2 *q = m + ex_e(i) + 4 * i;
+    return factor(ld(q), ld(q + 1), ld(q + 2));
+}
+
+// One wavefront conditions the matrix at m on the mode of its row i, in place
+// (the rows above are left as they are); returns -det^{-1/2}.
+__device__ __forceinline__ dd condition(double2 *m, int i, int lane)
+{
+    const Piv f = factor_at(m, i);
+    __syncthreads();
+    if (lane < i) make_y(m, i, lane, f);
+    __syncthreads();
+    for (int t = lane; t < i * (i + 1) / 2; t += 64) {
+        int r, c;
+        tri_ij(t, r, c);
+        update(m, m + ex_e(i), m, r, c);
+    }
+    __syncthreads();
+    return dd_neg(dd_mul(f.i0, f.i1));
+}
+
+// The matrix of K modes of a lane's node: the prefix of its parent's matrix at
+// m, less the terms of the parent's first mode (row K, whose y stand there)
+// where inc
+template <int K>
+__device__ __forceinline__ void load_node(dd (&A)[ex_e(K)], const double2 *m, bool inc, bool one)
+{
+    dd y[K][4];
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y[j][t] = one ? dd_make(0.0) : sel(inc, ld(m + ex_e(K) + 4 * j + t));
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+#pragma unroll
+        for (int j = 0; j < i; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int e = ex_e(i) + 4 * j + t, r = t >> 1, c = t & 1;
+                A[e] = dd_fms2(ld(m + e), y[i][r], y[j][c], y[i][2 + r], y[j][2 + c]);
+            }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const int e = ex_e(i) + 4 * i + t, r = t == 2, c = t > 0;
+            A[e] = dd_fms2(ld(m + e), y[i][r], y[i][c], y[i][2 + r], y[i][2 + c]);
+        }
+    }
+}
+
+// Modes of a row of R = min(n, EX_R) that one lane walks in registers: few for
+// the short rows (64 lanes then share the row's nodes: latency), EX_S for the
+// long ones (the levels of 32 nodes fill the LDS)
+__device__ __forceinline__ int ex_s(int R) { return R >= EX_R ? EX_S : R == 9 ? 3 : R >= 2 ? 2 : 1; }
 
 __device__ __forceinline__ dd wave_dd_sum(dd v)
 {
@@ -175,166 +259,191 @@ __device__ __forceinline__ dd wave_dd_sum(dd v)
     return v;
 }
 
-// One work item: row p = item >> lgS, part i = item & (S - 1) of its 2^h prefix
-// assignments (rows of more than maxn clicks, or with modes outside [0, M) or
-// not ascending, are left to k_exact_final, which flags them).
+// whether a row's modes are in [0, M) and ascend (n <= 64; every lane gets it)
+__device__ __forceinline__ bool wave_row_ok(const int *__restrict__ row, int n, int M, int lane)
+{
+    bool bad = false;
+    if (lane < n) {
+        const int m = row[lane];
+        bad = m < 0 || m >= M || (lane > 0 && m <= row[lane - 1]);
+    }
+    return __ballot(bad) == 0ull;
+}
+
+// One work item: row p = block >> lgG, part g of the at most 2^lgG parts of its
+// 2^h prefix assignments (rows of more than maxn clicks, or with modes outside
+// [0, M) or not ascending, are left to k_exact_final, which flags them).
+// SMALL: rows of at most EX_SMALL clicks only (fewer registers, less LDS).
+template <bool SMALL>
 __global__ __launch_bounds__(64) void k_exact(int M, const double *__restrict__ qi_hi,
                                               const double *__restrict__ qi_lo,
                                               const int *__restrict__ offsets,
-                                              const int *__restrict__ modes, int lgS, int maxn,
+                                              const int *__restrict__ modes, int lgG, int maxn,
                                               double *__restrict__ part)
 {
-    extern __shared__ __attribute__((aligned(16))) double exsh[];
-    __shared__ double nacc_h[2][64], nacc_l[2][64];
-    __shared__ int npar[2][64];
-    __shared__ double ninv_h[3][32], ninv_l[3][32];
-    __shared__ int gidx[2 * GBS_MAX_N_EXACT];
-    __shared__ int s_bad;
-    const int BUF = ex_buf(maxn);
-    double *bh0 = exsh, *bh1 = bh0 + BUF, *bl0 = bh1 + BUF, *bl1 = bl0 + BUF;
-    short *lr = (short *)(bl1 + BUF), *lc = lr + BUF;
+    __shared__ double2 buf[SMALL ? EX_CAP_SMALL : EX_CAP];
+    __shared__ double2 nacc[32];
+    __shared__ short gidx[32];
     const int lane = threadIdx.x;
     const long long item = blockIdx.x;
-    const int p = (int)(item >> lgS), ip = (int)(item & ((1LL << lgS) - 1));
+    const int p = (int)(item >> lgG), ip = (int)(item & ((1LL << lgG) - 1));
     const int o = offsets[p], n = offsets[p + 1] - o;
     if (n <= 0 || n > maxn) return;
-    const int D = 2 * M;
-    const int h = n > EX_R ? n - EX_R : 0;
-    const int R = n - h;
-    const int lgI = h < EX_LGI ? h : EX_LGI;   // this row's items: 2^lgI
-    if (ip >= (1 << lgI)) return;
-    const int lgC = h - lgI;                    // prefix assignments per item: 2^lgC
-    if (lane == 0) {
-        int bad = 0;
-        for (int i = 0; i < n; ++i) {
-            const int m = modes[o + i];
-            if (m < 0 || m >= M || (i > 0 && m <= modes[o + i - 1])) bad = 1;
-        }
-        s_bad = bad;
-    }
-    // packed-index -> (row, col) tables for up to 2 maxn rows
-    for (int r = lane; r < 2 * maxn; r += 64)
-        for (int c = 0; c <= r; ++c) {
-            int e = r * (r + 1) / 2 + c;
-            if (e < BUF) {
-                lr[e] = (short)r;
-                lc[e] = (short)c;
-            }
-        }
-    __syncthreads();
-    if (s_bad) return;
+    const int h = SMALL ? 0 : max(n - EX_R, 0), R = n - h;
+    const int lgP = min(h, lgG);  // this row's parts: 2^lgP
+    if (ip >= (1 << lgP)) return;
+    if (!wave_row_ok(modes + o, n, M, lane)) return;
+    const int lgZ = h - lgP, nin = min(lgZ, EX_IN);  // assignments per part: 2^lgZ
+    const int D = 2 * M, S = ex_s(R), L = max(R - S - 1, 0);
+    const int root = SMALL ? ex_lev(R, L + 1) : R == EX_R ? EX_ROOT : ex_lev(R, L + 1);
+    constexpr int NREG = (ex_e(EX_R + EX_IN) + 63) / 64;
+    const dd sign = dd_make(n & 1 ? -1.0 : 1.0);
     dd rtot = dd_make(0.0);
     double rab = 0.0;
-    for (int zi = 0; zi < (1 << lgC); ++zi) {
-        const int z0 = (ip << lgC) | zi;
-        // local mode list: included prefix modes, then the last R modes
-        int kz = 0;
-        if (lane == 0) {
-            for (int i = 0; i < h; ++i)
-                if (z0 >> i & 1) gidx[kz++] = modes[o + i];
-            for (int i = h; i < n; ++i) gidx[kz++] = modes[o + i];
-        }
-        __syncthreads();
-        const int nz0 = __popc(z0);
-        int k = nz0 + R;
-        Buf B0{bh0, bl0}, B1{bh1, bl1};
-        for (int e = lane; e < k * (2 * k + 1); e += 64) {
-            int r = lr[e], c = lc[e];
-            int gr = gidx[r >> 1] + ((r & 1) ? M : 0);
-            int gc = gidx[c >> 1] + ((c & 1) ? M : 0);
-            B0.put(e, dd{qi_hi[(long)gr * D + gc], qi_lo[(long)gr * D + gc]});
-        }
-        __syncthreads();
-        // condition on the included prefix modes
-        dd acc = dd_make(1.0);
-        int cur = 0;
-        for (int s = 0; s < nz0; ++s) {
-            Buf src = cur ? B1 : B0, dst = cur ? B0 : B1;
-            const Sym2 s00 = sblk(src, 0, 0);
-            const dd det = det2(s00);
-            const Sym2 inv = inv2(s00, det);
-            acc = dd_mul(acc, dd_rsqrt(det));
-            const int cnt = (k - 1) * (2 * k - 1);
-            for (int e = lane; e < cnt; e += 64) schur_first(src, 0, dst, 0, k, inv, e, lr, lc);
-            __syncthreads();
-            cur ^= 1;
-            --k;
-        }
-        // breadth-first expansion of the next m modes
-        const int sl = R < 3 ? R : 3;
-        const int m = R - sl;
-        if (lane == 0) {
-            nacc_h[0][0] = acc.hi;
-            nacc_l[0][0] = acc.lo;
-            npar[0][0] = nz0 & 1;
-        }
-        int nc = 0;  // node-info buffer
-        __syncthreads();
-        for (int lev = 0; lev < m; ++lev) {
-            Buf src = cur ? B1 : B0, dst = cur ? B0 : B1;
-            const int nodes = 1 << lev;
-            const int cs = k * (2 * k + 1);            // packed size per parent
-            const int cd = (k - 1) * (2 * k - 1);      // packed size per child
-            // children node info: 2i exclude, 2i+1 include
-            for (int i = lane; i < nodes; i += 64) {
-                const Sym2 s00 = sblk(src, i * cs, 0);
-                const dd det = det2(s00);
-                const Sym2 inv = inv2(s00, det);
-                ninv_h[0][i] = inv.a.hi; ninv_l[0][i] = inv.a.lo;
-                ninv_h[1][i] = inv.b.hi; ninv_l[1][i] = inv.b.lo;
-                ninv_h[2][i] = inv.c.hi; ninv_l[2][i] = inv.c.lo;
-                dd a = dd{nacc_h[nc][i], nacc_l[nc][i]};
-                const int par = npar[nc][i];
-                nacc_h[nc ^ 1][2 * i] = a.hi;
-                nacc_l[nc ^ 1][2 * i] = a.lo;
-                npar[nc ^ 1][2 * i] = par;
-                dd ai = dd_mul(a, dd_rsqrt(det));
-                nacc_h[nc ^ 1][2 * i + 1] = ai.hi;
-                nacc_l[nc ^ 1][2 * i + 1] = ai.lo;
-                npar[nc ^ 1][2 * i + 1] = par ^ 1;
+    for (int zm = 0; zm < (1 << (lgZ - nin)); ++zm) {
+        const int z0 = (ip << lgZ) | (zm << nin);
+        // the last R modes, then the nin inner prefix modes, then the other
+        // included prefix modes: rows 0, 1, ... of the matrix
+        int k = R + nin;
+        if (lane < k) gidx[lane] = (short)modes[o + (lane < R ? n - 1 - lane : lane - R)];
+        for (int b = nin; b < h; ++b)
+            if (z0 >> b & 1) {
+                if (lane == 0) gidx[k] = (short)modes[o + b];
+                ++k;
             }
+        __syncthreads();
+        double2 *m0 = buf + (h > 0 ? 0 : root);
+        for (int t = lane; t < k * (k + 1) / 2; t += 64) {
+            int i, j;
+            tri_ij(t, i, j);
+            const int gi = gidx[i], gj = gidx[j];
+            double2 *q = m0 + ex_e(i) + 4 * j;
+            const long x = (long)gi * D + gj, y = (long)(gi + M) * D + gj;
+            q[0] = make_double2(qi_hi[x], qi_lo[x]);
+            q[1] = i == j ? make_double2(qi_hi[y], qi_lo[y]) : make_double2(qi_hi[x + M], qi_lo[x + M]);
+            q[2] = i == j ? make_double2(qi_hi[y + M], qi_lo[y + M]) : make_double2(qi_hi[y], qi_lo[y]);
+            if (i != j) q[3] = make_double2(qi_hi[y + M], qi_lo[y + M]);
+        }
+        __syncthreads();
+        dd acc0 = sign;
+        for (int i = k - 1; i >= R + nin; --i) acc0 = dd_mul(acc0, condition(m0, i, lane));
+        double2 mr[NREG];
+        if (!SMALL && nin > 0)
+#pragma unroll
+            for (int t = 0; t < NREG; ++t) mr[t] = buf[min(lane + 64 * t, ex_e(R + nin) - 1)];
+        for (int zi = 0; zi < (1 << nin); ++zi) {
+            dd acc = acc0;
+            if (!SMALL && h > 0) {
+                __syncthreads();
+                if (nin > 0 && zi > 0) {
+#pragma unroll
+                    for (int t = 0; t < NREG; ++t)
+                        if (lane + 64 * t < ex_e(R + nin)) buf[lane + 64 * t] = mr[t];
+                    __syncthreads();
+                }
+                for (int b = nin - 1; b >= 0; --b)
+                    if (zi >> b & 1) acc = dd_mul(acc, condition(buf, R + b, lane));
+                // the root's matrix into its place (the two do not overlap)
+                static_assert(EX_ROOT >= ex_e(EX_R), "");
+                for (int e = lane; e < ex_e(EX_R); e += 64) buf[EX_ROOT + e] = buf[e];
+            }
+            if (lane == 0) nacc[0] = make_double2(acc.hi, acc.lo);
             __syncthreads();
-            for (int e = lane; e < 2 * nodes * cd; e += 64) {
-                const int child = e / cd, idx = e - child * cd;
-                const int parent = child >> 1;
-                if (child & 1) {
-                    const Sym2 inv{dd{ninv_h[0][parent], ninv_l[0][parent]},
-                                   dd{ninv_h[1][parent], ninv_l[1][parent]},
-                                   dd{ninv_h[2][parent], ninv_l[2][parent]}};
-                    schur_first(src, parent * cs, dst, child * cd, k, inv, idx, lr, lc);
-                } else {
-                    const int r = lr[idx] + 2, c = lc[idx] + 2;
-                    dst.put(child * cd + idx, src.get(parent * cs + pk(r, c)));
+            // where node v's matrix stands: that of its last included level
+            auto node_at = [&](int v) {
+                if (v == 0) return root;
+                const int l = 32 - __clz(v), s = v - (1 << (l - 1));
+                int at = 0, e = 0;
+#pragma unroll
+                for (int u = 1; u <= EX_LMAX; ++u) {
+                    if (u < l) at += (1 << (u - 1)) * ex_e(R - u);
+                    if (u == l) e = ex_e(R - u);
+                }
+                at += s * e;
+                if (!SMALL && R == EX_R && l == EX_LMAX && s >= (1 << (EX_LMAX - 1)) - EX_TUCK)
+                    at += ex_e(EX_S + 2);  // (tucked into the root's dead rows)
+                return at;
+            };
+            // breadth first: level lev takes mode row kr of its 2^lev nodes (a lane
+            // keeps its node over a level: 64 is a multiple of their number)
+            for (int lev = 0, to = 0; lev < L; ++lev) {
+                const int kr = R - 1 - lev, nodes = 1 << lev, v = lane & (nodes - 1);
+                double2 *m = buf + node_at(v);
+                for (int j = lane >> lev; j < kr; j += 64 >> lev) {
+                    const Piv f = factor_at(m, kr);
+                    make_y(m, kr, j, f);
+                    if (j == 0) {
+                        const dd a = dd_neg(dd_mul(ld(&nacc[v]), dd_mul(f.i0, f.i1)));
+                        st(&nacc[v + nodes], a);
+                    }
+                }
+                __syncthreads();
+                double2 *ch = buf + to + v * ex_e(kr);
+                if (!SMALL && R == EX_R && lev == EX_LMAX - 1 && v >= nodes - EX_TUCK) ch += ex_e(EX_S + 2);
+                for (int t = lane >> lev; t < kr * (kr + 1) / 2; t += 64 >> lev) {
+                    int i, j;
+                    tri_ij(t, i, j);
+                    update(m, m + ex_e(kr), ch, i, j);
+                }
+                to += ex_e(kr) << lev;
+                __syncthreads();
+            }
+            // the last S + 1 modes: lane v without the first of them, lane 32 + v with
+            const bool one = R <= S;  // (no level: a single lane walks the root)
+            const int v = lane & 31, nodes = 1 << L;
+            const bool inc = lane >= 32, on = one ? lane == 0 : v < nodes;
+            const double2 *m = buf + node_at(on ? v : 0);
+            dd a = ld(&nacc[on ? v : 0]);
+            if (!one) {
+                const Piv f = factor_at(m, S);
+                if (inc) a = dd_neg(dd_mul(a, dd_mul(f.i0, f.i1)));
+                double2 *q = buf + node_at(lane & (nodes - 1));
+                for (int j = lane >> L; j < S; j += 64 >> L) {
+                    const Piv g = factor_at(q, S);
+                    make_y(q, S, j, g);
+                }
+                __syncthreads();
+            }
+            dd tot = dd_make(0.0);
+            double ab = 0.0;
+            if (on) {
+                if (S <= 2) {
+                    if (S == 2) {
+                        dd A[ex_e(2)];
+                        load_node<2>(A, m, inc, one);
+                        walk<2>(A, a, tot, ab);
+                    } else {
+                        dd A[ex_e(1)];
+                        load_node<1>(A, m, inc, one);
+                        walk<1>(A, a, tot, ab);
+                    }
+                } else if constexpr (!SMALL) {
+                    // (R = 9 walks three modes, R = 10 four: the first of these
+                    // included, then not)
+                    dd A[ex_e(EX_S)], B[ex_e(EX_S - 1)];
+                    dd aa = a;
+                    if (S == EX_S) {
+                        load_node<EX_S>(A, m, inc, one);
+                        aa = dd_mul(a, step<EX_S>(A, B));
+                    } else {
+                        load_node<EX_S - 1>(B, m, inc, one);
+                    }
+#pragma unroll 1
+                    for (int half = S == EX_S ? 2 : 1; half > 0; --half) {
+                        walk<EX_S - 1>(B, aa, tot, ab);
+#pragma unroll
+                        for (int e = 0; e < ex_e(EX_S - 1); ++e) B[e] = A[e];
+                        aa = a;
+                    }
                 }
             }
+            rtot = dd_add(rtot, quick_two_sum(tot.hi, tot.lo));
+            rab += ab;
             __syncthreads();
-            cur ^= 1;
-            nc ^= 1;
-            --k;
         }
-        // leaves: one node per lane
-        dd tot = dd_make(0.0);
-        double ab = 0.0;
-        const int leaves = 1 << m;
-        if (lane < leaves) {
-            Buf src = cur ? B1 : B0;
-            const int cs = k * (2 * k + 1);
-            dd a = dd{nacc_h[nc][lane], nacc_l[nc][lane]};
-            const int par = (n + npar[nc][lane]) & 1;
-            if (sl == 3) leaf<3>(src, lane * cs, a, par, tot, ab);
-            else if (sl == 2) leaf<2>(src, lane * cs, a, par, tot, ab);
-            else if (sl == 1) leaf<1>(src, lane * cs, a, par, tot, ab);
-            else {
-                tot = (par & 1) ? dd_neg(a) : a;  // n = 0: the empty set only
-                ab = fabs(a.hi);
-            }
-        }
-        tot = wave_dd_sum(tot);
-        for (int mm = 32; mm > 0; mm >>= 1) ab += __shfl_xor(ab, mm);
-        rtot = dd_add(rtot, tot);
-        rab += ab;
-        __syncthreads();
     }
+    rtot = wave_dd_sum(rtot);
+    for (int mm = 32; mm > 0; mm >>= 1) rab += __shfl_xor(rab, mm);
     if (lane == 0) {
         part[3 * item] = rtot.hi;
         part[3 * item + 1] = rtot.lo;
@@ -342,38 +451,40 @@ __global__ __launch_bounds__(64) void k_exact(int M, const double *__restrict__ 
     }
 }
 
-// Per row: the CSR check, the fixed-order sum of the item partials, times
-// det(Q)^{-1/2}.  Outputs: p, status (required), logp, kappa (nullable).
-__global__ void k_exact_final(int P, int M, const int *__restrict__ offsets, const int *__restrict__ modes,
-                              int lgS, int maxn, const double *__restrict__ part,
-                              const double *__restrict__ scal, double *__restrict__ p_out,
-                              double *__restrict__ logp_out, double *__restrict__ kappa_out,
-                              int *__restrict__ status_out)
+// Per row (one wavefront): the CSR check, the fixed-order sum of the parts,
+// times det(Q)^{-1/2}.  Outputs: p, status (required), logp, kappa (nullable).
+__global__ __launch_bounds__(256) void k_exact_final(int P, int M, const int *__restrict__ offsets,
+                                                     const int *__restrict__ modes, int lgG, int maxn,
+                                                     const double *__restrict__ part,
+                                                     const double *__restrict__ scal, double *__restrict__ p_out,
+                                                     double *__restrict__ logp_out, double *__restrict__ kappa_out,
+                                                     int *__restrict__ status_out)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= P) return;
     const int o = offsets[p], n = offsets[p + 1] - o;
-    bool bad = n < 0 || n > maxn;
-    for (int i = 0; i < n && !bad; ++i) {
-        const int m = modes[o + i];
-        bad = m < 0 || m >= M || (i > 0 && m <= modes[o + i - 1]);
-    }
-    if (bad) {
-        p_out[p] = NAN;
-        if (logp_out) logp_out[p] = NAN;
-        if (kappa_out) kappa_out[p] = NAN;
-        status_out[p] = GBS_PS_BADROW;
+    if (n < 0 || n > maxn || !wave_row_ok(modes + o, n, M, lane)) {
+        if (lane == 0) {
+            p_out[p] = NAN;
+            if (logp_out) logp_out[p] = NAN;
+            if (kappa_out) kappa_out[p] = NAN;
+            status_out[p] = GBS_PS_BADROW;
+        }
         return;
     }
     const int h = n > EX_R ? n - EX_R : 0;
-    const int ni = 1 << (h < EX_LGI ? h : EX_LGI);
-    const long long i0 = (long long)p << lgS;
+    const int ni = 1 << (h < lgG ? h : lgG);
+    const long long i0 = (long long)p << lgG;
     dd s = dd_make(0.0);
     double ab = 0.0;
-    for (int i = 0; i < ni; ++i) {
-        s = dd_add(s, dd{part[3 * (i0 + i)], part[3 * (i0 + i) + 1]});
-        ab += part[3 * (i0 + i) + 2];
-    }
+    if (n > 0)
+        for (int i = lane; i < ni; i += 64) {
+            s = dd_add(s, dd{part[3 * (i0 + i)], part[3 * (i0 + i) + 1]});
+            ab += part[3 * (i0 + i) + 2];
+        }
+    s = wave_dd_sum(s);
+    for (int mm = 32; mm > 0; mm >>= 1) ab += __shfl_xor(ab, mm);
+    if (lane != 0) return;
     if (n == 0) {
         s = dd_make(1.0);
         ab = 1.0;
@@ -393,31 +504,48 @@ __global__ void k_exact_final(int P, int M, const int *__restrict__ offsets, con
 
 }  // namespace
 
-// work items of a batch whose rows hold at most maxn clicks: P << exact_lgs(maxn)
+// Partial sums that a batch of rows of at most maxn clicks may take:
+// P << exact_lgs(maxn) (the size of the buffers and the limit of the fixed one)
 int exact_lgs(int maxn)
 {
-    const int h = maxn > EX_R ? maxn - EX_R : 0;
+    const int h = maxn > 9 ? maxn - 9 : 0;
     return h < EX_LGI ? h : EX_LGI;
 }
 
-// The exact path on device CSR: partials in d_part (3 doubles per work item,
-// at least P << exact_lgs(maxn) items), results into the device outputs.
+// Parts per row, 2^lg: enough for about 2^14 work items (1024 run at a time; the
+// rows' unequal shares then even out, while the blocks of short rows that find
+// nothing to do cost 7 ns each: 4096 rows of 6-14 clicks take 764, 752, 939 and
+// 1430 us with 2^13 .. 2^16 items, model build included), at most one per prefix
+// assignment and 2^EX_LGI, and for large batches of long rows no fewer than
+// leave a part 2^14 assignments (half a second).
+static int exact_lgg(int P, int maxn)
+{
+    const int h = maxn > EX_R ? maxn - EX_R : 0, most = std::min(h, EX_LGI);
+    int lgP = 0;
+    while (lgP < 30 && (1LL << lgP) < P) ++lgP;
+    return std::min(most, std::max(14 - lgP, std::max(most - 6, 0)));
+}
+
+// The exact path on device CSR: partials in d_part (3 doubles per part, at
+// least P << exact_lgs(maxn) of them), results into the device outputs.
 int exact_launch(gbs_ctx *ctx, int P, const int32_t *d_off, const int32_t *d_modes, int maxn, double *d_part,
                  double *p_dev, double *logp_dev, double *kappa_dev, int32_t *status_dev)
 {
     if (P == 0) return 0;
     DevModel &m = ctx->model;
     hipStream_t st = ctx->stream;
-    const int lgS = exact_lgs(maxn);
-    const long long nitems = (long long)P << lgS;
-    if (nitems > 0x7fffffffLL) return set_err(ctx, GBS_E_INVAL, "exact: too many work items (rows x 2^12)");
-    const int lds = ex_lds_bytes(maxn);
-    if (int rc = func_lds_limit(ctx, (const void *)k_exact, lds)) return rc;
+    if (((long long)P << exact_lgs(maxn)) > 0x7fffffffLL)
+        return set_err(ctx, GBS_E_INVAL, "exact: too many work items (rows x 2^12)");
+    const int lgG = exact_lgg(P, maxn);
+    const unsigned nitems = (unsigned)P << lgG;
     const int ts = timer_begin(ctx, TG_EXACT);
-    if (maxn > 0)
-        hipLaunchKernelGGL(k_exact, dim3((unsigned)nitems), dim3(64), lds, st, m.M, m.qi_hi, m.qi_lo, d_off,
-                           d_modes, lgS, maxn, d_part);
-    hipLaunchKernelGGL(k_exact_final, dim3((P + 127) / 128), dim3(128), 0, st, P, m.M, d_off, d_modes, lgS, maxn,
+    if (maxn > EX_SMALL)
+        hipLaunchKernelGGL(k_exact<false>, dim3(nitems), dim3(64), 0, st, m.M, m.qi_hi, m.qi_lo, d_off, d_modes,
+                           lgG, maxn, d_part);
+    else if (maxn > 0)
+        hipLaunchKernelGGL(k_exact<true>, dim3(nitems), dim3(64), 0, st, m.M, m.qi_hi, m.qi_lo, d_off, d_modes,
+                           lgG, maxn, d_part);
+    hipLaunchKernelGGL(k_exact_final, dim3((P + 3) / 4), dim3(256), 0, st, P, m.M, d_off, d_modes, lgG, maxn,
                        d_part, m.scal, p_dev, logp_dev, kappa_dev, status_dev);
     timer_end(ctx, ts);
     HIP_TRY(ctx, hipGetLastError());

@@ -261,8 +261,7 @@ int adj_workspace(gbs_ctx *ctx, gbs_plan *pl)
     e = e ? e : dev_alloc(ctx, &pl->d_rscr, rtot);
     e = e ? e : dev_alloc(ctx, &pl->d_qibar, D * D);
     e = e ? e : dev_alloc(ctx, &pl->d_qitmp, D * D);
-    e = e ? e : dev_alloc(ctx, &pl->d_det, 2);
-    if (!pl->d_grad) e = e ? e : dev_alloc(ctx, &pl->d_grad, D);
+    e = e ? e : dev_alloc(ctx, &pl->d_det, 3);
     if (pl->nbig > 0) {
         // larger rows, per workgroup: at order 2 the pair blocks of Z(w) as
         // 16 x 16 planes; otherwise M(w), the pair blocks of Z(w) at order 1 and
@@ -370,7 +369,7 @@ int gbs_set_model(gbs_ctx *ctx, int M, const double *U_re, const double *U_im, c
     HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM, r, M * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM + M, eta, M * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     m.from_params = true;
-    return model_build_dev(ctx, nullptr, true);
+    return model_build_dev(ctx, m.params, m.params + MM, m.params + 2 * MM, m.params + 2 * MM + M, nullptr, true);
 }
 
 int gbs_set_model_dev(gbs_ctx *ctx, int M, const double *U_re_dev, const double *U_im_dev,
@@ -382,14 +381,8 @@ int gbs_set_model_dev(gbs_ctx *ctx, int M, const double *U_re_dev, const double 
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     int rc = model_alloc(ctx, M);
     if (rc) return rc;
-    DevModel &m = ctx->model;
-    size_t MM = (size_t)M * M;
-    HIP_TRY(ctx, hipMemcpyAsync(m.params, U_re_dev, MM * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + MM, U_im_dev, MM * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM, r_dev, M * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM + M, eta_dev, M * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
-    m.from_params = true;
-    return model_build_dev(ctx, nullptr, false);
+    ctx->model.from_params = true;
+    return model_build_dev(ctx, U_re_dev, U_im_dev, r_dev, eta_dev, nullptr, false);
 }
 
 int gbs_set_timing(gbs_ctx *ctx, int on)
@@ -445,7 +438,7 @@ int gbs_set_covariance(gbs_ctx *ctx, int M, const double *sigma)
         return set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
     }
     ctx->model.from_params = false;
-    rc = model_build_dev(ctx, d_sigma, true);
+    rc = model_build_dev(ctx, nullptr, nullptr, nullptr, nullptr, d_sigma, true);
     (void)hipFree(d_sigma);
     return rc;
 }

@@ -3,11 +3,11 @@
 // A value is hi + lo with |lo| <= ulp(hi)/2, ~106 significant bits.  Built from
 // two error-free transformations: Knuth's TwoSum (s + e = a + b exactly) and
 // the product with its rounding error recovered by one fused multiply-add
-// (Dekker 1971 with an FMA in place of the splitting).  Division and square
-// root take an fp64 estimate and one Newton correction in double-double.
-// exp uses argument reduction by ln 2, a further halving, a Taylor series and
-// repeated squaring.  Every function turns floating-point contraction off: a
-// product fused into a later addition would break the error-free steps.
+// (Dekker 1971 with an FMA in place of the splitting).  The square roots take
+// an fp64 estimate and one correction.  exp uses argument reduction by ln 2, a
+// further division by 1024, a Taylor series and repeated squaring.  Every
+// function turns floating-point contraction off: a product fused into a later
+// addition would break the error-free steps.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -91,43 +91,6 @@ __host__ __device__ __forceinline__ dd dd_mul_d(dd x, double b)
     return quick_two_sum(p.hi, p.lo);
 }
 
-// x - y*z
-__host__ __device__ __forceinline__ dd dd_fnma(dd x, dd y, dd z)
-{
-#pragma clang fp contract(off)
-    return dd_sub(x, dd_mul(y, z));
-}
-
-__host__ __device__ __forceinline__ dd dd_div(dd x, dd y)
-{
-#pragma clang fp contract(off)
-    double q1 = x.hi / y.hi;
-    dd r = dd_sub(x, dd_mul_d(y, q1));
-    double q2 = r.hi / y.hi;
-    r = dd_sub(r, dd_mul_d(y, q2));
-    double q3 = r.hi / y.hi;
-    dd q = quick_two_sum(q1, q2);
-    return dd_add_d(q, q3);
-}
-
-__host__ __device__ __forceinline__ dd dd_recip(dd y)
-{
-#pragma clang fp contract(off)
-    return dd_div(dd_make(1.0), y);
-}
-
-// x / b for an fp64 divisor
-__host__ __device__ __forceinline__ dd dd_div_d(dd x, double b)
-{
-#pragma clang fp contract(off)
-    double q1 = x.hi / b;
-    dd r = dd_sub(x, two_prod(q1, b));
-    double q2 = r.hi / b;
-    r = dd_sub(r, two_prod(q2, b));
-    double q3 = r.hi / b;
-    return dd_add_d(quick_two_sum(q1, q2), q3);
-}
-
 // sqrt for x > 0: s = sqrt(hi), then s + (x - s^2) / (2 s).
 __host__ __device__ __forceinline__ dd dd_sqrt(dd x)
 {
@@ -180,22 +143,24 @@ __device__ __forceinline__ dd dd_fms2(dd a, dd p, dd q, dd r, dd s)
     return quick_two_sum(u.hi, lo);
 }
 
-// exp(x) for |x| < 700.  x = k ln2 + r; r' = r / 1024; Taylor to degree 14;
+// exp(x) for |x| < 700.  x = k ln2 + r; r' = r / 1024 (at most 3.4e-4); Taylor to
+// degree 9 (the next term is below 2e-41), coefficients 1/i! as double-doubles;
 // square 10 times; scale by 2^k.
 __host__ __device__ inline dd dd_exp(dd x)
 {
 #pragma clang fp contract(off)
     const dd ln2 = dd{6.93147180559945286227e-01, 2.31904681384629955842e-17};
+    const dd cf[10] = {{1.0, 0.0}, {1.0, 0.0},
+                       {0.5, 0.0}, {0.16666666666666666, 9.25185853854297e-18},
+                       {0.041666666666666664, 2.3129646346357427e-18}, {0.008333333333333333, 1.1564823173178714e-19},
+                       {0.001388888888888889, -5.300543954373577e-20}, {0.0001984126984126984, 1.7209558293420705e-22},
+                       {2.48015873015873e-05, 2.1511947866775882e-23}, {2.7557319223985893e-06, -1.858393274046472e-22}};
     double k = rint(x.hi / ln2.hi);
     dd r = dd_sub(x, dd_mul_d(ln2, k));
     r = dd_mul_d(r, 1.0 / 1024.0);
-    // Horner: sum_{i=0}^{14} r^i / i!
-    dd s = dd_make(1.0);
-    for (int i = 14; i >= 1; --i) {
-        s = dd_div_d(dd_mul(s, r), (double)i);  // s = 1 + s * r / i
-        s = dd_add_d(s, 1.0);
-    }
-    // s now holds 1 + r(1 + r/2(1 + r/3(...))) = exp(r)
+    dd s = cf[9];
+#pragma unroll
+    for (int i = 8; i >= 0; --i) s = dd_add(dd_mul(s, r), cf[i]);
     for (int i = 0; i < 10; ++i) s = dd_mul(s, s);
     double sc = ldexp(1.0, (int)k);
     return dd{s.hi * sc, s.lo * sc};

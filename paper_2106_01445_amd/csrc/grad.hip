@@ -32,8 +32,8 @@
 //   k_adj_reduce   per row: sum of the items' R in a fixed order, the
 //                  contour-independent terms, A_bar = V R V^T, added into the
 //                  adjoint of Q^{-1} at the row's mode pairs (global atomics)
-//   k_adj_model    Q_bar = -(sum w)/2 Q^{-1} - Q^{-1} Psi Q^{-1}, then sigma_bar,
-//                  and the chain to r and eta through the model build
+//   k_adj_model, k_adj_params  Q_bar = -(sum w)/2 Q^{-1} - Q^{-1} Psi Q^{-1}, then
+//                  sigma_bar, and the chain to r and eta through the model build
 #include "contour_common.h"
 
 #include <algorithm>
@@ -1943,9 +1943,60 @@ __global__ __launch_bounds__(256) void k_adj_reduce(int M, const int *__restrict
     }
 }
 
+// One wavefront's 32 x 32 block (bi, bj) of C = A B, A(i, k) at a(i, k) and
+// B(k, j) at b(k, j), n x n, on the matrix cores (zero outside; two tiles share
+// each operand fetch): acc[s][t] holds tile (2 bi + s, 2 bj + t), its element e
+// at row 4e + lane/16, column lane%16.
+template <class FA, class FB>
+__device__ __forceinline__ void gemm_block(int n, int bi, int bj, FA a, FB b, dbl4 (&acc)[2][2], int lane)
+{
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int i0 = 32 * bi + l16, i1 = i0 + 16, j0 = 32 * bj + l16, j1 = j0 + 16;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[s][t] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < n; k0 += 16) {
+        double a0[4], a1[4], b0[4], b1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 4 * u + lq;
+            const bool ok = k < n;
+            a0[u] = ok && i0 < n ? a(i0, k) : 0.0;
+            a1[u] = ok && i1 < n ? a(i1, k) : 0.0;
+            b0[u] = ok && j0 < n ? b(k, j0) : 0.0;
+            b1[u] = ok && j1 < n ? b(k, j1) : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            acc[0][0] = mfma4(a0[u], b0[u], acc[0][0]);
+            acc[0][1] = mfma4(a0[u], b1[u], acc[0][1]);
+            acc[1][0] = mfma4(a1[u], b0[u], acc[1][0]);
+            acc[1][1] = mfma4(a1[u], b1[u], acc[1][1]);
+        }
+    }
+}
+// f(i, j, value) for the block's elements inside n x n
+template <class F>
+__device__ __forceinline__ void gemm_each(int n, int bi, int bj, const dbl4 (&acc)[2][2], int lane, F f)
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = 32 * bi + 16 * s + 4 * e + (lane >> 4), j = 32 * bj + 16 * t + (lane & 15);
+                if (i < n && j < n) f(i, j, acc[s][t][e]);
+            }
+}
+
 // k_adj_reduce for the larger rows (perm[0..nbig)): R and T = R V^T in HBM
-// scratch (2 N^2 per row), A_bar = V T added into Psi.
-__global__ __launch_bounds__(256) void k_adj_reduce_big(int M, const int *__restrict__ offsets,
+// scratch (2 N^2 per row), A_bar = V T (its blocks on and above the diagonal,
+// the others by symmetry) added into Psi.  Both products run on the matrix
+// cores, a wavefront per 32 x 32 block: with a dot product per thread, whose
+// operands are read at a stride, 512 rows of 40-110 clicks took 21.1 ms.
+__global__ __launch_bounds__(512) void k_adj_reduce_big(int M, const int *__restrict__ offsets,
                                                         const int *__restrict__ modes,
                                                         const int *__restrict__ perm,
                                                         const long long *__restrict__ voff,
@@ -1962,7 +2013,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce_big(int M, const int *__rest
                                                         unsigned long long *__restrict__ det)
 {
     __shared__ int g[2 * GBS_MAX_N_APPROX];
-    const int p = perm[blockIdx.x], tid = threadIdx.x, nt = blockDim.x;
+    const int p = perm[blockIdx.x], tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wid = tid >> 6;
     const int o = offsets[p], n = offsets[p + 1] - o, N = 2 * n;
     const RowPlan rp = rows[p];
     const int it0 = row_item0[p];
@@ -1988,93 +2039,113 @@ __global__ __launch_bounds__(256) void k_adj_reduce_big(int M, const int *__rest
         R[(long)j * N + i] = s;
     }
     __syncthreads();
-    for (int idx = tid; idx < N * N; idx += nt) {
-        const int k = idx / N, j = idx - k * N;
-        double s = 0.0;
-        for (int l = 0; l < N; ++l) s = fma(R[(long)k * N + l], Vt[(long)l * N + j], s);
-        T[idx] = s;
+    const int B = (N + 31) / 32;
+    dbl4 acc[2][2];
+    for (int u = wid; u < B * B; u += 8) {
+        gemm_block(N, u / B, u % B, [&](int i, int k) { return R[(long)k * N + i]; },
+                   [&](int k, int j) { return Vt[(long)k * N + j]; }, acc, lane);
+        gemm_each(N, u / B, u % B, acc, lane, [&](int i, int j, double v) { T[(long)i * N + j] = v; });
     }
     __syncthreads();
     const long D = 2L * M;
-    for (int idx = tid; idx < N * N; idx += nt) {
-        const int i = idx / N, j = idx - i * N;
-        double s = 0.0;
-        for (int k = 0; k < N; ++k) s = fma(Vt[(long)k * N + i], T[(long)k * N + j], s);
-        psi_add(psi + g[i] * D + g[j], s, mode, det);
+    for (int u = wid; u < B * (B + 1) / 2; u += 8) {
+        int bi, bj;
+        upper_tile(u, bi, bj);
+        gemm_block(N, bi, bj, [&](int i, int k) { return Vt[(long)k * N + i]; },
+                   [&](int k, int j) { return T[(long)k * N + j]; }, acc, lane);
+        gemm_each(N, bi, bj, acc, lane, [&](int i, int j, double v) {
+            if (i > j) return;
+            psi_add(psi + g[i] * D + g[j], v, mode, det);
+            if (i < j) psi_add(psi + g[j] * D + g[i], v, mode, det);
+        });
     }
 }
 
-// Model adjoint, one workgroup: Q_bar = -(W/2) Q^{-1} - Q^{-1} Psi Q^{-1} with W the
-// sum of w_p over rows with a result; sigma_bar = Q_bar; then through
+// Model adjoint: Q_bar = -(W/2) Q^{-1} - Q^{-1} Psi Q^{-1} with W the sum of w_p over
+// rows with a result; sigma_bar = Q_bar; then through
 // sigma = D sigma0 D + (I - D^2)/2 and sigma0 = O diag(e^{-2r}, e^{2r}) O^T / 2.
-__global__ __launch_bounds__(1024) void k_adj_model(int M, int P, const double *__restrict__ qi,
-                                                    const double *__restrict__ params,
-                                                    const double *__restrict__ dl,
-                                                    const int *__restrict__ status,
-                                                    double *__restrict__ psi, double *__restrict__ tmp,
-                                                    double *__restrict__ grad)
+// Three products of (2M)^2 matrices, a launch each with a wavefront per 32 x 32
+// block on the matrix cores, then a wavefront per mode for r_bar and eta_bar.
+// (In one workgroup, a dot product per thread, this took 74 / 2260 / 6240 /
+// 18000 us at 20 / 70 / 100 / 144 modes.)
+//   stage 0: tmp = Psi Q^{-1}, and W (the last block); 1: psi <- sigma_bar;
+//   2: tmp = sigma0_bar O with sigma0_bar = D sigma_bar D
+__device__ __forceinline__ double o_at(int M, const double *ure, const double *uim, int i, int k)
 {
-    __shared__ double red[1024];
-    const int D = 2 * M, tid = threadIdx.x, nt = blockDim.x;
+    if (i < M) return k < M ? ure[(long)i * M + k] : -uim[(long)i * M + k - M];
+    return k < M ? uim[(long)(i - M) * M + k] : ure[(long)(i - M) * M + k - M];
+}
+
+template <int STAGE>
+__global__ __launch_bounds__(64) void k_adj_model(int M, int P, const double *__restrict__ qi,
+                                                  const double *__restrict__ params,
+                                                  const double *__restrict__ dl,
+                                                  const int *__restrict__ status, double *psi, double *tmp,
+                                                  double *wsum)
+{
+    const int D = 2 * M, B = (D + 31) / 32, lane = threadIdx.x;
+    if (STAGE == 0 && blockIdx.x == (unsigned)(B * B)) {
+        double ws = 0.0;
+#pragma unroll 8
+        for (int p = lane; p < P; p += 64)
+            if ((status[p] & GBS_PS_FAILED) == 0 && isfinite(dl[p])) ws += dl[p];
+        for (int off = 32; off > 0; off >>= 1) ws += __shfl_xor(ws, off);
+        if (lane == 0) *wsum = ws;
+        return;
+    }
+    const int bi = blockIdx.x / B, bj = blockIdx.x % B;
+    const double *ure = params, *uim = params + (long)M * M, *eta = params + 2L * M * M + M;
+    dbl4 acc[2][2];
+    if (STAGE == 0) {
+        gemm_block(D, bi, bj, [&](int i, int k) { return psi[(long)i * D + k]; },
+                   [&](int k, int j) { return qi[(long)k * D + j]; }, acc, lane);
+        gemm_each(D, bi, bj, acc, lane, [&](int i, int j, double v) { tmp[(long)i * D + j] = v; });
+    } else if (STAGE == 1) {
+        const double hw = -0.5 * *wsum;
+        gemm_block(D, bi, bj, [&](int i, int k) { return qi[(long)k * D + i]; },
+                   [&](int k, int j) { return tmp[(long)k * D + j]; }, acc, lane);
+        gemm_each(D, bi, bj, acc, lane,
+                  [&](int i, int j, double v) { psi[(long)i * D + j] = hw * qi[(long)i * D + j] - v; });
+    } else {
+        auto sq = [&](int i) { return sqrt(eta[i < M ? i : i - M]); };
+        gemm_block(D, bi, bj, [&](int i, int k) { return psi[(long)i * D + k] * sq(k); },
+                   [&](int k, int j) { return o_at(M, ure, uim, k, j); }, acc, lane);
+        gemm_each(D, bi, bj, acc, lane, [&](int i, int j, double v) { tmp[(long)i * D + j] = sq(i) * v; });
+    }
+}
+
+// r_bar_j = -e^{-2 r_j} (O^T sigma0_bar O)_{jj} + e^{2 r_j} (O^T sigma0_bar O)_{M+j,M+j};
+// eta_bar_m = (1/eta_m) sum_{i in quads(m)} sum_j sigma0_bar_ij sigma0_ij
+//             - (sigma_bar_{m,m} + sigma_bar_{M+m,M+m}) / 2,
+// with sum_j sigma0_bar_ij sigma0_ij = sum_k O_ik (lambda_k / 2) (sigma0_bar O)_ik,
+// lambda = (e^{-2r}, e^{2r}); one wavefront per mode
+__global__ __launch_bounds__(64) void k_adj_params(int M, const double *__restrict__ params,
+                                                   const double *__restrict__ sbar, const double *__restrict__ tmp,
+                                                   double *__restrict__ grad_r, double *__restrict__ grad_eta)
+{
+    const int D = 2 * M, m = blockIdx.x, lane = threadIdx.x;
     const double *ure = params, *uim = params + (long)M * M;
     const double *r = params + 2L * M * M, *eta = r + M;
-    double ws = 0.0;
-    for (int p = tid; p < P; p += nt)
-        if ((status[p] & GBS_PS_FAILED) == 0 && isfinite(dl[p])) ws += dl[p];
-    ws = block_sum(ws, red);
-    // tmp = Psi Q^{-1}
-    for (int idx = tid; idx < D * D; idx += nt) {
-        const int i = idx / D, j = idx - i * D;
-        double s = 0.0;
-        for (int k = 0; k < D; ++k) s = fma(psi[(long)i * D + k], qi[(long)k * D + j], s);
-        tmp[idx] = s;
+    double bx = 0.0, bp = 0.0, s = 0.0;
+    for (int i = lane; i < D; i += 64) {
+        bx = fma(o_at(M, ure, uim, i, m), tmp[(long)i * D + m], bx);
+        bp = fma(o_at(M, ure, uim, i, M + m), tmp[(long)i * D + M + m], bp);
     }
-    __syncthreads();
-    // psi <- sigma_bar = -(W/2) Q^{-1} - Q^{-1} tmp
-    for (int idx = tid; idx < D * D; idx += nt) {
-        const int i = idx / D, j = idx - i * D;
-        double s = 0.0;
-        for (int k = 0; k < D; ++k) s = fma(qi[(long)i * D + k], tmp[(long)k * D + j], s);
-        psi[idx] = -0.5 * ws * qi[idx] - s;
-    }
-    __syncthreads();
-    auto O = [&](int i, int k) {
-        if (i < M) return k < M ? ure[i * M + k] : -uim[i * M + k - M];
-        return k < M ? uim[(i - M) * M + k] : ure[(i - M) * M + k - M];
-    };
-    auto sq = [&](int i) { return sqrt(eta[i % M]); };
-    // tmp = sigma0_bar O with sigma0_bar = D sigma_bar D
-    for (int idx = tid; idx < D * D; idx += nt) {
-        const int i = idx / D, k = idx - i * D;
-        double s = 0.0;
-        for (int j = 0; j < D; ++j) s = fma(psi[(long)i * D + j] * sq(j), O(j, k), s);
-        tmp[idx] = sq(i) * s;
-    }
-    __syncthreads();
-    // r_bar_j = -e^{-2 r_j} (O^T sigma0_bar O)_{jj} + e^{2 r_j} (O^T sigma0_bar O)_{M+j,M+j}
-    for (int j = tid; j < M; j += nt) {
-        double bx = 0.0, bp = 0.0;
-        for (int i = 0; i < D; ++i) {
-            bx = fma(O(i, j), tmp[(long)i * D + j], bx);
-            bp = fma(O(i, M + j), tmp[(long)i * D + M + j], bp);
+    for (int k = lane; k < M; k += 64) {
+        const double em = 0.5 * exp(-2.0 * r[k]), ep = 0.5 * exp(2.0 * r[k]);
+        for (int i = m; i < D; i += M) {
+            s = fma(o_at(M, ure, uim, i, k) * em, tmp[(long)i * D + k], s);
+            s = fma(o_at(M, ure, uim, i, M + k) * ep, tmp[(long)i * D + M + k], s);
         }
-        grad[j] = -exp(-2.0 * r[j]) * bx + exp(2.0 * r[j]) * bp;
     }
-    __syncthreads();
-    // eta_bar_m = (1/eta_m) sum_{i in quads(m)} sum_j sigma0_bar_ij sigma0_ij
-    //             - (sigma_bar_{m,m} + sigma_bar_{M+m,M+m}) / 2,
-    // with sum_j sigma0_bar_ij sigma0_ij = sum_k O_ik (lambda_k / 2) (sigma0_bar O)_ik,
-    // lambda = (e^{-2r}, e^{2r})
-    for (int m = tid; m < M; m += nt) {
-        double s = 0.0;
-        for (int qd = 0; qd < 2; ++qd) {
-            const int i = m + qd * M;
-            for (int k = 0; k < M; ++k) {
-                s = fma(O(i, k) * (0.5 * exp(-2.0 * r[k])), tmp[(long)i * D + k], s);
-                s = fma(O(i, M + k) * (0.5 * exp(2.0 * r[k])), tmp[(long)i * D + M + k], s);
-            }
-        }
-        grad[M + m] = s / eta[m] - 0.5 * (psi[(long)m * D + m] + psi[(long)(M + m) * D + M + m]);
+    for (int off = 32; off > 0; off >>= 1) {
+        bx += __shfl_xor(bx, off);
+        bp += __shfl_xor(bp, off);
+        s += __shfl_xor(s, off);
+    }
+    if (lane == 0) {
+        grad_r[m] = -exp(-2.0 * r[m]) * bx + exp(2.0 * r[m]) * bp;
+        grad_eta[m] = s / eta[m] - 0.5 * (sbar[(long)m * D + m] + sbar[(long)(M + m) * D + M + m]);
     }
 }
 
@@ -2194,7 +2265,7 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
                                pl->d_roff, pl->d_rscr, pl->d_qibar, mode, pl->d_det);
         }
         if (pl->nbig > 0)
-            hipLaunchKernelGGL(k_adj_reduce_big, dim3(pl->nbig), dim3(256), 0, st, M, pl->d_offsets,
+            hipLaunchKernelGGL(k_adj_reduce_big, dim3(pl->nbig), dim3(512), 0, st, M, pl->d_offsets,
                                pl->d_modes, pl->d_perm, pl->d_voff, pl->d_alpha, pl->d_v, pl->d_rows, dl,
                                status, pl->d_ritem0, pl->d_roff, pl->d_rscr, pl->d_wbig, pl->d_qibar, mode,
                                pl->d_det);
@@ -2204,11 +2275,17 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
                            pl->d_qibar, pl->d_det);
     timer_end(ctx, ts);
     ts = timer_begin(ctx, TG_ADJ_MODEL);
-    hipLaunchKernelGGL(k_adj_model, dim3(1), dim3(1024), 0, st, M, P, m.qi_hi, m.params, dl,
-                       status, pl->d_qibar, pl->d_qitmp, pl->d_grad);
+    const int B = (D + 31) / 32;
+    double *wsum = (double *)(pl->d_det + 2);
+    hipLaunchKernelGGL(k_adj_model<0>, dim3(B * B + 1), dim3(64), 0, st, M, P, m.qi_hi, m.params, dl, status,
+                       pl->d_qibar, pl->d_qitmp, wsum);
+    hipLaunchKernelGGL(k_adj_model<1>, dim3(B * B), dim3(64), 0, st, M, P, m.qi_hi, m.params, dl, status,
+                       pl->d_qibar, pl->d_qitmp, wsum);
+    hipLaunchKernelGGL(k_adj_model<2>, dim3(B * B), dim3(64), 0, st, M, P, m.qi_hi, m.params, dl, status,
+                       pl->d_qibar, pl->d_qitmp, wsum);
+    hipLaunchKernelGGL(k_adj_params, dim3(M), dim3(64), 0, st, M, m.params, pl->d_qibar, pl->d_qitmp, grad_r,
+                       grad_eta);
     timer_end(ctx, ts);
-    HIP_TRY(ctx, hipMemcpyAsync(grad_r, pl->d_grad, M * sizeof(double), hipMemcpyDeviceToDevice, st));
-    HIP_TRY(ctx, hipMemcpyAsync(grad_eta, pl->d_grad + M, M * sizeof(double), hipMemcpyDeviceToDevice, st));
     HIP_TRY(ctx, hipGetLastError());
     return 0;
 }

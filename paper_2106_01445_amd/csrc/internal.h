@@ -46,7 +46,7 @@ struct DevModel {
     bool from_params = false;       // set_model (true) or set_covariance (false)
     double *q_hi = nullptr, *q_lo = nullptr;
     double *qi_hi = nullptr, *qi_lo = nullptr;
-    double *chol_hi = nullptr, *chol_lo = nullptr;  // Cholesky factor L (lower), then scratch
+    double *work_hi = nullptr, *work_lo = nullptr;  // the inversion's work matrix
     double *params = nullptr;       // U_re, U_im (M^2 each), r, eta (M each) on the device
     double *scal = nullptr;         // [0] log det Q, [1..2] det(Q)^{-1/2} as dd, [3] flag (non-PD)
     double *expd = nullptr;         // e^{-2r}, e^{2r} as dd (4M doubles) and sqrt(eta) dd (4M)
@@ -144,7 +144,8 @@ struct gbs_plan {
     // (P + 1) and rows (nnz); the exact path's p and log p (P each)
     int32_t *d_da = nullptr;
     double *d_da_x = nullptr;
-    // deterministic gradients: the largest term into Psi (bit pattern), its scale
+    // deterministic gradients: the largest term into Psi (bit pattern), its scale;
+    // then the sum of the rows' weights (fp64)
     unsigned long long *d_det = nullptr;
     int32_t *d_status = nullptr;          // P
     size_t v_total = 0;
@@ -160,7 +161,7 @@ struct gbs_plan {
     double *d_rscr = nullptr;             // per item: upper triangle of R
     double *d_qibar = nullptr;            // (2M)^2: Psi (adjoint of Q^{-1}), then sigma_bar
     double *d_qitmp = nullptr;            // (2M)^2 scratch
-    double *d_grad = nullptr;             // 2M: grad r, grad eta
+    double *d_grad = nullptr;             // 2M: grad r, grad eta (gbs_grad's own)
     double *d_dl = nullptr;               // P
     cplx *d_ascr = nullptr;               // per-workgroup adjoint scratch of the larger rows
     int ascr_blocks = 0;
@@ -177,7 +178,8 @@ int set_err(gbs_ctx *ctx, int code, const std::string &msg);
     } while (0)
 
 // kernels' host launchers ----------------------------------------------------
-int model_build_dev(gbs_ctx *ctx, const double *sigma_dev, bool sync);
+int model_build_dev(gbs_ctx *ctx, const double *ure, const double *uim, const double *r, const double *eta,
+                    const double *sigma_dev, bool sync);
 int approx_forward(gbs_ctx *ctx, gbs_plan *plan, double *logp_dev, int32_t *status_dev);
 // status_dev[p] |= bits for every row (stream-ordered; NULL status: nothing)
 int status_or(gbs_ctx *ctx, int P, int32_t *status_dev, int bits);

@@ -3,10 +3,26 @@
 //   sigma = D O diag(e^{-2r}, e^{2r}) O^T D / 2 + (I - D^2)/2,   Q = sigma + I/2
 //   O = [[Re U, -Im U], [Im U, Re U]],  D = diag(sqrt eta, sqrt eta)
 //
-// Q is factored Q = L L^T (one workgroup, right-looking), inverted column by
-// column from L (one workgroup per column) and log det Q, det(Q)^{-1/2} kept.
-// Everything stays in HBM as hi/lo fp64 planes, row-major (2M)^2, xxpp order.
+// Q is inverted by symmetric Gauss-Jordan sweeps over blocks of 16 rows, one
+// launch per block, every 16 x 16 tile a workgroup: with P the block's own tile,
+//   A_ss <- -P^{-1},  A_is <- A_is P^{-1},  A_ij <- A_ij - A_is P^{-1} A_sj,
+// after the last block -Q^{-1}.  The pivots d_k met inside the blocks give
+// positive definiteness, log det Q = sum log d_k and det(Q)^{-1/2} =
+// prod d_k^{-1/2}.  Everything stays in HBM as hi/lo fp64 planes, row-major
+// (2M)^2, xxpp order.
+//
+// What bounds it: the chain of 2M pivots (a double-double reciprocal, a product
+// and a barrier each, about 0.35 us), which every workgroup of a launch walks
+// for itself so that no other launch stands between the blocks.  Blocks of 16
+// keep the tiles' products (2 x 16 terms per entry) below that chain.  Against
+// a column-by-column Cholesky factor in one workgroup and a pair of triangular
+// solves per column of the inverse, the inversion takes 9 / 30 / 91 / 220 us
+// instead of 38 / 101 / 1160 / 8040 at M = 8 / 20 / 70 / 144 (a launch per block
+// is 9 to 12 us), and the assembly of Q 3 / 8 / 17 / 30 instead of
+// 9 / 19 / 68 / 157.
 #include "internal.h"
+
+#define SWB 16
 
 namespace {
 
@@ -20,23 +36,35 @@ __device__ __forceinline__ void st_dd(double *hi, double *lo, long i, dd v)
     lo[i] = v.lo;
 }
 
-// e^{-2 r_k}, e^{2 r_k} (dd) and sqrt(eta_k) (dd).  Layout of expd:
+// The caller's U, r, eta into the model's own copy (where they are not there
+// already), and e^{-2 r_k}, e^{2 r_k} (dd) and sqrt(eta_k) (dd).  Layout of expd:
 // [0,2M) hi of d, [2M,4M) lo of d, [4M,5M) hi of s, [5M,6M) lo of s.
-__global__ void k_model_scalars(int M, const double *__restrict__ r,
-                                const double *__restrict__ eta, double *__restrict__ expd)
+__global__ void k_model_scalars(int M, const double *ure, const double *uim, const double *r, const double *eta,
+                                double *params, double *__restrict__ expd)
 {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= M) return;
-    dd em = dd_exp(dd_make(-2.0 * r[k]));
-    dd ep = dd_exp(dd_make(2.0 * r[k]));
-    dd s = eta[k] > 0.0 ? dd_sqrt(dd_make(eta[k])) : dd_make(0.0);
-    int D = 2 * M;
-    expd[k] = em.hi;
-    expd[D + k] = em.lo;
-    expd[M + k] = ep.hi;
-    expd[D + M + k] = ep.lo;
-    expd[2 * D + k] = s.hi;
-    expd[2 * D + M + k] = s.lo;
+    const int k = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    if (k < M) {
+        const double rk = r[k], ek = eta[k];
+        dd em = dd_exp(dd_make(-2.0 * rk));
+        dd ep = dd_exp(dd_make(2.0 * rk));
+        dd s = ek > 0.0 ? dd_sqrt(dd_make(ek)) : dd_make(0.0);
+        int D = 2 * M;
+        expd[k] = em.hi;
+        expd[D + k] = em.lo;
+        expd[M + k] = ep.hi;
+        expd[D + M + k] = ep.lo;
+        expd[2 * D + k] = s.hi;
+        expd[2 * D + M + k] = s.lo;
+        if (ure != params) {
+            params[2 * M * M + k] = rk;
+            params[2 * M * M + M + k] = ek;
+        }
+    }
+    if (ure != params)
+        for (int i = k; i < M * M; i += nt) {
+            params[i] = ure[i];
+            params[M * M + i] = uim[i];
+        }
 }
 
 __device__ __forceinline__ double o_entry(int M, const double *ure, const double *uim, int i,
@@ -46,144 +74,176 @@ __device__ __forceinline__ double o_entry(int M, const double *ure, const double
     return k < M ? uim[(i - M) * M + k] : ure[(i - M) * M + k - M];
 }
 
-// One thread per entry (i, j) of Q.
-__global__ void k_build_q(int M, const double *__restrict__ ure, const double *__restrict__ uim,
-                          const double *__restrict__ eta, const double *__restrict__ expd,
-                          const double *__restrict__ sigma, double *__restrict__ q_hi,
-                          double *__restrict__ q_lo)
+// One 16 x 16 tile (ti >= tj) of Q per workgroup, one entry per thread, written
+// with its mirror image; the rows of O and of O diag(e^{-2r}, e^{2r}) staged in
+// LDS 16 columns at a time.
+__global__ __launch_bounds__(256) void k_build_q(int M, const double *__restrict__ ure,
+                                                 const double *__restrict__ uim,
+                                                 const double *__restrict__ eta, const double *__restrict__ expd,
+                                                 const double *__restrict__ sigma, double *__restrict__ q_hi,
+                                                 double *__restrict__ q_lo)
 {
-    int D = 2 * M;
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    int i = blockIdx.y;
-    if (j >= D || i >= D) return;
-    dd q;
+    const int ti = blockIdx.x, tj = blockIdx.y;
+    if (ti < tj) return;
+    __shared__ double oa[SWB][SWB + 1];
+    __shared__ double2 ob[SWB][SWB + 1];
+    const int D = 2 * M, r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    const int i = ti * SWB + r, j = tj * SWB + c;
+    dd q = dd_make(0.0);
     if (sigma) {
-        q = dd_make(sigma[(long)i * D + j]);
-        if (i == j) q = dd_add_d(q, 0.5);
+        if (i < D && j < D) {
+            q = dd_make(sigma[(long)i * D + j]);
+            if (i == j) q = dd_add_d(q, 0.5);
+        }
     } else {
         dd acc = dd_make(0.0);
-        for (int k = 0; k < D; ++k) {
-            double a = o_entry(M, ure, uim, i, k);
-            double b = o_entry(M, ure, uim, j, k);
-            if (a == 0.0 || b == 0.0) continue;
-            dd t = dd_mul(two_prod(a, b), dd{expd[k], expd[D + k]});
-            acc = dd_add(acc, t);
+        const int jr = tj * SWB + r;  // (this thread stages row r of either side)
+        for (int k0 = 0; k0 < D; k0 += SWB) {
+            const int k = k0 + c;
+            const bool kok = k < D;
+            oa[r][c] = kok && i < D ? o_entry(M, ure, uim, i, k) : 0.0;
+            const dd b = dd_mul_d(dd{kok ? expd[k] : 0.0, kok ? expd[D + k] : 0.0},
+                                  kok && jr < D ? o_entry(M, ure, uim, jr, k) : 0.0);
+            ob[r][c] = make_double2(b.hi, b.lo);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < SWB; ++t) {
+                // (error-free leading product and sum; what is below them in one
+                // fp64 sum, folded back once per 16 terms)
+                const double a = oa[r][t];
+                const double2 v = ob[c][t];
+                const dd f = two_prod(a, v.x);
+                const dd s = two_sum(acc.hi, f.hi);
+                acc.hi = s.hi;
+                acc.lo += s.lo + fma(a, v.y, f.lo);
+            }
+            acc = quick_two_sum(acc.hi, acc.lo);
+            __syncthreads();
         }
-        acc = dd_mul_d(acc, 0.5);
-        dd si = dd{expd[2 * D + (i % M)], expd[2 * D + M + (i % M)]};
-        dd sj = dd{expd[2 * D + (j % M)], expd[2 * D + M + (j % M)]};
-        q = dd_mul(dd_mul(acc, si), sj);
-        // diagonal: (1 - eta)/2 from the loss channel plus 1/2 = 1 - eta/2
-        if (i == j) q = dd_add(q, two_sum(1.0, -0.5 * eta[i % M]));
+        if (i < D && j < D) {
+            acc = dd_mul_d(acc, 0.5);
+            dd si = dd{expd[2 * D + (i % M)], expd[2 * D + M + (i % M)]};
+            dd sj = dd{expd[2 * D + (j % M)], expd[2 * D + M + (j % M)]};
+            q = dd_mul(dd_mul(acc, si), sj);
+            // diagonal: (1 - eta)/2 from the loss channel plus 1/2 = 1 - eta/2
+            if (i == j) q = dd_add(q, two_sum(1.0, -0.5 * eta[i % M]));
+        }
     }
-    st_dd(q_hi, q_lo, (long)i * D + j, q);
+    if (i < D && j <= i) {
+        st_dd(q_hi, q_lo, (long)i * D + j, q);
+        if (i != j) st_dd(q_hi, q_lo, (long)j * D + i, q);
+    }
 }
 
-// In-place right-looking Cholesky in one workgroup.  scal: [0] log det Q,
-// [1],[2] det(Q)^{-1/2} (dd), [3] 1 if not positive definite,
-// [8 .. 8+2D) 1/L_jj as dd (hi then lo planes).
-__global__ void k_chol(int D, double *__restrict__ l_hi, double *__restrict__ l_lo,
-                       double *__restrict__ scal)
+__device__ __forceinline__ dd wave_dd_prod(dd v)
 {
-    __shared__ double s_inv_hi, s_inv_lo;
-    __shared__ int s_bad;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    double logdet = 0.0;
-    dd rdet = dd_make(1.0);
-    if (tid == 0) s_bad = 0;
+    for (int m = 32; m > 0; m >>= 1) v = dd_mul(v, dd{__shfl_xor(v.hi, m), __shfl_xor(v.lo, m)});
+    return v;
+}
+
+// One sweep over block s, from src to dst (both full; a workgroup per tile
+// ti >= tj, one entry per thread, written with its mirror image; rows past 2M
+// act as rows of the identity).  scal: [0] log det Q, [1],[2] det(Q)^{-1/2}
+// (dd), [3] 1 if not positive definite (dst is then the identity after the last
+// block, so that no later kernel meets what the sweeps left), [8 .. 8+2D) the
+// pivots as dd (hi then lo planes).
+__global__ __launch_bounds__(256) void k_sweep(int D, int s, int last, const double *__restrict__ s_hi,
+                                               const double *__restrict__ s_lo, double *__restrict__ d_hi,
+                                               double *__restrict__ d_lo, double *__restrict__ scal)
+{
+    const int ti = blockIdx.x, tj = blockIdx.y;
+    if (ti < tj) return;
+    __shared__ double2 col[2][SWB], inv[SWB][SWB + 1], ais[SWB][SWB + 1], ajs[SWB][SWB + 1], prod[SWB][SWB + 1];
+    __shared__ double2 piv[SWB];
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    const int i = ti * SWB + r, j = tj * SWB + c;
+    bool bad = s > 0 && scal[3] != 0.0;
+    auto at = [&](int a, int b) {
+        if (a < D && b < D) return ld_dd(s_hi, s_lo, (long)a * D + b);
+        return dd_make(a == b ? 1.0 : 0.0);
+    };
+    const int sr = s * SWB + r, sc = s * SWB + c;
+    dd p = at(sr, sc);
+    const dd mine = at(i, j), vi = at(i, sc), vj = at(tj * SWB + r, sc);
+    ais[r][c] = make_double2(vi.hi, vi.lo);
+    ajs[r][c] = make_double2(vj.hi, vj.lo);
+    if (c == 0) col[0][r] = make_double2(p.hi, p.lo);
     __syncthreads();
-    for (int j = 0; j < D; ++j) {
-        if (tid == 0) {
-            dd piv = ld_dd(l_hi, l_lo, (long)j * D + j);
-            if (!(piv.hi > 0.0)) {
-                s_bad = 1;
-            } else {
-                dd l = dd_sqrt(piv);
-                dd inv = dd_recip(l);
-                st_dd(l_hi, l_lo, (long)j * D + j, l);
-                s_inv_hi = inv.hi;
-                s_inv_lo = inv.lo;
-                scal[8 + j] = inv.hi;
-                scal[8 + D + j] = inv.lo;
-                logdet += 2.0 * (log(l.hi) + l.lo / l.hi);
-                rdet = dd_mul(rdet, inv);
+    // P by single sweeps, its column k passed on through LDS
+#pragma unroll 1
+    for (int k = 0; k < SWB; ++k) {
+        const double2 *cl = col[k & 1];
+        const double2 dv = cl[k], cr = cl[r], cc = cl[c];
+        const dd d = dd{dv.x, dv.y}, ac = dd{cc.x, cc.y};
+        bad = bad || !(d.hi > 0.0);
+        // 1/d: the fp64 value y and y e, e = 1 - d y
+        const double y = 1.0 / d.hi;
+        const double e = fma(-d.lo, y, fma(-d.hi, y, 1.0));
+        const dd id = quick_two_sum(y, y * fma(e, e, e));
+        const dd t = dd_mul(r == k ? ac : dd{cr.x, cr.y}, id);
+        if (r == k && c == k)
+            p = dd_neg(id);
+        else if (r == k || c == k)
+            p = t;
+        else
+            p = dd_fms(p, t, ac);
+        if (threadIdx.x == 0) piv[k] = dv;
+        if (c == k + 1) col[(k + 1) & 1][r] = make_double2(p.hi, p.lo);
+        __syncthreads();
+    }
+    inv[r][c] = make_double2(-p.hi, -p.lo);
+    __syncthreads();
+    auto get = [](const double2 &v) { return dd{v.x, v.y}; };
+    dd out;
+    if (ti == s && tj == s) {
+        out = p;
+    } else {
+        // the block's row or column: P^{-1} A_sj = (A_js P^{-1})^T, or A_is P^{-1}
+        const bool row = ti == s;
+        dd acc = dd_make(0.0);
+#pragma unroll 4
+        for (int k = 0; k < SWB; k += 2)
+            acc = row ? dd_fms2(acc, get(inv[r][k]), get(ajs[c][k]), get(inv[r][k + 1]), get(ajs[c][k + 1]))
+                      : dd_fms2(acc, get(ais[r][k]), get(inv[c][k]), get(ais[r][k + 1]), get(inv[c][k + 1]));
+        out = dd_neg(acc);
+        if (ti != s && tj != s) {
+            prod[r][c] = make_double2(out.hi, out.lo);
+            __syncthreads();
+            acc = mine;
+#pragma unroll 4
+            for (int k = 0; k < SWB; k += 2)
+                acc = dd_fms2(acc, get(prod[r][k]), get(ajs[c][k]), get(prod[r][k + 1]), get(ajs[c][k + 1]));
+            out = acc;
+        }
+    }
+    if (last) out = bad ? dd_make(i == j ? 1.0 : 0.0) : dd_neg(out);
+    if (i < D && j <= i) {
+        st_dd(d_hi, d_lo, (long)i * D + j, out);
+        if (i != j) st_dd(d_hi, d_lo, (long)j * D + i, out);
+    }
+    if (ti == s && tj == s && threadIdx.x < 64) {
+        const int lane = threadIdx.x, n0 = s * SWB;
+        if (lane < SWB && n0 + lane < D) {
+            scal[8 + n0 + lane] = piv[lane].x;
+            scal[8 + D + n0 + lane] = piv[lane].y;
+        }
+        if (lane == 0 && (bad || s == 0)) scal[3] = bad ? 1.0 : 0.0;
+        if (last) {
+            double ld = 0.0;
+            dd rd = dd_make(1.0);
+            for (int k = lane; k < D; k += 64) {
+                const dd d = k < n0 ? dd{scal[8 + k], scal[8 + D + k]} : get(piv[k - n0]);
+                ld += log(d.hi) + d.lo / d.hi;
+                rd = dd_mul(rd, dd_rsqrt(d));
+            }
+            for (int m = 32; m > 0; m >>= 1) ld += __shfl_xor(ld, m);
+            rd = wave_dd_prod(rd);
+            if (lane == 0) {
+                scal[0] = ld;
+                scal[1] = rd.hi;
+                scal[2] = rd.lo;
             }
         }
-        __syncthreads();
-        if (s_bad) break;
-        dd inv = dd{s_inv_hi, s_inv_lo};
-        for (int i = j + 1 + tid; i < D; i += nt) {
-            long ij = (long)i * D + j;
-            st_dd(l_hi, l_lo, ij, dd_mul(ld_dd(l_hi, l_lo, ij), inv));
-        }
-        __syncthreads();
-        int m = D - j - 1;
-        for (int idx = tid; idx < m * m; idx += nt) {
-            int ii = idx / m, kk = idx - ii * m;
-            if (kk > ii) continue;
-            int i = j + 1 + ii, k = j + 1 + kk;
-            dd lij = ld_dd(l_hi, l_lo, (long)i * D + j);
-            dd lkj = ld_dd(l_hi, l_lo, (long)k * D + j);
-            long ik = (long)i * D + k;
-            st_dd(l_hi, l_lo, ik, dd_sub(ld_dd(l_hi, l_lo, ik), dd_mul(lij, lkj)));
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        scal[0] = logdet;
-        scal[1] = rdet.hi;
-        scal[2] = rdet.lo;
-        scal[3] = s_bad ? 1.0 : 0.0;
-    }
-}
-
-// Column j of Q^{-1} = L^{-T} L^{-1} e_j, one 64-lane workgroup per column.
-__global__ void k_chol_inv(int D, const double *__restrict__ l_hi, const double *__restrict__ l_lo,
-                           const double *__restrict__ scal, double *__restrict__ qi_hi,
-                           double *__restrict__ qi_lo)
-{
-    extern __shared__ double sh[];
-    double *b_hi = sh, *b_lo = sh + D;
-    const int j = blockIdx.x, lane = threadIdx.x, nt = blockDim.x;
-    if (scal[3] != 0.0) return;
-    for (int i = lane; i < D; i += nt) {
-        b_hi[i] = (i == j) ? 1.0 : 0.0;
-        b_lo[i] = 0.0;
-    }
-    __syncthreads();
-    // forward: L y = e_j  (y_i = 0 for i < j)
-    for (int k = j; k < D; ++k) {
-        dd yk = dd_mul(dd{b_hi[k], b_lo[k]}, dd{scal[8 + k], scal[8 + D + k]});
-        __syncthreads();
-        for (int i = k + 1 + lane; i < D; i += nt) {
-            dd v = dd_sub(dd{b_hi[i], b_lo[i]}, dd_mul(ld_dd(l_hi, l_lo, (long)i * D + k), yk));
-            b_hi[i] = v.hi;
-            b_lo[i] = v.lo;
-        }
-        if (lane == 0) {
-            b_hi[k] = yk.hi;
-            b_lo[k] = yk.lo;
-        }
-        __syncthreads();
-    }
-    // backward: L^T x = y
-    for (int k = D - 1; k >= 0; --k) {
-        dd xk = dd_mul(dd{b_hi[k], b_lo[k]}, dd{scal[8 + k], scal[8 + D + k]});
-        __syncthreads();
-        for (int i = lane; i < k; i += nt) {
-            dd v = dd_sub(dd{b_hi[i], b_lo[i]}, dd_mul(ld_dd(l_hi, l_lo, (long)k * D + i), xk));
-            b_hi[i] = v.hi;
-            b_lo[i] = v.lo;
-        }
-        if (lane == 0) {
-            b_hi[k] = xk.hi;
-            b_lo[k] = xk.lo;
-        }
-        __syncthreads();
-    }
-    for (int i = lane; i < D; i += nt) {
-        qi_hi[(long)i * D + j] = b_hi[i];
-        qi_lo[(long)i * D + j] = b_lo[i];
     }
 }
 
@@ -191,7 +251,7 @@ __global__ void k_chol_inv(int D, const double *__restrict__ l_hi, const double 
 
 static void free_model(DevModel &m)
 {
-    double **ptrs[] = {&m.q_hi, &m.q_lo, &m.qi_hi, &m.qi_lo, &m.chol_hi, &m.chol_lo,
+    double **ptrs[] = {&m.q_hi, &m.q_lo, &m.qi_hi, &m.qi_lo, &m.work_hi, &m.work_lo,
                        &m.params, &m.scal, &m.expd};
     for (double **p : ptrs) {
         if (*p) (void)hipFree(*p);
@@ -208,7 +268,7 @@ int model_alloc(gbs_ctx *ctx, int M)
     m.M = M;
     m.have = false;
     size_t D = 2 * (size_t)M, DD = D * D * sizeof(double);
-    double **mats[] = {&m.q_hi, &m.q_lo, &m.qi_hi, &m.qi_lo, &m.chol_hi, &m.chol_lo};
+    double **mats[] = {&m.q_hi, &m.q_lo, &m.qi_hi, &m.qi_lo, &m.work_hi, &m.work_lo};
     for (double **p : mats)
         if (hipMalloc((void **)p, DD) != hipSuccess) {
             free_model(m);
@@ -227,29 +287,32 @@ int model_alloc(gbs_ctx *ctx, int M)
 
 void model_release(gbs_ctx *ctx) { free_model(ctx->model); ctx->model.M = 0; }
 
-// Build Q, its factor and inverse.  Parameters must already be in
-// ctx->model.params (U_re, U_im, r, eta) unless sigma_dev is given.
-int model_build_dev(gbs_ctx *ctx, const double *sigma_dev, bool sync)
+// Build Q and its inverse.  ure, uim, r, eta: device arrays (the model's own
+// copy ctx->model.params, or the caller's, which are copied there), ignored
+// where sigma_dev is given.
+int model_build_dev(gbs_ctx *ctx, const double *ure, const double *uim, const double *r, const double *eta,
+                    const double *sigma_dev, bool sync)
 {
     DevModel &m = ctx->model;
     int M = m.M, D = 2 * M;
     hipStream_t st = ctx->stream;
-    const double *ure = m.params, *uim = m.params + (size_t)M * M;
-    const double *r = m.params + 2 * (size_t)M * M, *eta = r + M;
     const int tslot = timer_begin(ctx, TG_MODEL);
-    if (!sigma_dev) {
-        hipLaunchKernelGGL(k_model_scalars, dim3((M + 63) / 64), dim3(64), 0, st, M, r, eta,
+    if (!sigma_dev)
+        hipLaunchKernelGGL(k_model_scalars, dim3((M * M + 255) / 256), dim3(256), 0, st, M, ure, uim, r, eta, m.params,
                            m.expd);
+    const int T = (D + SWB - 1) / SWB;
+    hipLaunchKernelGGL(k_build_q, dim3(T, T), dim3(256), 0, st, M, m.params, m.params + (size_t)M * M,
+                       m.params + 2 * (size_t)M * M + M, m.expd, sigma_dev, m.q_hi, m.q_lo);
+    // (the sweeps go back and forth between the work matrix and Q^{-1}'s place,
+    // the last one into the latter)
+    const double *sh = m.q_hi, *sl = m.q_lo;
+    for (int s = 0; s < T; ++s) {
+        const bool home = ((T - 1 - s) & 1) == 0;
+        double *dh = home ? m.qi_hi : m.work_hi, *dl = home ? m.qi_lo : m.work_lo;
+        hipLaunchKernelGGL(k_sweep, dim3(T, T), dim3(256), 0, st, D, s, s == T - 1, sh, sl, dh, dl, m.scal);
+        sh = dh;
+        sl = dl;
     }
-    hipLaunchKernelGGL(k_build_q, dim3((D + 127) / 128, D), dim3(128), 0, st, M, ure, uim, eta,
-                       m.expd, sigma_dev, m.q_hi, m.q_lo);
-    HIP_TRY(ctx, hipMemcpyAsync(m.chol_hi, m.q_hi, (size_t)D * D * sizeof(double),
-                                hipMemcpyDeviceToDevice, st));
-    HIP_TRY(ctx, hipMemcpyAsync(m.chol_lo, m.q_lo, (size_t)D * D * sizeof(double),
-                                hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_chol, dim3(1), dim3(1024), 0, st, D, m.chol_hi, m.chol_lo, m.scal);
-    hipLaunchKernelGGL(k_chol_inv, dim3(D), dim3(64), 2 * D * sizeof(double), st, D, m.chol_hi,
-                       m.chol_lo, m.scal, m.qi_hi, m.qi_lo);
     timer_end(ctx, tslot);
     HIP_TRY(ctx, hipGetLastError());
     if (!sync) {

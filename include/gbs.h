@@ -404,8 +404,8 @@ int gbs_mcmc_da_step_dev(gbs_ctx *ctx, gbs_plan *plan, const double *u_dev, int3
  * synchronises the stream, writes the summed milliseconds per kernel group
  * since the last call into ms[GBS_TIMING_GROUPS] and the launch counts into
  * count[GBS_TIMING_GROUPS] (0 model build, 1 row set-up, 2 work-queue build,
- * 3 contour/cluster, 4 DFT and fit, 5 exact subsets, 6 adjoint of the fit and
- * DFT, 7 adjoint of the contour/cluster step, 8 adjoint per row and its
+ * 3 contour/cluster, 4 DFT and fit, in a gradient call with its adjoint, 5 exact
+ * subsets, 6 unused, 7 adjoint of the contour/cluster step, 8 adjoint per row and its
  * scatter into the mode pairs, 9 adjoint of the model build, 10 the second
  * pass of a forward call: re-tilted and escalated rows, their contour and
  * fits), then clears the record.  Either array may be NULL. */

@@ -15,8 +15,9 @@
 //                  2x2-block elimination with one principal square root per
 //                  block (each block's determinant lies off the negative axis);
 //                  the results, times G_0(w)/G_0(rho), go to HBM
-//   k_dft_fit      one workgroup per row: sector moments by a direct DFT over the
-//                  contour, one max-entropy fit per sector, log-sum over sectors
+//   k_dft_fit      one workgroup per row: sector moments by a DFT over the contour,
+//                  one max-entropy fit per sector, log-sum over sectors; in a
+//                  gradient call also their adjoint back to the contour values
 #include "contour_common.h"
 
 
@@ -526,8 +527,19 @@ __global__ __launch_bounds__(CONT_THREADS) void k_contour(
 }
 
 // ---------------------------------------------------------------------------
-// k_dft_fit: sector moments, fits, log-sum, and the estimated rounding error of
-// the result.
+// k_dft_fit: sector moments, fits, log-sum, the estimated rounding error of the
+// result, and with GRAD the cotangents of the contour values.
+//
+// The tilted moments tau_t[kappa] replace the contour values in the row's own
+// planes of sw.  Most sectors weigh nothing: a sector whose upper bound
+// S_0[kappa] (q <= 1) is below 1e-17 of a lower bound L of the estimate changes
+// the sum by < 1e-14 and is left out (at 70 modes a fifth of the resolved ones
+// remain).  L comes from a first round that fits 64 sectors spread evenly over
+// the well-resolved range (tilted weights from 1e-7 of the largest: further out
+// moments drown in the transform's rounding, and fits to such run through all
+// their steps), one per quad (of both parities: pure states have no odd
+// sectors); the second round fits the others that count, starting from the
+// parameters of the first round's sectors on either side, interpolated.
 //
 // Rounding estimate.  A contour value S_t(w_q) carries a relative rounding
 // error of about u_t (u_0 = ROUND_FP64 for the fp64 G_0; u_t = u_clu for the
@@ -547,21 +559,43 @@ __global__ __launch_bounds__(CONT_THREADS) void k_contour(
 //           its contour on the estimate's mean photon number kbar and pass 1
 //           runs it again; where that is not possible it is flagged
 //           GBS_PS_CONTOUR.
+//
+// GRAD: for L = sum_p w_p log p_hat_p, the log-sum and each fit differentiated
+// (implicitly: d log q / dm = -u) give the sector cotangents
+//   d L / d tau_0 = w pi_kappa (1 + u.m) / tau_0,
+//   d L / d tau_t = -w pi_kappa u_t binv_t / tau_0,
+// pi_kappa the sector's share of the estimate, and the transform's transpose
+// (the same transform) the cotangents of the contour values, in asw; a row
+// without a result, or of weight 0, gets zeros.  (The fits' results wait in the
+// planes of the moments, their log-terms in the last plane of asw, which is
+// the last one to be written.)
+//
+// Measured against one thread per sector from c = 0, every sector of the first
+// 256 fitted, two evaluations per Newton step, and the fits run again for the
+// adjoint (us): 4096 rows at 70 modes, order 3, 4270 -> 1440; 1024 rows at 20
+// modes, order 3, 1900 -> 314; 64 rows at 20 modes, order 2, 207 -> 98, with the
+// adjoint 470 -> 117; 512 rows at 144 modes, order 2, with the adjoint
+// 2870 -> 430; 16 rows of 2-6 clicks 168 -> 75.
 // ---------------------------------------------------------------------------
-template <int ORDER, int PASS = 0>
+template <int ORDER, int PASS, bool GRAD>
 __global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__ offsets,
-                                                         RowPlan *__restrict__ rows,
-                                                         const cplx *__restrict__ sw,
+                                                         RowPlan *__restrict__ rows, cplx *__restrict__ sw,
                                                          double *__restrict__ logp,
                                                          int *__restrict__ status, double u_clu,
-                                                         double esc_bound, int allow_retilt)
+                                                         double esc_bound, int allow_retilt,
+                                                         const double *__restrict__ dl, cplx *__restrict__ asw)
 {
-    constexpr int pass = PASS;
+    constexpr int pass = PASS, JM = ORDER >= 4 ? 4 : 3, NG = FIT_THREADS / FIT_G;
     extern __shared__ __attribute__((aligned(16))) double sh[];
-    __shared__ double red[FIT_THREADS], red2[FIT_THREADS];
+    __shared__ double red[2 * 5 * FIT_THREADS / 64];
+    __shared__ int s_cnt[FIT_THREADS / 64], s_len;
     const int p = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int n = offsets[p + 1] - offsets[p];
     RowPlan rp = rows[p];
+    cplx *const aw = GRAD ? asw + (long)p * (ORDER + 1) * GBS_QCAP : nullptr;
+    auto no_part = [&]() {
+        for (int i = tid; i < (ORDER + 1) * GBS_QCAP; i += nt) aw[i] = cmk(0.0, 0.0);
+    };
     if (pass == 1 && !(rp.flags & (GBS_PS_ESCALATED | GBS_ROW_RETILT))) return;
     if (n == 0) {
         if (tid == 0) {
@@ -569,6 +603,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__
             if (status) status[p] = 0;
             rows[p].err = 0.0;
         }
+        if (GRAD) no_part();
         return;
     }
     if (rp.status != 0) {
@@ -576,162 +611,245 @@ __global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__
             logp[p] = NAN;
             if (status) status[p] = rp.status | (rp.flags & GBS_PS_PUBLIC);
         }
+        if (GRAD) no_part();
         return;
     }
     const int K = rp.K, Q = K / 2 + 1, jp = min(ORDER, n - 1);
     const DftShape dsh = dft_shape(K);
     cplx *X = (cplx *)sh;            // K
-    cplx *W = X + K;                 // K/2
+    cplx *W = X + GBS_KMAX;          // K/2
     for (int m = tid; m < K / 2; m += nt) {
         const cplx u = unit_root(m, K);
         W[m] = cmk(u.re, -u.im);
     }
     // tilted sector moments tau_t[kappa] = Re FFT(S_t(w_q))[kappa] / K, where the
-    // points q > K/2 are the conjugates of K - q (real coefficients)
-    // (loops over t and j unrolled: every index into tau is static)
-    constexpr int NT = ORDER >= 4 ? 5 : 4;  // moments held per sector
-    double tau[FIT_KPT][NT];
+    // points q > K/2 are the conjugates of K - q (real coefficients); dt: the
+    // rounding of the tilted moments, u_t (1/K) sum_q |S_t(w_q)|
+    auto plane = [&](int t) { return (double *)(sw + ((long)p * (ORDER + 1) + t) * GBS_QCAP); };
+    double *const ell = GRAD ? (double *)(aw + ORDER * GBS_QCAP) : nullptr;
     const double invK = 1.0 / K;
+    double dt[JM + 1], tmax = 0.0;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (t <= ORDER && t <= jp) {
-            const cplx *src = sw + ((long)p * (ORDER + 1) + t) * GBS_QCAP;
-            for (int q = tid; q < K; q += nt) {
-                const cplx v = q < Q ? src[q] : cmk(src[K - q].re, -src[K - q].im);
-                const int rq = dft_pos(dsh, q);
-                X[rq] = v;
-            }
-            __syncthreads();
-            dft_lds(X, W, dsh);
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) {
-                const int kap = n + tid + nt * j;
-                tau[j][t] = kap < K ? X[kap].re * invK : 0.0;
-            }
-            __syncthreads();
-        } else {
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) tau[j][t] = 0.0;
+    for (int t = 0; t <= JM; ++t) {
+        dt[t] = 0.0;
+        if (t > ORDER || t > jp) continue;
+        const cplx *src = (const cplx *)plane(t);
+        double *dst = plane(t);
+        double a = 0.0;
+        for (int q = tid; q < K; q += nt) {
+            const cplx v = q < Q ? src[q] : cmk(src[K - q].re, -src[K - q].im);
+            X[dft_pos(dsh, q)] = v;
+            a += sqrt(v.re * v.re + v.im * v.im);
         }
+        dt[t] = (t == 0 ? ROUND_FP64 : u_clu) * (block_sum(a, red) * invK);
+        dft_lds(X, W, dsh);
+        for (int kap = n + tid; kap < K; kap += nt) {
+            const double v = X[kap].re * invK;
+            dst[kap] = v;
+            if (t == 0) {
+                tmax = fmax(tmax, v);
+                if (GRAD) ell[kap] = -INFINITY;
+            }
+        }
+        __syncthreads();
     }
-    double tmax = 0.0;
-    for (int j = 0; j < FIT_KPT; ++j)
-        if (n + tid + nt * j < K) tmax = fmax(tmax, tau[j][0]);
     tmax = block_max(tmax, red);
     const double thr = 1e-14 * tmax;
-    // rounding of the tilted moments: tau_t[kappa] = (1/K) sum_q S_t(w_q)
-    // e^{-2 pi i q kappa / K}, so contour values with relative errors u_t
-    // leave at most u_t (1/K) sum_q |S_t(w_q)| in each moment
-    double dt[4];
+    // (X is free now: the basis, the first round's results, the list of the second)
+    double *phi = (double *)X;                       // 4 n
+    double *ca = phi + 4 * GBS_MAX_N_APPROX;         // JM per sector of the first round
+    int *ja = (int *)(ca + 4 * NG);                  // their moments' number (0: none)
+    unsigned short *list = (unsigned short *)(ja + NG);
+    fit_basis(n, phi);
+    __syncthreads();
+    const int gl = tid & (FIT_G - 1), grp = tid / FIT_G;
+    // log-sums of the fitted and of the unresolved sectors, of term * rounding
+    // estimate of log(term), of term / tau_0 and of term * kappa
+    double lm[5], ls[5];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        double s0 = 0.0;
-        if (t <= ORDER && t <= jp) {
-            const cplx *src = sw + ((long)p * (ORDER + 1) + (t <= ORDER ? t : 0)) * GBS_QCAP;
-            double a = 0.0;
-            for (int q = tid; q < Q; q += nt)
-                a += (q == 0 || q == K / 2 ? 1.0 : 2.0) * sqrt(src[q].re * src[q].re + src[q].im * src[q].im);
-            s0 = block_sum(a, red) / K;
-        }
-        dt[t] = (t == 0 ? ROUND_FP64 : u_clu) * s0;
-    }
-    double fm = -INFINITY, fs = 0.0, um = -INFINITY, us = 0.0;
+    for (int i = 0; i < 5; ++i) lm[i] = -INFINITY, ls[i] = 0.0;
     int nsec = 0;
-    // log-sums of term_kappa * rounding estimate of log(term_kappa)
-    double em = -INFINITY, es = 0.0, eh = -INFINITY, esh = 0.0, ek = -INFINITY, esk = 0.0;
-    double lower = -INFINITY;  // log of a lower bound of the total (after pass 0)
-    // Pass 0 fits each thread's first sector; its block log-sum is a lower
-    // bound L of the estimate.  Later sectors whose upper bound S_0[kappa]
-    // (q <= 1) is below 1e-17 L are skipped: they change the sum by < 1e-14.
+    const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
+                            6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
+                            24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
+    auto log_weight = [&](double t0, int kap) { return log(t0) + rp.log_g_rho - kap * rp.log_rho; };
+    auto usable = [&](double t0) { return t0 >= thr && t0 > 0.0; };
+    auto sector = [&](int kap, int js, const double *cs) {
+        double tau[JM + 1];
 #pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j) {
-        if (j == 1) {
-            double mx = block_max(fm, red);
-            double sm = block_sum(fm == -INFINITY ? 0.0 : fs * exp(fm - mx), red);
-            lower = sm > 0.0 ? mx + log(sm) : -INFINITY;
-        }
-        const int kap = n + tid + nt * j;
-        if (kap >= K) continue;
-        const double t0 = tau[j][0];
-        if (!(t0 >= thr) || !(t0 > 0.0)) continue;
-        const double lw = log(t0) + rp.log_g_rho - kap * rp.log_rho;
-        if (lw < lower + log(1e-17)) continue;
-        const SectorFitT<ORDER >= 4 ? 4 : 3> f =
-            fit_sector<ORDER >= 4 ? 4 : 3>(n, 0, jp, t0, tau[j][1], tau[j][2], tau[j][3], ORDER >= 4 ? tau[j][NT - 1] : 0.0);
-        if (f.bad) {
-            lse_add(um, us, lw);
-        } else {
-            lse_add(fm, fs, lw + f.lq);
-            ++nsec;
-            double u[4];
-            fit_sensitivity<ORDER >= 4 ? 4 : 3>(n, f, u);
-            const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
-                                    6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
-                                    24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
-            double um0 = 1.0, e1 = 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (t < f.jr) {
-                    um0 += fabs(u[t] * f.m[t]);
-                    e1 += fabs(u[t]) * binv[t] * dt[t + 1];
-                }
-            const double e = (dt[0] * um0 + e1) / t0;
-            lse_add(em, es, lw + f.lq + log(e));
-            lse_add(eh, esh, lw + f.lq - log(t0));
-            lse_add(ek, esk, lw + f.lq + log((double)kap));
-        }
-    }
-    // block log-sum-exp of the fitted and the unresolved sectors
-    double fmx = block_max(fm, red);
-    double fsum = block_sum(fm == -INFINITY ? 0.0 : fs * exp(fm - fmx), red);
-    double umx = block_max(um, red2);
-    double usum = block_sum(um == -INFINITY ? 0.0 : us * exp(um - umx), red2);
-    double ns = block_sum((double)nsec, red);
-    const double emx = block_max(em, red2);
-    const double esum = block_sum(em == -INFINITY ? 0.0 : es * exp(em - emx), red2);
-    const double ehx = block_max(eh, red2);
-    const double ehsum = block_sum(eh == -INFINITY ? 0.0 : esh * exp(eh - ehx), red2);
-    const double ekx = block_max(ek, red2);
-    const double eksum = block_sum(ek == -INFINITY ? 0.0 : esk * exp(ek - ekx), red2);
-    if (tid == 0) {
-        double tot = fmx + log(fsum);
-        double unres = umx + log(usum);
-        int stt = 0;
-        double out = rp.log_pvac + tot;
-        if (fsum > 0.0 && usum > 0.0 && unres > tot + log(1e-10)) {
-            stt = GBS_PS_FIT_NOCONV;
-            out = NAN;
-        }
-        if (!(fsum > 0.0)) out = -INFINITY;
-        // estimated rounding error of log p_hat in this precision; the
-        // contour cannot resolve the sectors that carry the estimate when their
-        // tilted weights, averaged with their shares of the estimate (the
-        // harmonic mean sum_kappa w_kappa / tau_kappa), fall below 1e-6: the
-        // transform's rounding floor (~1e-16 of the contour's tilted weight)
-        // then reaches 1e-10 of the estimate
-        const double err = fsum > 0.0 && esum > 0.0 ? exp(emx + log(esum) - tot) : 0.0;
-        int flags = rp.flags & ~GBS_ROW_RETILT;
-        if (fsum > 0.0 && ehsum > 0.0 && ehx + log(ehsum) - tot > log(1e6)) {
-            // the estimate's sectors lie far out in the tilted distribution: on
-            // the first pass, tilt the contour afresh towards their mean photon
-            // number and run the row again; otherwise report it
-            const double kbar = eksum > 0.0 ? exp(ekx + log(eksum) - tot) : 0.0;
-            const bool moves = kbar > 1.02 * rp.kbar ? rp.rho < 0.97 * rp.rconv : kbar < rp.kbar / 1.02;
-            if (pass == 0 && allow_retilt && moves) {
-                flags |= GBS_ROW_RETILT;
-                rows[p].kbar = kbar;
-                if (esc_bound > 0.0) flags |= GBS_PS_ESCALATED;  // (the rerun is fp64)
+        for (int t = 0; t <= JM; ++t) tau[t] = t <= ORDER && t <= jp ? plane(t)[kap] : 0.0;
+        const double t0 = tau[0], lw = log_weight(t0, kap);
+        const SectorFitT<JM> f = fit_sector<JM>(n, 0, jp, (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0,
+                                                js, cs[0], cs[1], cs[2], JM >= 4 ? cs[JM - 1] : 0.0);
+        if (gl == 0) {
+            if (f.bad) {
+                lse_add(lm[1], ls[1], lw);
             } else {
-                flags |= GBS_PS_CONTOUR;
+                ++nsec;
+                double um0 = 1.0, e1 = 0.0, um = 0.0;
+#pragma unroll
+                for (int t = 0; t < JM; ++t)
+                    if (t < f.jr) {
+                        um0 += fabs(f.u[t] * f.m[t]);
+                        um += f.u[t] * f.m[t];
+                        e1 += fabs(f.u[t]) * binv[t] * dt[t + 1];
+                    }
+                const double e = (dt[0] * um0 + e1) / t0, el = lw + f.lq;
+                lse_add(lm[0], ls[0], el);
+                lse_add(lm[2], ls[2], el + log(e));
+                lse_add(lm[3], ls[3], el - log(t0));
+                lse_add(lm[4], ls[4], el + log((double)kap));
+                if (GRAD) {
+                    // the cotangents over w pi (a singular H: the sector's weight only)
+                    const bool ok = f.jr == 0 || fabs(f.u[0]) < 1e299;
+                    ell[kap] = el;
+                    plane(0)[kap] = (1.0 + (ok ? um : 0.0)) / t0;
+#pragma unroll
+                    for (int t = 1; t <= JM; ++t)
+                        if (t <= ORDER && t <= jp)
+                            plane(t)[kap] = ok && t <= f.jr ? -f.u[t - 1] * binv[t - 1] / t0 : 0.0;
+                }
             }
         }
-        // (mixed precision: rows over the bound, and rows whose fits failed)
-        if (pass == 0 && esc_bound > 0.0 && (!(err <= esc_bound) || stt != 0)) flags |= GBS_PS_ESCALATED;
+        return f;
+    };
+    // first round: sectors first(0..NG-1) up to kmax
+    double far = -1.0;
+    for (int kap = n + tid; kap < K; kap += nt)
+        if (plane(0)[kap] >= 1e-7 * tmax) far = kap;
+    const int kmax = (int)block_max(far, red);
+    const int stride = max(1, (kmax - n + NG) / NG);
+    auto first = [&](int i) { return n + stride * i + (stride > 1 ? (stride * i + (i >> 1)) & 1 : 0); };
+    const double none[4] = {0.0, 0.0, 0.0, 0.0};
+    {
+        const int kap = first(grp);
+        int jr = 0;
+        if (kap <= kmax && usable(plane(0)[kap])) {
+            const SectorFitT<JM> f = sector(kap, 0, none);
+            if (!f.bad) {
+                jr = f.jr;
+#pragma unroll
+                for (int t = 0; t < JM; ++t)
+                    if (gl == 0) ca[JM * grp + t] = f.c[t];
+            }
+        }
+        if (gl == 0) ja[grp] = jr;
+    }
+    __syncthreads();
+    if (stride > 1 || kmax < K - 1) {
+        double m1[1] = {lm[0]}, s1[1] = {ls[0]};
+        block_lse<1>(m1, s1, red);
+        const double floor_ = (s1[0] > 0.0 ? m1[0] + log(s1[0]) : -INFINITY) + log(1e-17);
+        // the second round's sectors, ascending
+        if (tid == 0) s_len = 0;
+        __syncthreads();
+        for (int k0 = n; k0 < K; k0 += nt) {
+            const int kap = k0 + tid;
+            bool need = false;
+            const int i = (kap - n) / stride;
+            if (kap < K && !(kap <= kmax && i < NG && first(i) == kap)) {
+                const double t0 = plane(0)[kap];
+                need = usable(t0) && !(log_weight(t0, kap) < floor_);
+            }
+            const unsigned long long bal = __ballot(need);
+            if ((tid & 63) == 0) s_cnt[tid >> 6] = __popcll(bal);
+            __syncthreads();
+            int at = s_len;
+            for (int w = 0; w < (tid >> 6); ++w) at += s_cnt[w];
+            if (need) list[at + __popcll(bal & ((1ull << (tid & 63)) - 1ull))] = (unsigned short)kap;
+            __syncthreads();
+            if (tid == nt - 1) s_len = at + s_cnt[tid >> 6];
+            __syncthreads();
+        }
+        const int len = s_len;
+        for (int i = grp; i < len; i += NG) {
+            const int kap = list[i];
+            // the first round's sectors on either side
+            int a = (kap - n) / stride;
+            if (first(a) > kap) --a;
+            a = min(a, NG - 1);
+            const int b = a + 1;
+            const int jra = a >= 0 ? ja[a] : 0, jrb = b < NG ? ja[b] : 0;
+            double cs[4] = {0.0, 0.0, 0.0, 0.0};
+            const double x = jra == jrb && a >= 0 ? (double)(kap - first(a)) / (double)(first(b) - first(a))
+                                                  : jra > 0 ? 0.0 : 1.0;
+            const int js = jra > 0 ? jra : jrb;
+            if (js > 0)
+#pragma unroll
+                for (int t = 0; t < JM; ++t)
+                    cs[t] = (x < 1.0 ? (1.0 - x) * ca[JM * a + t] : 0.0) + (x > 0.0 ? x * ca[JM * b + t] : 0.0);
+            sector(kap, js, cs);
+        }
+    }
+    block_lse<5>(lm, ls, red);
+    const double ns = block_sum((double)nsec, red);
+    const double fsum = ls[0], usum = ls[1], esum = ls[2], ehsum = ls[3], eksum = ls[4];
+    const double tot = lm[0] + log(fsum), unres = lm[1] + log(usum);
+    int stt = 0;
+    double out = rp.log_pvac + tot;
+    if (fsum > 0.0 && usum > 0.0 && unres > tot + log(1e-10)) {
+        stt = GBS_PS_FIT_NOCONV;
+        out = NAN;
+    }
+    if (!(fsum > 0.0)) out = -INFINITY;
+    // estimated rounding error of log p_hat in this precision; the
+    // contour cannot resolve the sectors that carry the estimate when their
+    // tilted weights, averaged with their shares of the estimate (the
+    // harmonic mean sum_kappa w_kappa / tau_kappa), fall below 1e-6: the
+    // transform's rounding floor (~1e-16 of the contour's tilted weight)
+    // then reaches 1e-10 of the estimate
+    const double err = fsum > 0.0 && esum > 0.0 ? exp(lm[2] + log(esum) - tot) : 0.0;
+    int flags = rp.flags & ~GBS_ROW_RETILT;
+    if (fsum > 0.0 && ehsum > 0.0 && lm[3] + log(ehsum) - tot > log(1e6)) {
+        // the estimate's sectors lie far out in the tilted distribution: on
+        // the first pass, tilt the contour afresh towards their mean photon
+        // number and run the row again; otherwise report it
+        const double kbar = eksum > 0.0 ? exp(lm[4] + log(eksum) - tot) : 0.0;
+        const bool moves = kbar > 1.02 * rp.kbar ? rp.rho < 0.97 * rp.rconv : kbar < rp.kbar / 1.02;
+        if (pass == 0 && allow_retilt && moves) {
+            flags |= GBS_ROW_RETILT;
+            if (tid == 0) rows[p].kbar = kbar;
+            if (esc_bound > 0.0) flags |= GBS_PS_ESCALATED;  // (the rerun is fp64)
+        } else {
+            flags |= GBS_PS_CONTOUR;
+        }
+    }
+    // (mixed precision: rows over the bound, and rows whose fits failed)
+    if (pass == 0 && esc_bound > 0.0 && (!(err <= esc_bound) || stt != 0)) flags |= GBS_PS_ESCALATED;
+    if (tid == 0) {
         logp[p] = out;
         if (status) status[p] = stt | (flags & GBS_PS_PUBLIC);
         rows[p].nsec = (int)ns;
         rows[p].flags = flags;
         rows[p].err = err;
+    }
+    if constexpr (GRAD) {
+        if (flags & GBS_ROW_RETILT) return;  // (the second pass writes the row's cotangents)
+        const double wp = dl[p];
+        if (stt != 0 || wp == 0.0 || !isfinite(wp) || !(fsum > 0.0)) {
+            no_part();
+            return;
+        }
+        // alpha_t(w_q) = c_q FFT(tbar_t)[q], c_q = 1/K at q = 0, K/2 and 2/K otherwise
+#pragma unroll 1
+        for (int t = 0; t <= ORDER; ++t) {
+            cplx *dst = aw + t * GBS_QCAP;
+            if (t > jp) {
+                for (int q = tid; q < Q; q += nt) dst[q] = cmk(0.0, 0.0);
+                continue;
+            }
+            __syncthreads();
+            for (int k = tid; k < K; k += nt) {
+                const double el = k >= n ? ell[k] : -INFINITY;
+                X[dft_pos(dsh, k)] = cmk(el > -INFINITY ? wp * exp(el - tot) * plane(t)[k] : 0.0, 0.0);
+            }
+            __syncthreads();
+            dft_lds(X, W, dsh);
+            for (int q = tid; q < Q; q += nt) {
+                const double cq = (q == 0 || q == K / 2) ? invK : 2.0 * invK;
+                dst[q] = cscale(X[q], cq);
+            }
+        }
     }
 }
 
@@ -743,17 +861,19 @@ __global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__
 // p_k(n') = S_0[k] q_k(n'), p(n') = sum_k p_k(n') (LDS accumulators, one block).
 // Sectors below the transform's noise floor (1e-14 of the largest tilted
 // weight) are left out; a sector whose fit fails sets GBS_PS_FIT_NOCONV when
-// its weight exceeds 1e-10 of the total.
+// its weight exceeds 1e-10 of the total.  A quad per sector.
 // ---------------------------------------------------------------------------
+#define DIST_THREADS 1024
 template <int ORDER>
-__global__ __launch_bounds__(FIT_THREADS) void k_dist_fit(const int *__restrict__ offsets,
-                                                          const RowPlan *__restrict__ rows,
-                                                          const cplx *__restrict__ sw, int nk,
-                                                          const int *__restrict__ ks, double *__restrict__ p_n,
-                                                          double *__restrict__ p_k, int *__restrict__ status)
+__global__ __launch_bounds__(DIST_THREADS) void k_dist_fit(const int *__restrict__ offsets,
+                                                           const RowPlan *__restrict__ rows,
+                                                           cplx *__restrict__ sw, int nk,
+                                                           const int *__restrict__ ks, double *__restrict__ p_n,
+                                                           double *__restrict__ p_k, int *__restrict__ status)
 {
+    constexpr int JM = ORDER >= 4 ? 4 : 3;
     extern __shared__ __attribute__((aligned(16))) double sh[];
-    __shared__ double red[FIT_THREADS];
+    __shared__ double red[DIST_THREADS / 64];
     __shared__ double pacc[2 * GBS_NSMALL + 2];
     __shared__ double s_fail;
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -770,86 +890,73 @@ __global__ __launch_bounds__(FIT_THREADS) void k_dist_fit(const int *__restrict_
     const int K = rp.K, Q = K / 2 + 1, jp = min(ORDER, n - 1);
     const DftShape dsh = dft_shape(K);
     cplx *X = (cplx *)sh;
-    cplx *W = X + K;
+    cplx *W = X + GBS_KMAX;
     for (int m = tid; m < K / 2; m += nt) {
         const cplx u = unit_root(m, K);
         W[m] = cmk(u.re, -u.im);
     }
-    constexpr int NT = ORDER >= 4 ? 5 : 4;
-    double tau[FIT_KPT][NT];
+    // (the moments replace the contour values in the row's planes: row 0)
+    auto plane = [&](int t) { return (double *)(sw + (long)t * GBS_QCAP); };
     const double invK = 1.0 / K;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (t <= ORDER && t <= jp) {
-            const cplx *src = sw + (long)t * GBS_QCAP;  // (the row's planes: row 0)
-            for (int q = tid; q < K; q += nt) {
-                const cplx v = q < Q ? src[q] : cmk(src[K - q].re, -src[K - q].im);
-                X[dft_pos(dsh, q)] = v;
-            }
-            __syncthreads();
-            dft_lds(X, W, dsh);
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) {
-                const int kap = tid + nt * j;
-                tau[j][t] = kap < K ? X[kap].re * invK : 0.0;
-            }
-            __syncthreads();
-        } else {
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) tau[j][t] = 0.0;
-        }
-    }
     double tmax = 0.0;
-#pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j)
-        if (tid + nt * j < K) tmax = fmax(tmax, tau[j][0]);
+#pragma unroll 1
+    for (int t = 0; t <= jp; ++t) {
+        const cplx *src = (const cplx *)plane(t);
+        double *dst = plane(t);
+        for (int q = tid; q < K; q += nt) {
+            const cplx v = q < Q ? src[q] : cmk(src[K - q].re, -src[K - q].im);
+            X[dft_pos(dsh, q)] = v;
+        }
+        __syncthreads();
+        dft_lds(X, W, dsh);
+        for (int kap = tid; kap < K; kap += nt) {
+            const double v = X[kap].re * invK;
+            dst[kap] = v;
+            if (t == 0) tmax = fmax(tmax, v);
+        }
+        __syncthreads();
+    }
     tmax = block_max(tmax, red);
     const double thr = 1e-14 * tmax;
-    const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
-                            6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
-                            24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
+    double *phi = (double *)X;
+    fit_basis(n, phi);
+    __syncthreads();
+    const int gl = tid & (FIT_G - 1);
+    for (int kap = tid / FIT_G; kap < K; kap += nt / FIT_G) {
+        double tau[JM + 1];
 #pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j) {
-        const int kap = tid + nt * j;
-        if (kap >= K) continue;
-        const double t0 = tau[j][0];
+        for (int t = 0; t <= JM; ++t) tau[t] = t <= ORDER && t <= jp ? plane(t)[kap] : 0.0;
+        const double t0 = tau[0];
         if (!(t0 >= thr) || !(t0 > 0.0)) continue;
         const double w0 = exp(log(t0) + rp.log_pvac + rp.log_g_rho - kap * rp.log_rho);  // S_0[k]
         int slot = -1;
         for (int i = 0; i < nk; ++i)
             if (ks[i] == kap) slot = i;
-        if (kap == 0) {
-            atomicAdd(&pacc[0], w0);
-            if (slot >= 0) p_k[slot * (n + 1)] = w0;
-            continue;
-        }
         const int s = min(kap, n), v0 = n - s;
-        if (s == 1) {
-            atomicAdd(&pacc[1], w0);
-            if (slot >= 0) p_k[slot * (n + 1) + 1] = w0;
-            continue;
-        }
-        const SectorFitT<ORDER >= 4 ? 4 : 3> f = fit_sector<ORDER >= 4 ? 4 : 3>(
-            n, v0, min(jp, s - 1), t0, tau[j][1], tau[j][2], tau[j][3], ORDER >= 4 ? tau[j][NT - 1] : 0.0);
+        SectorFitT<JM> f;
+        f.jr = f.bad = 0;
+        if (s > 1)
+            f = fit_sector<JM>(n, v0, min(jp, s - 1), (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0, 0,
+                               0.0, 0.0, 0.0, 0.0);
         if (f.bad) {
-            atomicAdd(&s_fail, w0);
+            if (gl == 0) atomicAdd(&s_fail, w0);
             continue;
         }
         if (f.jr == 0) {
-            // no usable moment (m_1 <= 0): every detector the sector can reach fires
-            atomicAdd(&pacc[s], w0);
-            if (slot >= 0) p_k[slot * (n + 1) + s] = w0;
+            // the vacuum, one photon, or no usable moment (m_1 <= 0): every
+            // detector the sector can reach fires
+            if (gl == 0) {
+                atomicAdd(&pacc[s], w0);
+                if (slot >= 0) p_k[slot * (n + 1) + s] = w0;
+            }
             continue;
         }
         // q(n') = exp(lq - c . phi(v)), v = n - n' (lq = minus the log-partition sum)
-        for (int v = v0; v < n; ++v) {
-            const double ph[4] = {v * binv[0], 0.5 * v * (v - 1.0) * binv[1],
-                                  v * (v - 1.0) * (v - 2.0) / 6.0 * binv[2],
-                                  v * (v - 1.0) * (v - 2.0) * (v - 3.0) / 24.0 * binv[3]};
+        for (int v = v0 + gl; v < n; v += FIT_G) {
             double z = f.lq;
 #pragma unroll
-            for (int t = 0; t < (ORDER >= 4 ? 4 : 3); ++t)
-                if (t < f.jr) z -= f.c[t] * ph[t];
+            for (int t = 0; t < JM; ++t)
+                if (t < f.jr) z -= f.c[t] * phi[4 * v + t];
             const double pv = w0 * exp(z);
             atomicAdd(&pacc[n - v], pv);
             if (slot >= 0) p_k[slot * (n + 1) + n - v] = pv;
@@ -935,8 +1042,10 @@ int launch_contour(gbs_ctx *ctx, gbs_plan *pl, int nmax)
 // rows whose contour is re-tilted (new radius, rerun) -- not on a frozen plan,
 // whose radii stay as they are.  Order 4 runs in fp64 only (the plan
 // enforces it).
-template <int ORDER>
-int launch_order(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
+// dl (a gradient call): the weights of the rows; the fits then also leave the
+// cotangents of the contour values.
+template <int ORDER, bool GRAD>
+int launch_order(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status, const double *dl)
 {
     hipStream_t st = ctx->stream;
     const int P = pl->P, nbig = pl->nbig;
@@ -967,15 +1076,15 @@ int launch_order(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
     }
     timer_end(ctx, ts);
     size_t lds_f = sizeof(cplx) * (GBS_KMAX + GBS_KMAX / 2);
-    if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER>, (int)lds_f))) return rc;
+    if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER, 0, GRAD>, (int)lds_f))) return rc;
     const int retilt = !pl->frozen && !pl->whole;
     ts = timer_begin(ctx, TG_FIT);
-    hipLaunchKernelGGL(k_dft_fit<ORDER>, dim3(P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
+    hipLaunchKernelGGL((k_dft_fit<ORDER, 0, GRAD>), dim3(P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
                        pl->d_rows, pl->d_sw, logp, status, mixed ? ROUND_FP32 : ROUND_FP64,
-                       mixed ? MIXED_BOUND : 0.0, retilt);
+                       mixed ? MIXED_BOUND : 0.0, retilt, dl, pl->d_asw);
     timer_end(ctx, ts);
     if (mixed || retilt) {
-        if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER, 1>, (int)lds_f))) return rc;
+        if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER, 1, GRAD>, (int)lds_f))) return rc;
         ts = timer_begin(ctx, TG_PASS2);
         hipLaunchKernelGGL(k_retilt, dim3((P + 255) / 256), dim3(256), 0, st, P, pl->d_offsets, pl->d_alpha,
                            pl->d_rows);
@@ -983,8 +1092,8 @@ int launch_order(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
                            pl->d_perm, pl->d_rows, pl->d_items, pl->d_counter, GBS_PS_ESCALATED | GBS_ROW_RETILT);
         if (nbig > 0 && (rc = launch_contour<ORDER, true, cplx, true>(ctx, pl, pl->max_n))) return rc;
         if (nbig < P && (rc = launch_contour<ORDER, false, cplx, true>(ctx, pl, nsmall_max))) return rc;
-        hipLaunchKernelGGL((k_dft_fit<ORDER, 1>), dim3(P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
-                           pl->d_rows, pl->d_sw, logp, status, ROUND_FP64, 0.0, 0);
+        hipLaunchKernelGGL((k_dft_fit<ORDER, 1, GRAD>), dim3(P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
+                           pl->d_rows, pl->d_sw, logp, status, ROUND_FP64, 0.0, 0, dl, pl->d_asw);
         timer_end(ctx, ts);
     }
     HIP_TRY(ctx, hipGetLastError());
@@ -1003,7 +1112,7 @@ int dist_order(gbs_ctx *ctx, gbs_plan *pl, int nk, const int *ks, double *p_n, d
     if ((rc = launch_contour<ORDER, false, cplx>(ctx, pl, pl->max_n_small))) return rc;
     size_t lds_f = sizeof(cplx) * (GBS_KMAX + GBS_KMAX / 2);
     if ((rc = func_lds_limit(ctx, (const void *)k_dist_fit<ORDER>, (int)lds_f))) return rc;
-    hipLaunchKernelGGL(k_dist_fit<ORDER>, dim3(1), dim3(FIT_THREADS), lds_f, st, pl->d_offsets, pl->d_rows,
+    hipLaunchKernelGGL(k_dist_fit<ORDER>, dim3(1), dim3(DIST_THREADS), lds_f, st, pl->d_offsets, pl->d_rows,
                        pl->d_sw, nk, ks, p_n, p_k, status);
     HIP_TRY(ctx, hipGetLastError());
     return 0;
@@ -1023,10 +1132,11 @@ int launch_plain(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
     if ((rc = plain_contour(ctx, pl))) return rc;
     timer_end(ctx, ts);
     size_t lds_f = sizeof(cplx) * (GBS_KMAX + GBS_KMAX / 2);
-    if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER>, (int)lds_f))) return rc;
+    if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER, 0, false>, (int)lds_f))) return rc;
     ts = timer_begin(ctx, TG_FIT);
-    hipLaunchKernelGGL(k_dft_fit<ORDER>, dim3(pl->P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
-                       pl->d_rows, pl->d_sw, logp, status, ROUND_FP64, 0.0, 0);
+    hipLaunchKernelGGL((k_dft_fit<ORDER, 0, false>), dim3(pl->P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
+                       pl->d_rows, pl->d_sw, logp, status, ROUND_FP64, 0.0, 0, (const double *)nullptr,
+                       (cplx *)nullptr);
     timer_end(ctx, ts);
     HIP_TRY(ctx, hipGetLastError());
     return 0;
@@ -1063,13 +1173,14 @@ int status_or(gbs_ctx *ctx, int P, int32_t *status_dev, int bits)
 }
 
 namespace {
-int forward_order(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *status_dev)
+template <bool GRAD>
+int forward_order(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *status_dev, const double *dl)
 {
     switch (pl->order) {
-    case 1: return launch_order<1>(ctx, pl, logp_dev, status_dev);
-    case 2: return launch_order<2>(ctx, pl, logp_dev, status_dev);
-    case 3: return launch_order<3>(ctx, pl, logp_dev, status_dev);
-    case 4: return launch_order<4>(ctx, pl, logp_dev, status_dev);
+    case 1: return launch_order<1, GRAD>(ctx, pl, logp_dev, status_dev, dl);
+    case 2: return launch_order<2, GRAD>(ctx, pl, logp_dev, status_dev, dl);
+    case 3: return launch_order<3, GRAD>(ctx, pl, logp_dev, status_dev, dl);
+    case 4: return launch_order<4, GRAD>(ctx, pl, logp_dev, status_dev, dl);
     default: return set_err(ctx, -1, "order must be 1, 2, 3 or 4");
     }
 }
@@ -1077,12 +1188,15 @@ int forward_order(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *status_
 
 // Order 4 has no fp32 cluster kernels: asked for the mixed tier, it runs in
 // fp64 and every row reports GBS_PS_ESCALATED.
-int approx_forward(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *status_dev)
+// dl_dev: the rows' weights where the adjoint follows (its workspace is there),
+// else null.
+int approx_forward(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *status_dev, const double *dl_dev)
 {
     if (pl->P == 0) return 0;
     const bool esc_all = pl->order == 4 && pl->prec == GBS_PREC_MIXED;
     if (esc_all) pl->prec = GBS_PREC_FP64;
-    int rc = forward_order(ctx, pl, logp_dev, status_dev);
+    int rc = dl_dev ? forward_order<true>(ctx, pl, logp_dev, status_dev, dl_dev)
+                    : forward_order<false>(ctx, pl, logp_dev, status_dev, nullptr);
     if (esc_all) {
         pl->prec = GBS_PREC_MIXED;
         if (rc == 0) rc = status_or(ctx, pl->P, status_dev, GBS_PS_ESCALATED);

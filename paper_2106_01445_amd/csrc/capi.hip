@@ -680,7 +680,8 @@ int time_pass(gbs_ctx *ctx, gbs_plan *pl, bool adjoint, const double *dl, double
     double best = 1e300;
     int rc = 0;
     for (int rep = 0; rep < 2 && !rc; ++rep) {
-        if (adjoint && (rc = approx_forward(ctx, pl, pl->d_logp, pl->d_status))) break;
+        if (adjoint && (rc = adj_workspace(ctx, pl))) break;
+        if (adjoint && (rc = approx_forward(ctx, pl, pl->d_logp, pl->d_status, dl))) break;
         (void)hipEventRecord(a, ctx->stream);
         rc = adjoint ? approx_backward(ctx, pl, dl, pl->d_status, g, g + ctx->model.M)
                      : approx_forward(ctx, pl, pl->d_logp, pl->d_status);
@@ -886,7 +887,8 @@ int gbs_grad_dev(gbs_ctx *ctx, gbs_plan *pl, const double *dl_dev, double *logp_
     const bool esc_all = pl->prec != GBS_PREC_FP64;
     const int prec = pl->prec;
     pl->prec = GBS_PREC_FP64;
-    int rc = approx_forward(ctx, pl, lp, stt);
+    int rc = adj_workspace(ctx, pl);
+    if (rc == 0) rc = approx_forward(ctx, pl, lp, stt, dl_dev);
     if (rc == 0) {
         pl->have_run = true;
         rc = approx_backward(ctx, pl, dl_dev, stt, grad_r_dev, grad_eta_dev);

@@ -23,36 +23,72 @@
 #ifndef DFT_RMAX
 #define DFT_RMAX 15
 #endif
-#define FIT_KPT (GBS_KMAX / FIT_THREADS)
 
 namespace {
 
+__device__ __forceinline__ double wave_sum(double v)
+{
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    return v;
+}
+__device__ __forceinline__ double wave_max(double v)
+{
+    for (int m = 32; m > 0; m >>= 1) v = fmax(v, __shfl_xor(v, m));
+    return v;
+}
+// sum and maximum over a workgroup (red: one entry per wavefront)
 __device__ double block_sum(double v, double *red)
 {
-    const int tid = threadIdx.x;
-    red[tid] = v;
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
-    double r = red[0];
+    double r = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) r += red[w];
     __syncthreads();
     return r;
 }
 
 __device__ double block_max(double v, double *red)
 {
-    const int tid = threadIdx.x;
-    red[tid] = v;
+    v = wave_max(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (tid < s) red[tid] = fmax(red[tid], red[tid + s]);
-        __syncthreads();
-    }
     double r = red[0];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = fmax(r, red[w]);
     __syncthreads();
     return r;
+}
+
+// log-sums over a workgroup of C pairs (largest exponent m, sum s of
+// exp(. - m)) per thread, each as such a pair (red: 2 C entries per wavefront)
+template <int C>
+__device__ __forceinline__ void block_lse(double (&m)[C], double (&s)[C], double *red)
+{
+    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    double mx[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) mx[i] = wave_max(m[i]);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < C; ++i) red[w * C + i] = mx[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        mx[i] = red[i];
+        for (int u = 1; u < nw; ++u) mx[i] = fmax(mx[i], red[u * C + i]);
+        s[i] = wave_sum(m[i] == -INFINITY ? 0.0 : s[i] * exp(m[i] - mx[i]));
+    }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < C; ++i) red[(nw + w) * C + i] = s[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        m[i] = mx[i];
+        s[i] = 0.0;
+        for (int u = 0; u < nw; ++u) s[i] += red[(nw + u) * C + i];
+    }
+    __syncthreads();
 }
 
 __device__ __forceinline__ cplx warp_csum(cplx v)
@@ -363,164 +399,211 @@ __device__ __forceinline__ SlotMT<C> slot_view(cplx *base, int n)
     return m;
 }
 
-// Log-partition sum of the exp-polynomial on n' = 1..n - v0 (v = n - n' empty modes,
-// basis phi_t = C(v, t) ib[t]) and, with WANT_E, the mean E[phi] and the
-// second moments E2 (upper triangle, row-major) of its JP features.  JP is a
-// template argument so that every array index is static (kept in registers).
-template <int JP, bool WANT_E>
-__device__ __forceinline__ void fit_eval(int n, int v0, const double *ib, const double *c, double *lse,
-                                         double *E, double *E2)
+// ---------------------------------------------------------------------------
+// Sector fits.  Four lanes (a quad) work on one sector: each takes every fourth
+// term of the support, and the sums over it meet by quad permutations, so that
+// all four lanes hold the same values and take the same branches.
+// What bounds them: the chain of Newton steps, each a sum of n exponentials.
+// One evaluation per step serves its line search, the next step's Hessian and,
+// at the last point, the sensitivity; a quarter of the terms per lane shortens
+// it; neighbouring sectors' parameters start most fits (k_dft_fit).
+// ---------------------------------------------------------------------------
+#define FIT_G 4  // lanes per sector
+typedef const __attribute__((address_space(3))) double *LdsTab;  // (a table in LDS)
+
+__device__ __forceinline__ double quad_xor(double x, int ctrl1)
 {
-    double zmax = -1e300;
-    for (int v = v0; v < n; ++v) {
-        const double f[4] = {v * ib[0], 0.5 * v * (v - 1) * ib[1], v * (v - 1.0) * (v - 2.0) / 6.0 * ib[2],
-                             v * (v - 1.0) * (v - 2.0) * (v - 3.0) / 24.0 * ib[3]};
-        double z = 0.0;
-#pragma unroll
-        for (int t = 0; t < JP; ++t) z -= c[t] * f[t];
-        zmax = fmax(zmax, z);
+    int lo = __double2loint(x), hi = __double2hiint(x);
+    if (ctrl1) {
+        lo = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);  // lanes 1, 0, 3, 2
+        hi = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
+    } else {
+        lo = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);  // lanes 2, 3, 0, 1
+        hi = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
     }
-    double s = 0.0, e[4] = {0, 0, 0, 0}, e2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int v = v0; v < n; ++v) {
-        const double f[4] = {v * ib[0], 0.5 * v * (v - 1) * ib[1], v * (v - 1.0) * (v - 2.0) / 6.0 * ib[2],
-                             v * (v - 1.0) * (v - 2.0) * (v - 3.0) / 24.0 * ib[3]};
-        double z = 0.0;
-#pragma unroll
-        for (int t = 0; t < JP; ++t) z -= c[t] * f[t];
-        const double wgt = exp(z - zmax);
-        s += wgt;
-        if (WANT_E) {
-#pragma unroll
-            for (int t = 0; t < JP; ++t) e[t] += wgt * f[t];
-            int k = 0;
-#pragma unroll
-            for (int t = 0; t < JP; ++t)
-#pragma unroll
-                for (int u = t; u < JP; ++u) e2[k++] += wgt * f[t] * f[u];
-        }
-    }
-    *lse = zmax + log(s);
-    if (WANT_E) {
-#pragma unroll
-        for (int t = 0; t < JP; ++t) E[t] = e[t] / s;
-#pragma unroll
-        for (int k = 0; k < JP * (JP + 1) / 2; ++k) E2[k] = e2[k] / s;
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double quad_sum(double x)
+{
+    x += quad_xor(x, 1);
+    return x + quad_xor(x, 0);
+}
+__device__ __forceinline__ double quad_max(double x)
+{
+    x = fmax(x, quad_xor(x, 1));
+    return fmax(x, quad_xor(x, 0));
+}
+
+// 1/x (x normal) by the hardware estimate and two Newton steps, within an ulp
+__device__ __forceinline__ double rcp_nr(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
+// The basis on the support, phi[4 v + t - 1] = C(v, t) / C(n-1, t) for v = n - n'
+// empty modes, t = 1..4 (zero where C(n-1, t) is), by the whole workgroup
+__device__ __forceinline__ void fit_basis(int n, double *phi)
+{
+    const double ib[4] = {n > 1 ? 1.0 / (n - 1.0) : 0.0, n > 2 ? 2.0 / ((n - 1.0) * (n - 2.0)) : 0.0,
+                          n > 3 ? 6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)) : 0.0,
+                          n > 4 ? 24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0)) : 0.0};
+    for (int v = threadIdx.x; v < n; v += blockDim.x) {
+        phi[4 * v] = v * ib[0];
+        phi[4 * v + 1] = 0.5 * v * (v - 1) * ib[1];
+        phi[4 * v + 2] = v * (v - 1.0) * (v - 2.0) / 6.0 * ib[2];
+        phi[4 * v + 3] = v * (v - 1.0) * (v - 2.0) * (v - 3.0) / 24.0 * ib[3];
     }
 }
 
-// Cholesky solve of the JP x JP system H x = r (H from E, E2 as the covariance
+// Log-partition sum of the exp-polynomial with parameters c on n' = 1..n - v0,
+// the mean E[phi] and the second moments E2 (upper triangle, row-major) of its
+// JP features; gl: this lane's place in its quad.  JP is a template argument so
+// that every array index is static (kept in registers).  Exponents are taken
+// relative to the first term's (whose weight is then 1), or to the largest if
+// one would exceed 600.
+template <int JP>
+__device__ __forceinline__ void fit_eval(int n, int v0, LdsTab phi, int gl, const double *c, double &lse,
+                                         double *E, double *E2)
+{
+    double zref = 0.0;
+#pragma unroll
+    for (int t = 0; t < JP; ++t) zref -= c[t] * phi[4 * v0 + t];
+    for (int pass = 0;; ++pass) {
+        double s = 0.0, e[JP], e2[JP * (JP + 1) / 2], mx = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < JP; ++t) e[t] = 0.0;
+#pragma unroll
+        for (int t = 0; t < JP * (JP + 1) / 2; ++t) e2[t] = 0.0;
+        for (int v = v0 + gl; v < n; v += FIT_G) {
+            double f[JP], z = 0.0;
+#pragma unroll
+            for (int t = 0; t < JP; ++t) {
+                f[t] = phi[4 * v + t];
+                z -= c[t] * f[t];
+            }
+            mx = fmax(mx, z);
+            const double w = exp(z - zref);
+            s += w;
+            int k = 0;
+#pragma unroll
+            for (int t = 0; t < JP; ++t) {
+                const double wf = w * f[t];
+                e[t] += wf;
+#pragma unroll
+                for (int u = t; u < JP; ++u) e2[k++] += wf * f[u];
+            }
+        }
+        mx = quad_max(mx);
+        if (pass == 0 && mx - zref > 600.0) {
+            zref = mx;  // (no exponent is above it: once is enough)
+            continue;
+        }
+        s = quad_sum(s);
+        lse = zref + log(s);
+        const double is = rcp_nr(s);
+#pragma unroll
+        for (int t = 0; t < JP; ++t) E[t] = quad_sum(e[t]) * is;
+#pragma unroll
+        for (int k = 0; k < JP * (JP + 1) / 2; ++k) E2[k] = quad_sum(e2[k]) * is;
+        return;
+    }
+}
+
+// L D L^T solve of the JP x JP system H x = r (H from E, E2 as the covariance
 // of the features, damped by 1e-14 of its trace); false if H is not positive.
 template <int JP>
 __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, const double *r, double *x)
 {
-    double Hm[4][4];
+    double H[JP][JP], L[JP][JP], id[JP], tr = 0.0;
     int k = 0;
 #pragma unroll
     for (int t = 0; t < JP; ++t)
 #pragma unroll
-        for (int u = t; u < JP; ++u) Hm[t][u] = Hm[u][t] = E2[k++] - E[t] * E[u];
-    double tr = 0.0;
+        for (int u = t; u < JP; ++u) H[u][t] = E2[k++] - E[t] * E[u];
 #pragma unroll
-    for (int t = 0; t < JP; ++t) tr += Hm[t][t];
-#pragma unroll
-    for (int t = 0; t < JP; ++t) Hm[t][t] += 1e-14 * tr;
+    for (int t = 0; t < JP; ++t) tr += H[t][t];
     if (!(tr > 0.0)) return false;
-    double L[4][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+    for (int t = 0; t < JP; ++t) H[t][t] += 1e-14 * tr;
+    // column j: H[i][j] <- L_ij d_j, L[i][j] = L_ij
 #pragma unroll
     for (int j = 0; j < JP; ++j) {
-        double d = Hm[j][j];
 #pragma unroll
-        for (int l = 0; l < j; ++l) d -= L[j][l] * L[j][l];
-        if (!(d > 0.0)) return false;
-        L[j][j] = sqrt(d);
+        for (int l = 0; l < j; ++l)
 #pragma unroll
-        for (int i = j + 1; i < JP; ++i) {
-            double sv = Hm[i][j];
+            for (int i = j; i < JP; ++i) H[i][j] -= L[j][l] * H[i][l];
+        if (!(H[j][j] > 0.0)) return false;
+        id[j] = rcp_nr(H[j][j]);
 #pragma unroll
-            for (int l = 0; l < j; ++l) sv -= L[i][l] * L[j][l];
-            L[i][j] = sv / L[j][j];
-        }
+        for (int i = j + 1; i < JP; ++i) L[i][j] = H[i][j] * id[j];
     }
-    double y[4];
 #pragma unroll
     for (int i = 0; i < JP; ++i) {
-        double sv = r[i];
+        x[i] = r[i];
 #pragma unroll
-        for (int l = 0; l < i; ++l) sv -= L[i][l] * y[l];
-        y[i] = sv / L[i][i];
+        for (int l = 0; l < i; ++l) x[i] -= L[i][l] * x[l];
     }
 #pragma unroll
     for (int i = JP - 1; i >= 0; --i) {
-        double sv = y[i];
+        x[i] *= id[i];
 #pragma unroll
-        for (int l = i + 1; l < JP; ++l) sv -= L[l][i] * x[l];
-        x[i] = sv / L[i][i];
+        for (int l = i + 1; l < JP; ++l) x[i] -= L[l][i] * x[l];
     }
     return true;
 }
 
 // Max-entropy fit on n' = 1..n - v0 (v = n - n' empty modes, v >= v0) of the JP
-// moments m[]; returns 0, minus the log-partition sum (log q(n) when v0 = 0)
-// and the parameters in c_out on success.
+// moments m[] by Newton's method on the convex dual, from the parameters c;
+// returns 1 if a Hessian is singular, 2 after FIT_MAXIT steps, else 0, minus the log-partition sum (log q(n) when v0 = 0), the parameters
+// in c and the sensitivity u = H^{-1} m (H the covariance of the basis under
+// the fit; 1e300 where H is singular) on success.
 template <int JP>
-__device__ __forceinline__ int fit_last_point(int n, int v0, const double *m, double *logq, double *c_out)
+__device__ __forceinline__ int fit_newton(int n, int v0, LdsTab phi, int gl, const double *m, double *c,
+                                          double &logq, double *u)
 {
-    double ib[4] = {0, 0, 0, 0};
-    ib[0] = 1.0 / (n - 1.0);
-    if (JP > 1) ib[1] = 2.0 / ((n - 1.0) * (n - 2.0));
-    if (JP > 2) ib[2] = 6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0));
-    if (JP > 3) ib[3] = 24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0));
-    double c[4] = {0, 0, 0, 0};
+    double lse, E[JP], E2[JP * (JP + 1) / 2];
+    fit_eval<JP>(n, v0, phi, gl, c, lse, E, E2);
     for (int it = 0; it <= FIT_MAXIT; ++it) {
-        double lse, E[4], E2[10];
-        fit_eval<JP, true>(n, v0, ib, c, &lse, E, E2);
-        double g[4] = {0, 0, 0, 0}, mg[4] = {0, 0, 0, 0};
+        double mg[JP], slope = 0.0, L0 = lse;
         bool conv = true;
 #pragma unroll
         for (int t = 0; t < JP; ++t) {
-            g[t] = m[t] - E[t];
-            mg[t] = -g[t];
-            if (!(fabs(g[t]) <= 1e-15 + 1e-12 * fabs(m[t]))) conv = false;
+            mg[t] = E[t] - m[t];
+            L0 += c[t] * m[t];
+            if (!(fabs(mg[t]) <= 1e-15 + 1e-12 * fabs(m[t]))) conv = false;
         }
-        // Newton step H x = -g, H the covariance of the features
-        double x[4] = {0, 0, 0, 0};
+        // Newton step H x = -g, g = m - E, H the covariance of the features
+        double x[JP], cn[JP];
         if (!fit_solve<JP>(E, E2, mg, x)) return 1;
+#pragma unroll
+        for (int t = 0; t < JP; ++t) slope -= mg[t] * x[t];
+        double st = 1.0;
+        for (;;) {
+#pragma unroll
+            for (int t = 0; t < JP; ++t) cn[t] = c[t] + st * x[t];
+            fit_eval<JP>(n, v0, phi, gl, cn, lse, E, E2);
+            // (Armijo, while the predicted decrease is above the rounding of the
+            // objective; one polishing step after convergence)
+            if (conv || !(-slope > 1e-13 * fmax(1.0, fabs(L0)))) break;
+            double l2 = lse;
+#pragma unroll
+            for (int t = 0; t < JP; ++t) l2 += cn[t] * m[t];
+            if (l2 <= L0 + 1e-4 * st * slope || !(st > 1e-12)) break;
+            st *= 0.5;
+        }
+#pragma unroll
+        for (int t = 0; t < JP; ++t) c[t] = cn[t];
         if (conv) {
-            double cn[4] = {0, 0, 0, 0};
+            logq = -lse;
+            if (!fit_solve<JP>(E, E2, m, u))
 #pragma unroll
-            for (int t = 0; t < JP; ++t) cn[t] = c[t] + x[t];
-            double l2;
-            fit_eval<JP, false>(n, v0, ib, cn, &l2, nullptr, nullptr);
-            *logq = -l2;
-            if (c_out)
-#pragma unroll
-                for (int t = 0; t < JP; ++t) c_out[t] = cn[t];
+                for (int t = 0; t < JP; ++t) u[t] = 1e300;
             return 0;
         }
-        double L0 = lse, slope = 0.0;
-#pragma unroll
-        for (int t = 0; t < JP; ++t) {
-            L0 += c[t] * m[t];
-            slope += g[t] * x[t];
-        }
-        double st = 1.0;
-        if (-slope > 1e-13 * fmax(1.0, fabs(L0))) {
-            while (st > 1e-12) {
-                double cn[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int t = 0; t < JP; ++t) cn[t] = c[t] + st * x[t];
-                double l2;
-                fit_eval<JP, false>(n, v0, ib, cn, &l2, nullptr, nullptr);
-#pragma unroll
-                for (int t = 0; t < JP; ++t) l2 += cn[t] * m[t];
-                if (l2 <= L0 + 1e-4 * st * slope) break;
-                st *= 0.5;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < JP; ++t) c[t] += st * x[t];
     }
-    return 1;
+    return 2;
 }
 
 __device__ __forceinline__ void lse_add(double &mx, double &s, double v)
@@ -587,18 +670,21 @@ __device__ __forceinline__ cplx dft_tw(const cplx *W, int K, int e)
     return e < K / 2 ? W[e] : cneg(W[e - K / 2]);
 }
 // In-place forward DFT of X[0..K) in LDS, input placed by dft_pos, output in
-// natural order.  All threads of the block take part.
+// natural order.  All threads of the block (at least DFT_MINT) take part; in
+// the r-point combines each thread takes outputs o = tid, tid + nt, ...:
+// X[o] = sum_j W^{j o} F_j[o mod L], held until every input has been read.
+#define DFT_MINT 256
 __device__ void dft_lds(cplx *X, const cplx *W, const DftShape &d)
 {
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int K = d.K, L = d.L, hl = L / 2;
-    for (int half = 1; half < L; half <<= 1) {
-        // W_L^{pos L / (2 half)} = W^{pos r L / (2 half)}
-        const int tstep = d.r * (L / (2 * half));
+    const int K = d.K, L = d.L;
+    for (int lh = 0; lh < d.lgL; ++lh) {
+        // W_L^{pos L / (2 half)} = W^{pos r L / (2 half)}, half = 2^lh (b counts
+        // the butterflies over all blocks: whole groups of 2 half entries)
+        const int half = 1 << lh, tstep = d.r << (d.lgL - lh - 1);
         for (int b = tid; b < K / 2; b += nt) {
-            const int blk = b / hl, bb = b - blk * hl;
-            const int grp = bb / half, pos = bb - grp * half;
-            const int i = blk * L + grp * 2 * half + pos, j = i + half;
+            const int pos = b & (half - 1);
+            const int i = ((b >> lh) << (lh + 1)) + pos, j = i + half;
             const cplx w = W[pos * tstep];
             const cplx u = X[i], v = cmul(w, X[j]);
             X[i] = cadd(u, v);
@@ -607,63 +693,70 @@ __device__ void dft_lds(cplx *X, const cplx *W, const DftShape &d)
         __syncthreads();
     }
     if (d.r > 1) {
-        for (int m = tid; m < L; m += nt) {
-            cplx f[DFT_RMAX];
+        cplx out[GBS_KMAX / DFT_MINT];
 #pragma unroll
-            for (int j = 0; j < DFT_RMAX; ++j)
-                if (j < d.r) f[j] = j == 0 ? X[m] : cmul(dft_tw(W, K, j * m), X[j * L + m]);
-            for (int s2 = 0; s2 < d.r; ++s2) {
-                cplx acc = f[0];
-                int e = 0;  // (j s2 mod r) L, stepped by s2 L
-#pragma unroll
-                for (int j = 1; j < DFT_RMAX; ++j) {
-                    if (j >= d.r) continue;
-                    e += s2 * L;
-                    if (e >= K) e -= K;
-                    acc = cadd(acc, cmul(dft_tw(W, K, e), f[j]));
-                }
-                X[s2 * L + m] = acc;
+        for (int i = 0; i < GBS_KMAX / DFT_MINT; ++i) {
+            const int o = tid + i * nt;
+            if (o >= K) continue;
+            const int m = o & (L - 1);
+            cplx acc = X[m];
+            int e = 0;  // j o mod K
+#pragma unroll 4
+            for (int j = 1; j < d.r; ++j) {
+                e += o;
+                if (e >= K) e -= K;
+                acc = cfma(dft_tw(W, K, e), X[j * L + m], acc);
             }
+            out[i] = acc;
         }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < GBS_KMAX / DFT_MINT; ++i)
+            if (tid + i * nt < K) X[tid + i * nt] = out[i];
         __syncthreads();
     }
 }
 
-
 // Result of one sector fit with at most JM moments: log q(n), the fitted
-// parameters and the moments (zero past the ones used), how many moments were
-// used, and bad != 0 if no fit succeeded.
+// parameters, the moments (zero past the ones used) and the sensitivity of log
+// q(n) to them (d log q / d m_t = -u_t, u = H^{-1} m; zero past the ones used),
+// how many moments were used, and bad != 0 if no fit succeeded.
 template <int JM>
 struct SectorFitT {
     double lq;
-    double c[JM];
-    double m[JM];
+    double c[JM], m[JM], u[JM];
     int jr, bad;
 };
-using SectorFit = SectorFitT<3>;
 
-// Fit one sector from its tilted moments t0..t4 (t0 > 0; moments past JM are
-// ignored) on n' = 1..n - v0 (v0 > 0: a sector with fewer photons than
+// Fit one sector by a quad from its tilted moments t0..t4 (t0 > 0; moments past
+// JM are ignored) on n' = 1..n - v0 (v0 > 0: a sector with fewer photons than
 // modes): the moments m_t = tau_t / (tau_0 C(n-1,t)) are used up to the
 // longest feasible prefix (0 < m_t < 1, decreasing in t, since
 // 0 <= phi_{t+1} <= phi_t <= 1).  A moment whose true value lies below the
 // transform's rounding floor can come out infeasible; it is then dropped, and
 // so is the next one if the fit fails.  With m_1 <= 0 every clicked mode
-// fires: q(n) = 1.  The moments arrive by value and the fit runs out of line,
-// so that callers index nothing at run time.
+// fires: q(n) = 1.
+// The fit starts from cs where that holds the parameters of js = jr moments (a
+// neighbouring sector's), else from the geometric distribution with the first
+// moment (its limit for a long support), and again from c = 0 where a Hessian
+// on the way was singular: the dual is convex, so the start only sets the
+// number of steps (measured with orders 2 / 3: 11 / 14 from c = 0, 7 / 12 from
+// the geometric one, 4 from a neighbour's).  The moments arrive by value and the fit runs out of line, so
+// that callers index nothing at run time.
 template <int JM>
-__device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, double t0, double t1, double t2,
-                                                  double t3, double t4)
+__device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, LdsTab phi, int gl, double t0,
+                                                  double t1, double t2, double t3, double t4, int js, double c1,
+                                                  double c2, double c3, double c4)
 {
     SectorFitT<JM> r;
     const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
                             6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
                             24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
-    const double tau[4] = {t1, t2, t3, t4};
+    const double tau[4] = {t1, t2, t3, t4}, cs[4] = {c1, c2, c3, c4};
 #pragma unroll
     for (int t = 0; t < JM; ++t) {
         r.m[t] = t < jp ? tau[t] / t0 * binv[t] : 0.0;
-        r.c[t] = 0.0;
+        r.c[t] = r.u[t] = 0.0;
     }
     int jr = 0;
 #pragma unroll
@@ -679,11 +772,20 @@ __device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, double 
     }
     int bad = 1;
     while (jr >= 1 && bad) {
-        switch (jr) {
-        case 1: bad = fit_last_point<1>(n, v0, r.m, &r.lq, r.c); break;
-        case 2: bad = fit_last_point<2>(n, v0, r.m, &r.lq, r.c); break;
-        case 3: bad = fit_last_point<JM >= 3 ? 3 : 1>(n, v0, r.m, &r.lq, r.c); break;
-        default: bad = fit_last_point<JM >= 4 ? 4 : 1>(n, v0, r.m, &r.lq, r.c); break;
+        // starts: 2 a neighbour's, 1 geometric, 0 zero
+        const double mu = r.m[0] * (n - 1.0);
+        bad = 1;
+        for (int start = js == jr ? 2 : 1; start >= 0 && bad == 1; --start) {
+            if (start == 1 && (v0 > 0 || !(mu < 0.5 * (n - 1.0)))) continue;
+#pragma unroll
+            for (int t = 0; t < JM; ++t) r.c[t] = start == 2 && t < jr ? cs[t] : 0.0;
+            if (start == 1) r.c[0] = (n - 1.0) * log1p(1.0 / mu);
+            switch (jr) {
+            case 1: bad = fit_newton<1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
+            case 2: bad = fit_newton<JM >= 2 ? 2 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
+            case 3: bad = fit_newton<JM >= 3 ? 3 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
+            default: bad = fit_newton<JM >= 4 ? 4 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
+            }
         }
         if (bad) --jr;
     }
@@ -693,40 +795,12 @@ __device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, double 
 #pragma unroll
         for (int t = 0; t < JM; ++t) r.c[t] = 0.0;
     }
+#pragma unroll
+    for (int t = 0; t < JM; ++t)
+        if (t >= jr) r.u[t] = 0.0;
     r.jr = jr;
     r.bad = bad;
     return r;
-}
-
-// Sensitivity of a fitted sector's log q(n) to its moments: d log q / d m_t =
-// -u_t with u = H^{-1} m, H the covariance of the basis under the fitted
-// distribution (t < jr; zero for the moments the fit did not use).
-template <int JM>
-__device__ __noinline__ void fit_sensitivity(int n, const SectorFitT<JM> &f, double *u)
-{
-    const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
-                            6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
-                            24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
-    double lse, E[4], E2[10];
-    bool ok = true;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) u[t] = 0.0;
-    switch (f.jr) {
-    case 0: return;
-    case 1: fit_eval<1, true>(n, 0, binv, f.c, &lse, E, E2); ok = fit_solve<1>(E, E2, f.m, u); break;
-    case 2: fit_eval<2, true>(n, 0, binv, f.c, &lse, E, E2); ok = fit_solve<2>(E, E2, f.m, u); break;
-    case 3:
-        fit_eval<JM >= 3 ? 3 : 1, true>(n, 0, binv, f.c, &lse, E, E2);
-        ok = fit_solve<JM >= 3 ? 3 : 1>(E, E2, f.m, u);
-        break;
-    default:
-        fit_eval<JM >= 4 ? 4 : 1, true>(n, 0, binv, f.c, &lse, E, E2);
-        ok = fit_solve<JM >= 4 ? 4 : 1>(E, E2, f.m, u);
-        break;
-    }
-    if (!ok)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) u[t] = 1e300;
 }
 
 }  // namespace

@@ -13,9 +13,9 @@
 // M = V diag(d) V^T) this is A_bar = V R V^T with
 //   R += Re[(w/2) d_i d_j (V^T Z V)_ij] + delta_ij Re[beta (rho dr_i - w d_i)/2],
 // dr_i = 1/(1 + rho(alpha_i - 1)).  Kernels:
-//   k_adj_fit      per row: the sector transform and fits again; the log-sum and
-//                  each fit differentiated (implicitly: d log q / dm = -H^{-1} m,
-//                  H the covariance of the fitted basis); the sector cotangents
+//   k_dft_fit      (approx.hip) per row, with the forward: the log-sum and each fit
+//                  differentiated (implicitly: d log q / dm = -H^{-1} m, H the
+//                  covariance of the fitted basis); the sector cotangents
 //                  pushed back through the FFT to alpha_t(w_q)
 //   k_adj_contour  per (row, 64 contour points): M(w) and the clusters again
 //                  (the same work units as the forward, in an order that spreads
@@ -44,152 +44,6 @@
 static_assert(GBS_ADJ_CHUNK_BIG <= ADJ_QCHUNK, "one pass of points per item fits s_wq");
 
 namespace {
-
-// ---------------------------------------------------------------------------
-// k_adj_fit
-// ---------------------------------------------------------------------------
-template <int ORDER>
-__global__ __launch_bounds__(FIT_THREADS) void k_adj_fit(const int *__restrict__ offsets,
-                                                         const RowPlan *__restrict__ rows,
-                                                         const cplx *__restrict__ sw,
-                                                         const double *__restrict__ dl,
-                                                         const int *__restrict__ status,
-                                                         cplx *__restrict__ asw)
-{
-    extern __shared__ __attribute__((aligned(16))) double sh[];
-    __shared__ double red[FIT_THREADS];
-    const int p = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-    const int n = offsets[p + 1] - offsets[p];
-    const RowPlan rp = rows[p];
-    const double wp = dl[p];
-    // (rows without a forward result take no part)
-    if (n == 0 || rp.status != 0 || (status[p] & GBS_PS_FAILED) || wp == 0.0 || !isfinite(wp)) {
-        for (int i = tid; i < (ORDER + 1) * GBS_QCAP; i += nt)
-            asw[(long)p * (ORDER + 1) * GBS_QCAP + i] = cmk(0.0, 0.0);
-        return;
-    }
-    const int K = rp.K, Q = K / 2 + 1, jp = min(ORDER, n - 1);
-    const DftShape dsh = dft_shape(K);
-    cplx *X = (cplx *)sh;
-    cplx *W = X + K;
-    for (int m = tid; m < K / 2; m += nt) {
-        const cplx u = unit_root(m, K);
-        W[m] = cmk(u.re, -u.im);
-    }
-    // (loops over t and j unrolled: every index into the per-thread arrays is static)
-    constexpr int NT = ORDER >= 4 ? 5 : 4;  // moments held per sector
-    constexpr int JM = ORDER >= 4 ? 4 : 3;  // most moments a fit uses
-    double tau[FIT_KPT][NT];
-    const double invK = 1.0 / K;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (t <= ORDER && t <= jp) {
-            const cplx *src = sw + ((long)p * (ORDER + 1) + t) * GBS_QCAP;
-            for (int q = tid; q < K; q += nt) {
-                const cplx v = q < Q ? src[q] : cmk(src[K - q].re, -src[K - q].im);
-                X[dft_pos(dsh, q)] = v;
-            }
-            __syncthreads();
-            dft_lds(X, W, dsh);
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) {
-                const int kap = n + tid + nt * j;
-                tau[j][t] = kap < K ? X[kap].re * invK : 0.0;
-            }
-            __syncthreads();
-        } else {
-#pragma unroll
-            for (int j = 0; j < FIT_KPT; ++j) tau[j][t] = 0.0;
-        }
-    }
-    double tmax = 0.0;
-#pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j)
-        if (n + tid + nt * j < K) tmax = fmax(tmax, tau[j][0]);
-    tmax = block_max(tmax, red);
-    const double thr = 1e-14 * tmax;
-    // forward pass again: which sectors are fitted, their log p_hat and fits
-    double ell[FIT_KPT];
-    SectorFitT<JM> fits[FIT_KPT];
-    double fm = -INFINITY, fs = 0.0, lower = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j) {
-        if (j == 1) {
-            double mx = block_max(fm, red);
-            double sm = block_sum(fm == -INFINITY ? 0.0 : fs * exp(fm - mx), red);
-            lower = sm > 0.0 ? mx + log(sm) : -INFINITY;
-        }
-        ell[j] = -INFINITY;
-        fits[j].jr = -1;
-        const int kap = n + tid + nt * j;
-        if (kap >= K) continue;
-        const double t0 = tau[j][0];
-        if (!(t0 >= thr) || !(t0 > 0.0)) continue;
-        const double lw = log(t0) + rp.log_g_rho - kap * rp.log_rho;
-        if (lw < lower + log(1e-17)) continue;
-        const SectorFitT<JM> f = fit_sector<JM>(n, 0, jp, t0, tau[j][1], tau[j][2], tau[j][3],
-                                                 ORDER >= 4 ? tau[j][NT - 1] : 0.0);
-        if (f.bad) continue;
-        fits[j] = f;
-        ell[j] = lw + f.lq;
-        lse_add(fm, fs, ell[j]);
-    }
-    const double fmx = block_max(fm, red);
-    const double fsum = block_sum(fm == -INFINITY ? 0.0 : fs * exp(fm - fmx), red);
-    const double total = fmx + log(fsum);
-    // sector cotangents: pi_kappa w_p d ell / d tau_t
-    const double binv[4] = {1.0 / (n - 1.0), 2.0 / ((n - 1.0) * (n - 2.0)),
-                            6.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0)),
-                            24.0 / ((n - 1.0) * (n - 2.0) * (n - 3.0) * (n - 4.0))};
-    double tbar[FIT_KPT][NT];
-#pragma unroll
-    for (int j = 0; j < FIT_KPT; ++j) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) tbar[j][t] = 0.0;
-        const int jr = fits[j].jr;
-        if (jr < 0 || !(fsum > 0.0)) continue;
-        const double pi = wp * exp(ell[j] - total);
-        const double t0 = tau[j][0];
-        const double *m = fits[j].m;
-        // H = Cov_c[phi] at the fitted c; u = H^{-1} m (zero if H is singular)
-        double u[4];
-        fit_sensitivity<JM>(n, fits[j], u);
-        if (!(fabs(u[0]) < 1e299))
-#pragma unroll
-            for (int t = 0; t < 4; ++t) u[t] = 0.0;
-        double um = 0.0;
-#pragma unroll
-        for (int t = 0; t < JM; ++t)
-            if (t < jr) um += u[t] * m[t];
-        tbar[j][0] = pi * (1.0 + um) / t0;
-#pragma unroll
-        for (int t = 1; t <= JM; ++t)
-            if (t <= jr) tbar[j][t] = -pi * u[t - 1] * binv[t - 1] / t0;
-    }
-    // alpha_t(w_q) = c_q FFT(tbar_t)[q], c_q = 1/K at q = 0, K/2 and 2/K otherwise
-#pragma unroll
-    for (int t = 0; t <= ORDER; ++t) {
-        cplx *dst = asw + ((long)p * (ORDER + 1) + t) * GBS_QCAP;
-        if (t > jp) {
-            for (int q = tid; q < Q; q += nt) dst[q] = cmk(0.0, 0.0);
-            continue;
-        }
-        for (int k = tid; k < K; k += nt) X[k] = cmk(0.0, 0.0);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < FIT_KPT; ++j) {
-            const int kap = n + tid + nt * j;
-            if (kap < K) X[dft_pos(dsh, kap)] = cmk(tbar[j][t], 0.0);
-        }
-        __syncthreads();
-        dft_lds(X, W, dsh);
-        for (int q = tid; q < Q; q += nt) {
-            const double cq = (q == 0 || q == K / 2) ? invK : 2.0 * invK;
-            dst[q] = cscale(X[q], cq);
-        }
-        __syncthreads();
-    }
-}
 
 // ---------------------------------------------------------------------------
 // k_adj_contour
@@ -2166,13 +2020,7 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
     hipStream_t st = ctx->stream;
     DevModel &m = ctx->model;
     const int P = pl->P, nmax = pl->max_n, M = m.M;
-    size_t lds_f = sizeof(cplx) * (GBS_KMAX + GBS_KMAX / 2);
-    if (int rc = func_lds_limit(ctx, (const void *)k_adj_fit<ORDER>, (int)lds_f)) return rc;
-    int ts = timer_begin(ctx, TG_ADJ_FIT);
-    hipLaunchKernelGGL(k_adj_fit<ORDER>, dim3(P), dim3(FIT_THREADS), lds_f, st, pl->d_offsets,
-                       pl->d_rows, pl->d_sw, dl, status, pl->d_asw);
-    timer_end(ctx, ts);
-    ts = timer_begin(ctx, TG_ADJ_CLUSTER);
+    int ts = timer_begin(ctx, TG_ADJ_CLUSTER);
     hipLaunchKernelGGL(k_adj_items, dim3(1), dim3(1024), 0, st, P, pl->nbig, pl->d_offsets, pl->d_perm,
                        pl->d_rows, pl->d_aitems, pl->d_roff, pl->d_ritem0, pl->d_counter, pl->d_axq);
     if constexpr (ORDER == 2) {
@@ -2292,8 +2140,6 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
 
 }  // namespace
 
-int adj_workspace(gbs_ctx *ctx, gbs_plan *pl);
-
 // complex entries of k_adj_pairs_big's per-workgroup scratch for rows of up to
 // n clicks: the four 16 x 16 planes of each upper 16 x 16 mode block of Z(w),
 // then each block's partial sums of Z's mode diagonals (2 x 16 x 3)
@@ -2306,8 +2152,6 @@ long long adj_pair_scratch(int n)
 int approx_backward(gbs_ctx *ctx, gbs_plan *pl, const double *dl_dev, const int32_t *status_dev,
                     double *grad_r_dev, double *grad_eta_dev)
 {
-    int rc = adj_workspace(ctx, pl);
-    if (rc) return rc;
     if (pl->P == 0) {
         hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, ctx->stream, (long)ctx->model.M, grad_r_dev);
         hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, ctx->stream, (long)ctx->model.M, grad_eta_dev);

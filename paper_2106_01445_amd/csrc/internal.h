@@ -180,7 +180,9 @@ int set_err(gbs_ctx *ctx, int code, const std::string &msg);
 // kernels' host launchers ----------------------------------------------------
 int model_build_dev(gbs_ctx *ctx, const double *ure, const double *uim, const double *r, const double *eta,
                     const double *sigma_dev, bool sync);
-int approx_forward(gbs_ctx *ctx, gbs_plan *plan, double *logp_dev, int32_t *status_dev);
+int approx_forward(gbs_ctx *ctx, gbs_plan *plan, double *logp_dev, int32_t *status_dev,
+                   const double *dl_dev = nullptr);
+int adj_workspace(gbs_ctx *ctx, gbs_plan *plan);
 // status_dev[p] |= bits for every row (stream-ordered; NULL status: nothing)
 int status_or(gbs_ctx *ctx, int P, int32_t *status_dev, int bits);
 int exact_run(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, double *p,

@@ -972,22 +972,23 @@ __global__ __launch_bounds__(DIST_THREADS) void k_dist_fit(const int *__restrict
 // ---------------------------------------------------------------------------
 // k_retilt: the rows marked for a re-tilt get a contour whose tilted mean
 // photon number is kbar (radius, size and log G_0(rho) from their spectrum),
-// one thread per row.
+// one wavefront per row.
 // ---------------------------------------------------------------------------
-__global__ void k_retilt(int P, const int *__restrict__ offsets, const double *__restrict__ alpha,
-                         RowPlan *__restrict__ rows)
+__global__ __launch_bounds__(256) void k_retilt(int P, const int *__restrict__ offsets,
+                                                const double *__restrict__ alpha, RowPlan *__restrict__ rows)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= P) return;
+    const int flags = rows[p].flags;
+    if (!(flags & GBS_ROW_RETILT)) return;
     RowPlan rp = rows[p];
-    if (!(rp.flags & GBS_ROW_RETILT) || rp.status != 0) return;
+    if (rp.status != 0) return;
     const int o = offsets[p], n = offsets[p + 1] - o;
-    const int flags = rp.flags;
     const double logdet_q = -2.0 * rp.log_pvac - rp.logdet_a;
     const double dev = rp.rconv < 1e299 ? 1.0 / rp.rconv : 0.0;
-    row_plan(rp, n, alpha + 2 * o, 1, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
+    row_plan(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
     rp.flags = flags;
-    rows[p] = rp;
+    if (lane == 0) rows[p] = rp;
 }
 
 template <int ORDER, bool BIG, class C, bool RERUN = false>
@@ -1086,7 +1087,7 @@ int launch_order(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status, cons
     if (mixed || retilt) {
         if ((rc = func_lds_limit(ctx, (const void *)k_dft_fit<ORDER, 1, GRAD>, (int)lds_f))) return rc;
         ts = timer_begin(ctx, TG_PASS2);
-        hipLaunchKernelGGL(k_retilt, dim3((P + 255) / 256), dim3(256), 0, st, P, pl->d_offsets, pl->d_alpha,
+        hipLaunchKernelGGL(k_retilt, dim3((P + 3) / 4), dim3(256), 0, st, P, pl->d_offsets, pl->d_alpha,
                            pl->d_rows);
         hipLaunchKernelGGL(k_build_items, dim3(1), dim3(1024), 0, st, P, nbig, pl->qchunk, pl->d_offsets,
                            pl->d_perm, pl->d_rows, pl->d_items, pl->d_counter, GBS_PS_ESCALATED | GBS_ROW_RETILT);

@@ -1,262 +1,435 @@
-// Per-row set-up of the order-j estimate: A = (Q^{-1})_CC = V diag(alpha) V^T
-// with the working matrices in HBM (L2-resident), one workgroup per row.
+// Per-row set-up of the order-j estimate: A = (Q^{-1})_CC = V diag(alpha) V^T,
+// one workgroup per row.
 //
 //   1. Householder reduction of A to tridiagonal form (symmetric rank-2
 //      updates of the trailing block, Golub & Van Loan, Matrix Computations,
-//      section 8.3.1);
-//   2. the orthogonal factor accumulated explicitly, last reflector first;
+//      section 8.3.1), the reflectors kept in the rows they annihilate;
+//   2. the orthogonal factor accumulated in their place, last reflector first;
 //   3. implicit symmetric QR steps with Wilkinson shifts on the tridiagonal
-//      matrix (ibid., section 8.3): one thread chases the bulge of a step with
-//      plane rotations and records them, then every thread applies them to its
-//      own row of the factor;
-//   4. the contour plan of the row from its spectrum.
-// The factor is kept column-major, which is the layout the contour kernels
+//      matrix (ibid., section 8.3): wavefront 0 chases the bulge of a step with
+//      plane rotations and records them, while the other wavefronts apply the
+//      rotations of the step before to the rows of the factor;
+//   4. the contour plan of the row from its spectrum, by wavefront 0.
+// The factor comes out column-major, which is the layout the contour kernels
 // read (eigenvector k contiguous).
+//
+// What bounds it: serial chains.  A Householder step is two reductions over the
+// trailing block's columns between two barriers (about 2500 cycles at 28
+// columns); a QR step is a chain of rotations, about 45 instructions each that a
+// single wavefront issues every 8 cycles, and 1.7 such steps per eigenvalue
+// follow one another.  So the columns' sums are split over the wavefronts and
+// met in LDS with one barrier, norms and inner products are formed by every
+// wavefront for itself on the DPP paths, the chase takes one inverse root per
+// rotation and no memory access, and the factor's update runs beside it.  Rows
+// of up to GBS_NSMALL clicks hold the matrix in LDS (57 KB at 40 clicks, 8 KB at
+// 14); larger ones in global memory (L2).  Against the matrix in global memory
+// for every row, one lane's chase with two divisions and a root between memory
+// accesses, the factor's update after it, and the plan's bisection in one
+// thread (us): 64 rows of 6-14 clicks 395 -> 165, one of 30 clicks 1030 -> 280,
+// 4096 of 15-40 clicks 7750 -> 5000, 512 of 40-110 clicks 22200 -> 9700.
 #include "contour_common.h"
-
-#define EIG_THREADS 256
 
 namespace {
 
-__global__ __launch_bounds__(EIG_THREADS) void k_eig(
+// bytes of LDS: each wavefront's partial sums, a reflector and its partner (in
+// their place two steps' rotations later), diagonal, couplings, and the matrix
+// of the small rows
+__host__ __device__ constexpr int eig_lds(int N, int waves, bool mat)
+{
+    return 8 * ((waves + 2) * N + 2 * N + (mat ? N * (N + 1) : 0));
+}
+
+// The active block [lo, hi] of the tridiagonal matrix below top: hi the highest
+// index at or below top whose coupling to the row above is not negligible (the
+// negligible ones set to zero), lo the lowest index joined to hi by
+// non-negligible couplings (its own set to zero); 64 candidates per ballot.
+// hi = 0: none is left.
+__device__ __forceinline__ void active_block(const double *dg, double *ed, int top, int lane, int &lo, int &hi)
+{
+    const double eps = 2.220446049250313e-16;
+    hi = lo = 0;
+    bool have = false;
+    for (int base = top; base >= 0; base -= 64) {
+        // lane: index idx, whether it is joined to the one above (ed[i] is
+        // negligible when |ed[i]| <= eps (|dg[i]| + |dg[i+1]|))
+        const int idx = base - lane, i = max(idx, 1);
+        const double e = fabs(ed[i - 1]), g = fabs(dg[i - 1]) + fabs(dg[i]);
+        const bool joined = idx > 0 && !(e <= eps * g);
+        unsigned long long bal = __ballot(joined);
+        int from = 0;  // lanes before this one are done with
+        if (!have) {
+            if (bal == 0ull) continue;
+            from = __ffsll((long long)bal) - 1;
+            hi = base - from;
+            have = true;
+        }
+        const unsigned long long open = ~bal & (~0ull << from);
+        if (open != 0ull) {
+            lo = base - (__ffsll((long long)open) - 1);
+            break;
+        }
+    }
+    for (int idx = hi + 1 + lane; idx <= top; idx += 64) ed[idx - 1] = 0.0;
+    if (lo > 0 && lane == 0) ed[lo - 1] = 0.0;
+}
+
+// 1/sqrt(x), x normal: the hardware's estimate (about 24 bits) and one
+// third-order step
+__device__ __forceinline__ double rsq_nr(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+__device__ __forceinline__ double lane_value(double x, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
+// One implicit QR step on [lo, hi] (hi > lo, uniform) by one wavefront, every
+// lane following the same chain; the rotations into rot.  64 steps of the chain
+// at a time, the block's entries come from and the results go to registers,
+// lane k those of the chunk's step k, so that no memory access stands in it.
+__device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, int lane, double2 *rot)
+{
+    // Wilkinson shift: the eigenvalue of the trailing 2 x 2 block closer to its
+    // last diagonal entry
+    const double e = ed[hi - 1], dh = dg[hi], dd = 0.5 * (dg[hi - 1] - dh);
+    const double q2 = fma(dd, dd, e * e);  // (> 0: e is not negligible)
+    const double den = dd + copysign(q2 > 1e-290 ? q2 * rsq_nr(q2) : sqrt(q2), dd);
+    const double mu = fabs(den) > 1e-290 ? fma(-e * e, rcp_nr(den), dh) : dh;
+    // a = dg[k] and b = ed[k] as rotated by the previous step
+    double a = dg[lo], b = ed[lo];
+    double x = a - mu, z = b;
+    for (int cb = lo; cb < hi; cb += 64) {
+        const int k0 = cb + lane, len = min(64, hi - cb);
+        // step k's d = dg[k + 1], en = ed[k + 1] (0 at the block's end)
+        const double dv = k0 < hi ? dg[k0 + 1] : 0.0, ev = k0 + 1 < hi ? ed[k0 + 1] : 0.0;
+        double nd = 0.0, nr = 0.0, nc = 1.0, ns = 0.0;
+        for (int k = 0; k < len; ++k) {
+            const double d = lane_value(dv, k), en = lane_value(ev, k);
+            // G_k on (k, k+1): c = x/r, s = z/r, r = (x^2 + z^2)^{1/2}; the next
+            // step's entries come from x, z and 1/r^2 directly
+            const double xx = x * x, zz = z * z, r2 = xx + zz, xz = x * z;
+            const double y = rsq_nr(r2), rc = y * y;
+            double c = x * y, sn = z * y, r = r2 * y;
+            double ek = fma(xz, d - a, (xx - zz) * b) * rc;
+            double dn = fma(-2.0 * xz, b, fma(xx, d, zz * a)) * rc;
+            if (!(r2 > 1e-290)) {
+                // (both entries negligible, or their squares out of range)
+                r = hypot(x, z);
+                c = r != 0.0 ? x / r : 1.0;
+                sn = r != 0.0 ? z / r : 0.0;
+                ek = fma(c * sn, d - a, (c * c - sn * sn) * b);
+                dn = fma(-2.0 * c * sn, b, fma(c * c, d, sn * sn * a));
+            }
+            const double nk = (a + d) - dn;
+            const bool me = lane == k;
+            nd = me ? nk : nd;
+            nr = me ? r : nr;
+            nc = me ? c : nc;
+            ns = me ? sn : ns;
+            x = ek;
+            z = sn * en;
+            b = c * en;
+            a = dn;
+        }
+        if (lane < len) {
+            dg[k0] = nd;
+            rot[k0] = make_double2(nc, ns);
+            if (k0 > lo) ed[k0 - 1] = nr;  // the bulge is gone
+        }
+    }
+    if (lane == 0) {
+        dg[hi] = a;
+        ed[hi - 1] = x;
+    }
+}
+
+// MAT: the matrix in LDS, row-major with odd stride N + 1 (rows of up to
+// GBS_NSMALL clicks); else in wbuf (row-major, stride N), and the factor in
+// place in vt_out from step 3 on.
+template <bool MAT, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_eig(
     int M, const double *__restrict__ qi, const double *__restrict__ scal,
     const int *__restrict__ offsets, const int *__restrict__ modes, const int *__restrict__ perm,
     const long long *__restrict__ voff, double *__restrict__ wbuf, double *__restrict__ alpha_out,
     double *__restrict__ vt_out, RowPlan *__restrict__ rows, int frozen)
 {
-    __shared__ double red[EIG_THREADS];
-    __shared__ double v[EIG_THREADS], w[EIG_THREADS];
-    __shared__ double dg[EIG_THREADS], ed[EIG_THREADS], tau[EIG_THREADS];
-    __shared__ double rc[EIG_THREADS], rs[EIG_THREADS];
-    __shared__ int s_m, s_lo, s_fail;
+    constexpr int NW = THREADS / 64;
+    constexpr int NJ = ((MAT ? 2 * GBS_NSMALL : 2 * GBS_MAX_N_APPROX) + 63) / 64;  // columns per lane
+    extern __shared__ __attribute__((aligned(16))) double sh[];
+    __shared__ int s_lo[2], s_hi[2];
     const int p = perm[blockIdx.x];
     const int o = offsets[p], n = offsets[p + 1] - o, N = 2 * n;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const double logdetQ = scal[0];
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long long vo = voff[p];
-    double *W = wbuf + 2 * vo;  // A, row-major, reduced in place (2 N^2 per row reserved)
-    double *Qf = vt_out + vo;   // orthogonal factor, column-major: Qf[c * N + r]
+    static_assert(NW >= 2, "two steps' rotations fit the reduction's arrays");
+    double *part = sh;                       // NW x N partial sums
+    double *v = part + NW * N, *w = v + N;   // the reflector, its partner in the rank-2
+                                             // update (every wavefront writes both, alike)
+    double2 *rot = (double2 *)sh;            // two steps', N each
+    double *dg = w + N, *ed = dg + N;
+    double *W = MAT ? ed + N : wbuf + 2 * vo;
+    const int ld = MAT ? N + 1 : N;
+    double *Qf = vt_out + vo;  // orthogonal factor, column-major: Qf[c * N + r]
     const int D = 2 * M;
-    for (int idx = tid; idx < N * N; idx += nt) {
+    for (int idx = tid; idx < N * N; idx += THREADS) {
         const int i = idx / N, j = idx - i * N;
         const int ri = i < n ? modes[o + i] : modes[o + i - n] + M;
         const int rj = j < n ? modes[o + j] : modes[o + j - n] + M;
-        W[idx] = qi[(long)ri * D + rj];
+        W[i * ld + j] = qi[(long)ri * D + rj];
     }
     __syncthreads();
     // 1. reduction: step k annihilates W[k][k+2..], reflector v (length m = N-k-1)
-    //    stored in row k right of the diagonal, tau[k]; diagonal dg, coupling ed
+    //    stored in row k right of the diagonal, its tau on the diagonal (dg, ed
+    //    hold the tridiagonal matrix); lanes take the trailing block's columns,
+    //    wavefronts its rows in turn
     for (int k = 0; k + 2 < N; ++k) {
         const int m = N - k - 1;
-        double *Wk = W + (long)k * N + k + 1;
+        double *Wk = W + (long)k * ld + k + 1, *W2 = Wk + ld;
         double sg = 0.0;
-        for (int i = tid; i < m; i += nt) {
+        for (int i = lane; i < m; i += 64) {
             const double x = Wk[i];
-            v[i] = x;
-            if (i > 0) sg += x * x;
-        }
-        sg = block_sum(sg, red);
-        if (tid == 0) {
-            const double x0 = v[0];
-            dg[k] = W[(long)k * N + k];
-            if (sg == 0.0) {
-                tau[k] = 0.0;
-                ed[k] = x0;
-            } else {
-                const double al = -copysign(sqrt(x0 * x0 + sg), x0);
-                const double v0 = x0 - al;
-                v[0] = v0;
-                tau[k] = 2.0 / (v0 * v0 + sg);
-                ed[k] = al;
+            if (i > 0) {
+                v[i] = x;
+                sg = fma(x, x, sg);
             }
         }
-        __syncthreads();
-        const double tk = tau[k];
-        for (int i = tid; i < m; i += nt) Wk[i] = v[i];
+        sg = wave_sum_dpp(sg);
+        const double x0 = Wk[0];
+        double tk = 0.0, al = x0, v0 = x0;
+        if (sg != 0.0) {
+            // (any al and tau as consistent as these to rounding will do: H is
+            // orthogonal to the rounding of tau, and couples row k by al)
+            const double r2 = fma(x0, x0, sg);
+            al = -copysign(r2 > 1e-290 ? r2 * rsq_nr(r2) : sqrt(r2), x0);
+            v0 = x0 - al;
+            const double vv = fma(v0, v0, sg);
+            tk = vv > 1e-290 ? 2.0 * rcp_nr(vv) : 2.0 / vv;
+        }
+        if (lane == 0) v[0] = v0;
         if (tk != 0.0) {
             // p = tau W2 v (W2 symmetric: column sums), then w = p - (tau/2)(p.v) v
-            double *W2 = W + (long)(k + 1) * N + k + 1;
-            double pv = 0.0;
-            for (int j = tid; j < m; j += nt) {
-                double s = 0.0;
-                for (int i = 0; i < m; ++i) s = fma(W2[(long)i * N + j], v[i], s);
-                w[j] = tk * s;
-                pv += w[j] * v[j];
+            for (int j = lane; j < m; j += 64) {
+                double s[4] = {0.0, 0.0, 0.0, 0.0};
+                int i = wid;
+                for (; i + 3 * NW < m; i += 4 * NW) {
+                    double x[4], y[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        x[u] = W2[i * ld + j + u * NW * ld];
+                        y[u] = v[i + u * NW];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) s[u] = fma(x[u], y[u], s[u]);
+                }
+                for (; i < m; i += NW) s[0] = fma(W2[i * ld + j], v[i], s[0]);
+                part[wid * N + j] = (s[0] + s[1]) + (s[2] + s[3]);
             }
-            pv = block_sum(pv, red);
+        }
+        __syncthreads();  // (also: row k has been read by every wavefront)
+        if (wid == 0) {
+            for (int i = lane; i < m; i += 64) Wk[i] = v[i];
+            if (lane == 0) {
+                dg[k] = W[(long)k * ld + k];
+                ed[k] = al;
+                W[(long)k * ld + k] = tk;
+            }
+        }
+        if (tk != 0.0) {
+            // (w is written once, when it is final: all wavefronts write it)
+            double pj[NJ], pv = 0.0;
+#pragma unroll
+            for (int u = 0; u < NJ; ++u) {
+                const int j = lane + 64 * u;
+                pj[u] = 0.0;
+                if (j >= m) continue;
+                double s = part[j];
+#pragma unroll
+                for (int t = 1; t < NW; ++t) s += part[t * N + j];
+                pj[u] = tk * s;
+                pv = fma(pj[u], v[j], pv);
+            }
+            pv = wave_sum_dpp(pv);
             const double kk = 0.5 * tk * pv;
-            for (int j = tid; j < m; j += nt) w[j] -= kk * v[j];
-            __syncthreads();
-            for (int idx = tid; idx < m * m; idx += nt) {
-                const int i = idx / m, j = idx - i * m;
-                W2[(long)i * N + j] -= v[i] * w[j] + w[i] * v[j];
+#pragma unroll
+            for (int u = 0; u < NJ; ++u) {
+                const int j = lane + 64 * u;
+                if (j < m) w[j] = pj[u] - kk * v[j];
+            }
+            for (int j = lane; j < m; j += 64) {
+                const double vj = v[j], wj = w[j];
+                int i = wid;
+                for (; i + 3 * NW < m; i += 4 * NW) {
+                    double x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = W2[i * ld + j + u * NW * ld];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        W2[i * ld + j + u * NW * ld] =
+                            fma(-w[i + u * NW], vj, fma(-v[i + u * NW], wj, x[u]));
+                }
+                for (; i < m; i += NW) W2[i * ld + j] = fma(-w[i], vj, fma(-v[i], wj, W2[i * ld + j]));
             }
         }
         __syncthreads();
     }
     if (tid == 0) {
         if (N >= 2) {
-            dg[N - 2] = W[(long)(N - 2) * N + N - 2];
-            ed[N - 2] = W[(long)(N - 2) * N + N - 1];
+            dg[N - 2] = W[(long)(N - 2) * ld + N - 2];
+            ed[N - 2] = W[(long)(N - 2) * ld + N - 1];
         }
         if (N >= 1) {  // (an empty row has nothing to reduce)
-            dg[N - 1] = W[(long)(N - 1) * N + N - 1];
+            dg[N - 1] = W[(long)(N - 1) * ld + N - 1];
             ed[N - 1] = 0.0;
         }
     }
-    // 2. factor: Qf = H_0 H_1 ... H_{N-3}, applied to the identity last first
-    for (int idx = tid; idx < N * N; idx += nt) {
-        const int c = idx / N, r = idx - c * N;
-        Qf[idx] = r == c ? 1.0 : 0.0;
+    __syncthreads();
+    // 2. factor H_0 H_1 ... H_{N-3}, in place: after step k the block of rows and
+    //    columns from k + 1 on holds H_k ... H_{N-3} (the identity's first row and
+    //    column of each block, still occupied by a used reflector, are put in on
+    //    the way); then the first row and column
+    if (N >= 2 && tid < 4) {
+        const int i = N - 2 + (tid >> 1), j = N - 2 + (tid & 1);
+        W[(long)i * ld + j] = i == j ? 1.0 : 0.0;
     }
+    if (N == 1 && tid == 0) W[0] = 1.0;
     __syncthreads();
     for (int k = N - 3; k >= 0; --k) {
-        const double tk = tau[k];
-        if (tk == 0.0) continue;
         const int m = N - k - 1;
-        const double *vk = W + (long)k * N + k + 1;
-        for (int i = tid; i < m; i += nt) v[i] = vk[i];
-        __syncthreads();
-        // u_j = tau sum_i v_i Qf[k+1+i][k+1+j]; Qf[k+1+i][k+1+j] -= v_i u_j
-        for (int j = tid; j < m; j += nt) {
-            const double *col = Qf + (long)(k + 1 + j) * N + k + 1;
-            double s = 0.0;
-            for (int i = 0; i < m; ++i) s = fma(col[i], v[i], s);
-            w[j] = tk * s;
+        double *Wk = W + (long)k * ld + k + 1, *W2 = Wk + ld;
+        const double tk = W[(long)k * ld + k];
+        const bool fresh = k < N - 3;  // (the last block, 2 x 2, was set above)
+        for (int i = lane; i < m; i += 64) v[i] = Wk[i];
+        // u_j = tau sum_i v_i Q2[i][j]; Q2[i][j] -= v_i u_j
+        auto q2 = [&](int i, int j) {
+            const double x = W2[i * ld + j];
+            return fresh && (i == 0 || j == 0) ? (i == j ? 1.0 : 0.0) : x;
+        };
+        for (int j = lane; j < m; j += 64) {
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            int i = wid;
+            for (; i + 3 * NW < m; i += 4 * NW) {
+                double x[4], y[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    x[u] = q2(i + u * NW, j);
+                    y[u] = v[i + u * NW];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) s[u] = fma(x[u], y[u], s[u]);
+            }
+            for (; i < m; i += NW) s[0] = fma(q2(i, j), v[i], s[0]);
+            part[wid * N + j] = (s[0] + s[1]) + (s[2] + s[3]);
         }
         __syncthreads();
-        for (int idx = tid; idx < m * m; idx += nt) {
-            const int j = idx / m, i = idx - j * m;
-            Qf[(long)(k + 1 + j) * N + k + 1 + i] -= v[i] * w[j];
+        for (int j = lane; j < m; j += 64) {
+            double u = part[j];
+#pragma unroll
+            for (int t = 1; t < NW; ++t) u += part[t * N + j];
+            u *= tk;
+            int i = wid;
+            for (; i + 3 * NW < m; i += 4 * NW) {
+                double x[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] = q2(i + t * NW, j);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) W2[(i + t * NW) * ld + j] = fma(-v[i + t * NW], u, x[t]);
+            }
+            for (; i < m; i += NW) W2[i * ld + j] = fma(-v[i], u, q2(i, j));
         }
         __syncthreads();
     }
-    // 3. implicit symmetric QR steps with Wilkinson shifts on (dg, ed); ed[i]
-    //    couples i and i+1.  The active block [lo, hi] is the lowest unreduced
-    //    one.  One thread chases the bulge of a step down the block with plane
-    //    rotations G_k on (k, k+1), choosing G_0 from the shifted first column
-    //    and every later one to annihilate the bulge below the subdiagonal,
-    //    and records (c_k, s_k); every thread then applies the rotations in
-    //    order to its own row of the factor (Qf <- Qf G_k).
-    const double eps = 2.220446049250313e-16;
-    if (tid == 0) {
-        s_fail = 0;
-        s_m = N - 1;
-    }
+    if (N >= 3)
+        for (int i = tid; i < N; i += THREADS) W[(long)i * ld] = W[i] = i == 0 ? 1.0 : 0.0;
     __syncthreads();
-    // (ed[i] is negligible when |ed[i]| <= eps (|dg[i]| + |dg[i+1]|))
-    auto small = [&](int i) { return fabs(ed[i]) <= eps * (fabs(dg[i]) + fabs(dg[i + 1])); };
-    for (int guard = 0; guard < 60 * N + 60; ++guard) {
-        if (tid < 64) {
-            // wavefront 0 finds the active block: hi = the highest index at or
-            // below s_m whose coupling to the row above is not negligible (the
-            // negligible ones set to zero), lo = the lowest index joined to hi
-            // by non-negligible couplings; 64 candidates per ballot
-            const int top = s_m;
-            int hi = 0;
-            for (int base = top; base > 0; base -= 64) {
-                const int idx = base - tid;
-                const bool stop = idx > 0 && !small(idx - 1);
-                const unsigned long long bal = __ballot(stop);
-                if (bal != 0ull) {
-                    hi = base - __ffsll((long long)bal) + 1;
-                    break;
-                }
-            }
-            for (int idx = hi + 1 + tid; idx <= top; idx += 64) ed[idx - 1] = 0.0;
-            int lo = -1;
-            if (hi > 0) {
-                for (int base = hi - 1;; base -= 64) {
-                    const int idx = base - tid;
-                    const bool stop = idx >= 0 && (idx == 0 || small(idx - 1));
-                    const unsigned long long bal = __ballot(stop);
-                    if (bal != 0ull) {
-                        lo = base - __ffsll((long long)bal) + 1;
-                        break;
-                    }
-                }
-            }
-            if (tid == 0) {
-                if (hi > 0) {
-                    if (lo > 0) ed[lo - 1] = 0.0;
-                    // Wilkinson shift: the eigenvalue of the trailing 2 x 2 block
-                    // closer to its last diagonal entry
-                    const double e = ed[hi - 1];
-                    const double dd = 0.5 * (dg[hi - 1] - dg[hi]);
-                    const double den = dd + copysign(sqrt(fma(dd, dd, e * e)), dd);
-                    const double mu = den != 0.0 ? dg[hi] - e * e / den : dg[hi];
-                    // the chase: a = dg[k] and b = ed[k] as rotated by the previous
-                    // step are carried in registers, d = dg[k + 1] and en = ed[k + 1]
-                    // are still the block's own values
-                    double a = dg[lo], b = ed[lo];
-                    double x = a - mu, z = b, bulge = 0.0;
-                    for (int k = lo; k < hi; ++k) {
-                        const double d = dg[k + 1];
-                        const double en = k + 1 < hi ? ed[k + 1] : 0.0;
-                        const double r = sqrt(fma(x, x, z * z));
-                        double c = 1.0, sn = 0.0;
-                        if (r != 0.0) {
-                            c = x / r;
-                            sn = z / r;
-                        }
-                        if (k > lo) ed[k - 1] = r;  // the bulge is gone
-                        const double cs = c * sn, c2 = c * c, s2 = sn * sn;
-                        dg[k] = c2 * a + 2.0 * cs * b + s2 * d;
-                        const double dn = s2 * a - 2.0 * cs * b + c2 * d;
-                        const double ek = cs * (d - a) + (c2 - s2) * b;
-                        ed[k] = ek;
-                        if (k + 1 < hi) {
-                            bulge = sn * en;
-                            b = c * en;
-                        }
-                        rc[k] = c;
-                        rs[k] = sn;
-                        x = ek;
-                        z = bulge;
-                        a = dn;
-                    }
-                    dg[hi] = a;
-                }
-                s_m = hi;
-                s_lo = lo;
-                if (hi > 0 && guard == 60 * N + 59) s_fail = 1;
-            }
-        }
-        __syncthreads();
-        const int hi = s_m, lo = s_lo;
-        if (hi == 0) break;
-        // the factor's rows: columns k and k+1 rotated for k = lo .. hi-1
-        for (int r = tid; r < N; r += nt) {
-            double qk = Qf[(long)lo * N + r];
-            for (int k = lo; k < hi; ++k) {
-                const double qn = Qf[(long)(k + 1) * N + r];
-                const double c = rc[k], sn = rs[k];
-                Qf[(long)k * N + r] = c * qk + sn * qn;
-                qk = c * qn - sn * qk;
-            }
-            Qf[(long)hi * N + r] = qk;
+    if (!MAT) {
+        // (the sweeps' rows are lanes: column-major)
+        for (int idx = tid; idx < N * N; idx += THREADS) {
+            const int c = idx / N, r = idx - c * N;
+            Qf[idx] = W[(long)r * N + c];
         }
         __syncthreads();
     }
-    if (tid == 0 && s_m > 0) s_fail = 1;
+    // 3. implicit symmetric QR steps on (dg, ed); ed[i] couples i and i+1
+    bool fail = false;
+    int top = N - 1;
+    for (int t = 0;; ++t) {
+        const int b = t & 1;
+        if (wid == 0) {
+            int lo = 0, hi = 0;
+            if (t < 60 * N + 60)
+                active_block(dg, ed, top, lane, lo, hi);
+            else
+                fail = top > 0;
+            lo = __builtin_amdgcn_readfirstlane(lo);
+            hi = __builtin_amdgcn_readfirstlane(hi);
+            if (hi > 0) chase(dg, ed, lo, hi, lane, rot + b * N);
+            top = hi;
+            if (lane == 0) {
+                s_lo[b] = lo;
+                s_hi[b] = hi;
+            }
+        } else if (t > 0) {
+            // the step before: columns k and k+1 rotated for k = lo .. hi-1, one
+            // row per lane
+            const int lo = s_lo[b ^ 1], hi = s_hi[b ^ 1];
+            const double2 *g = rot + (b ^ 1) * N;
+            for (int r = tid - 64; r < N; r += THREADS - 64) {
+                double *q = MAT ? W + (long)r * ld : Qf + r;
+                const int st = MAT ? 1 : N;
+                double qk = q[(long)lo * st];
+                int k = lo;
+                for (; k + 4 <= hi; k += 4) {
+                    double qn[4];
+                    double2 cs[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        qn[u] = q[(long)(k + u + 1) * st];
+                        cs[u] = g[k + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        q[(long)(k + u) * st] = fma(cs[u].x, qk, cs[u].y * qn[u]);
+                        qk = fma(cs[u].x, qn[u], -cs[u].y * qk);
+                    }
+                }
+                for (; k < hi; ++k) {
+                    const double qn = q[(long)(k + 1) * st];
+                    const double2 cs = g[k];
+                    q[(long)k * st] = fma(cs.x, qk, cs.y * qn);
+                    qk = fma(cs.x, qn, -cs.y * qk);
+                }
+                q[(long)hi * st] = qk;
+            }
+        }
+        __syncthreads();
+        if (s_hi[b] == 0) break;
+    }
+    if (MAT)
+        for (int idx = tid; idx < N * N; idx += THREADS) {
+            const int c = idx / N, r = idx - c * N;
+            Qf[idx] = W[r * ld + c];
+        }
     // 4. spectrum and plan
+    if (wid != 0) return;
     double lsum = 0.0, amin = 1e300, dev = 0.0;
-    for (int i = tid; i < N; i += nt) {
+    for (int i = lane; i < N; i += 64) {
         const double a = dg[i];
         alpha_out[2 * o + i] = a;
         lsum += log(a);
         amin = fmin(amin, a);
         dev = fmax(dev, fabs(a - 1.0));
     }
-    const double logdetA = block_sum(lsum, red);
-    amin = -block_max(-amin, red);
-    dev = block_max(dev, red);
-    if (tid == 0) {
-        RowPlan rp = rows[p];
-        row_plan(rp, n, dg, 1, logdetQ, logdetA, amin, dev, scal[3] != 0.0 || s_fail != 0, frozen & 1,
-                 (frozen & 2) != 0);
-        rows[p] = rp;
-    }
+    const double logdetA = wave_sum(lsum);
+    amin = -wave_max(-amin);
+    dev = wave_max(dev);
+    RowPlan rp = rows[p];
+    row_plan(rp, n, dg, lane, scal[0], logdetA, amin, dev, scal[3] != 0.0 || fail, frozen & 1, (frozen & 2) != 0);
+    if (lane == 0) rows[p] = rp;
 }
 
 }  // namespace
@@ -264,10 +437,35 @@ __global__ __launch_bounds__(EIG_THREADS) void k_eig(
 int eig_rows(gbs_ctx *ctx, gbs_plan *pl)
 {
     if (pl->P == 0) return 0;
-    hipLaunchKernelGGL(k_eig, dim3(pl->P), dim3(EIG_THREADS), 0, ctx->stream, ctx->model.M,
-                       ctx->model.qi_hi, ctx->model.scal, pl->d_offsets, pl->d_modes, pl->d_perm,
-                       pl->d_voff, pl->d_wbig, pl->d_alpha, pl->d_v, pl->d_rows,
-                       (pl->frozen ? 1 : 0) | (pl->whole ? 2 : 0));
+    const int fz = (pl->frozen ? 1 : 0) | (pl->whole ? 2 : 0);
+    // (rows by decreasing click count; the larger ones are perm[0..nbig))
+    if (pl->nbig > 0) {
+        const void *fn = (const void *)k_eig<false, 512>;
+        const int lds = eig_lds(2 * pl->max_n, 8, false);
+        if (int rc = func_lds_limit(ctx, fn, lds)) return rc;
+        hipLaunchKernelGGL((k_eig<false, 512>), dim3(pl->nbig), dim3(512), lds, ctx->stream, ctx->model.M,
+                           ctx->model.qi_hi, ctx->model.scal, pl->d_offsets, pl->d_modes, pl->d_perm, pl->d_voff,
+                           pl->d_wbig, pl->d_alpha, pl->d_v, pl->d_rows, fz);
+    }
+    // The small rows, largest first: one launch, or for batches of more rows than
+    // run at a time one per class of click counts, so that each class's LDS lets
+    // as many of its workgroups as possible share a compute unit (2 above 36
+    // clicks, then 3, 4 and 6).
+    constexpr int tops[] = {GBS_NSMALL, 36, 31, 25};
+    const bool classes = pl->P - pl->nbig > 4 * ctx->num_cu;
+    for (int i = pl->nbig, c = 0; i < pl->P; ++c) {
+        const int below = classes && c < 3 ? tops[c + 1] : -1, n0 = pl->h_n[pl->h_perm[i]];
+        int e = i;
+        if (below < 0) e = pl->P;
+        while (e < pl->P && pl->h_n[pl->h_perm[e]] > below) ++e;
+        if (e == i) continue;
+        const int lds = eig_lds(2 * n0, 4, true);
+        if (int rc = func_lds_limit(ctx, (const void *)k_eig<true, 256>, lds)) return rc;
+        hipLaunchKernelGGL((k_eig<true, 256>), dim3(e - i), dim3(256), lds, ctx->stream, ctx->model.M,
+                           ctx->model.qi_hi, ctx->model.scal, pl->d_offsets, pl->d_modes, pl->d_perm + i,
+                           pl->d_voff, pl->d_wbig, pl->d_alpha, pl->d_v, pl->d_rows, fz);
+        i = e;
+    }
     HIP_TRY(ctx, hipGetLastError());
     return 0;
 }

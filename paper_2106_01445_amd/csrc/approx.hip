@@ -572,13 +572,15 @@ __global__ __launch_bounds__(CONT_THREADS) void k_contour(
 //
 // Measured against one thread per sector from c = 0, every sector of the first
 // 256 fitted, two evaluations per Newton step, and the fits run again for the
-// adjoint (us): 4096 rows at 70 modes, order 3, 4270 -> 1440; 1024 rows at 20
-// modes, order 3, 1900 -> 314; 64 rows at 20 modes, order 2, 207 -> 98, with the
-// adjoint 470 -> 117; 512 rows at 144 modes, order 2, with the adjoint
-// 2870 -> 430; 16 rows of 2-6 clicks 168 -> 75.
+// adjoint (us): 4096 rows at 70 modes, order 3, 4270 -> 1410; 1024 rows at 20
+// modes, order 3, 1900 -> 300; 64 rows at 20 modes, order 2, 207 -> 103, with the
+// adjoint 470 -> 131; 512 rows at 144 modes, order 2, with the adjoint
+// 2870 -> 430; 16 rows of 2-6 clicks 168 -> 73.  Two workgroups per compute unit
+// at 256 registers: with more registers and one, 2340 and 456 in the first two;
+// three, 1365 and 340, but 133, 161 and 91 in the smaller.
 // ---------------------------------------------------------------------------
 template <int ORDER, int PASS, bool GRAD>
-__global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__ offsets,
+__global__ __launch_bounds__(FIT_THREADS, 2) void k_dft_fit(const int *__restrict__ offsets,
                                                          RowPlan *__restrict__ rows, cplx *__restrict__ sw,
                                                          double *__restrict__ logp,
                                                          int *__restrict__ status, double u_clu,
@@ -679,7 +681,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_dft_fit(const int *__restrict__
 #pragma unroll
         for (int t = 0; t <= JM; ++t) tau[t] = t <= ORDER && t <= jp ? plane(t)[kap] : 0.0;
         const double t0 = tau[0], lw = log_weight(t0, kap);
-        const SectorFitT<JM> f = fit_sector<JM>(n, 0, jp, (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0,
+        const SectorFitT<JM> f = fit_sector<JM, false>(n, 0, jp, (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0,
                                                 js, cs[0], cs[1], cs[2], JM >= 4 ? cs[JM - 1] : 0.0);
         if (gl == 0) {
             if (f.bad) {
@@ -936,7 +938,7 @@ __global__ __launch_bounds__(DIST_THREADS) void k_dist_fit(const int *__restrict
         SectorFitT<JM> f;
         f.jr = f.bad = 0;
         if (s > 1)
-            f = fit_sector<JM>(n, v0, min(jp, s - 1), (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0, 0,
+            f = fit_sector<JM, true>(n, v0, min(jp, s - 1), (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0, -1,
                                0.0, 0.0, 0.0, 0.0);
         if (f.bad) {
             if (gl == 0) atomicAdd(&s_fail, w0);
@@ -986,7 +988,10 @@ __global__ __launch_bounds__(256) void k_retilt(int P, const int *__restrict__ o
     const int o = offsets[p], n = offsets[p + 1] - o;
     const double logdet_q = -2.0 * rp.log_pvac - rp.logdet_a;
     const double dev = rp.rconv < 1e299 ? 1.0 / rp.rconv : 0.0;
-    row_plan(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
+    if (n <= 8)
+        row_plan<true>(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
+    else
+        row_plan<false>(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
     rp.flags = flags;
     if (lane == 0) rows[p] = rp;
 }

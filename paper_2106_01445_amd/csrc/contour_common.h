@@ -199,6 +199,9 @@ __host__ __device__ __forceinline__ int cont_fixed() { return 16 * (CONT_THREADS
 // With target > 0 the tilted mean is set to target instead (the re-tilt of a
 // row whose estimate lies in sectors far from the first target); the target
 // used is kept in kbar.
+// ORDERED: the radius by halvings alone and sums in index order (see
+// eig_ordered).
+template <bool ORDERED>
 __device__ __forceinline__ void row_plan(RowPlan &rp, int n, const double *alpha, int lane,
                                          double logdetQ, double logdetA, double amin, double dev,
                                          bool nonpd, int frozen, bool whole = false, double target_in = 0.0)
@@ -225,6 +228,14 @@ __device__ __forceinline__ void row_plan(RowPlan &rp, int n, const double *alpha
         // the tilted mean (increasing in rho) and its slope
         auto mfun = [&](double rho, double &slope) {
             double s = 0.0, d = 0.0;
+            if (ORDERED) {
+                slope = 0.0;
+                for (int i = 0; i < N; ++i) {
+                    const double a = alpha[i];
+                    s += 0.5 * rho * (1.0 - a) / (1.0 + rho * (a - 1.0));
+                }
+                return s;
+            }
             for (int i = lane; i < N; i += 64) {
                 const double b = 1.0 - alpha[i], q = 1.0 / (1.0 - rho * b);
                 s += 0.5 * rho * b * q;
@@ -244,7 +255,30 @@ __device__ __forceinline__ void row_plan(RowPlan &rp, int n, const double *alpha
         double rho;
         if (dev < 1e-300) rho = 1.0;
         else if (mfun(hi, slope) <= target) rho = hi;
-        else {
+        else if (ORDERED) {
+            // (at most 200 halvings, to the last few bits of rho)
+            double lo = 0.0;
+            for (int it = 0; it < 200 && hi - lo > 4e-16 * hi;) {
+                // lane l > 0 is node l of a binary tree of halvings: the bits of l
+                // below its leading one are the turns from the root, 1 for the
+                // upper half
+                double l = lo, h = hi;
+                for (int b = 30 - __clz(lane | 1); b >= 0; --b) {
+                    const double mid = 0.5 * (l + h);
+                    if (lane >> b & 1) l = mid;
+                    else h = mid;
+                }
+                const unsigned long long up = __ballot(mfun(0.5 * (l + h), slope) < target);
+                for (int node = 1; node < 64 && it < 200 && hi - lo > 4e-16 * hi; ++it) {
+                    const double mid = 0.5 * (lo + hi);
+                    const int right = (int)(up >> node & 1ull);
+                    if (right) lo = mid;
+                    else hi = mid;
+                    node = 2 * node + right;
+                }
+            }
+            rho = 0.5 * (lo + hi);
+        } else {
             // Newton steps inside the bracket, halved where they leave it or gain
             // less than a bit, to the last few bits of rho (a wavefront's lanes
             // take the terms: the 52 halvings of plain bisection, with the sums in
@@ -288,8 +322,17 @@ __device__ __forceinline__ void row_plan(RowPlan &rp, int n, const double *alpha
         rp.log_rho = log(rho);
     }
     double s = 0.0;
-    for (int i = lane; i < N; i += 64) s += log1p(rp.rho * (alpha[i] - 1.0));
-    rp.log_g_rho = 0.5 * logdetA - 0.5 * wave_sum_dpp(s);
+    if (ORDERED) {
+        // (each lane's terms, added in index order)
+        for (int b = 0; b < N; b += 64) {
+            const double t = b + lane < N ? log1p(rp.rho * (alpha[b + lane] - 1.0)) : 0.0;
+            for (int i = 0; i < min(64, N - b); ++i) s += __shfl(t, i);
+        }
+    } else {
+        for (int i = lane; i < N; i += 64) s += log1p(rp.rho * (alpha[i] - 1.0));
+        s = wave_sum_dpp(s);
+    }
+    rp.log_g_rho = 0.5 * logdetA - 0.5 * s;
 }
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
@@ -499,65 +542,91 @@ __device__ __forceinline__ void fit_basis(int n, double *phi)
 }
 
 // Log-partition sum of the exp-polynomial with parameters c on n' = 1..n - v0,
-// the mean E[phi] and the second moments E2 (upper triangle, row-major) of its
-// JP features; gl: this lane's place in its quad.  JP is a template argument so
-// that every array index is static (kept in registers).  Exponents are taken
-// relative to the first term's (whose weight is then 1), or to the largest if
-// one would exceed 600.
-template <int JP>
+// and about f0, its JP features at its largest term: the mean E[phi - f0] and the
+// second moments E2 (upper triangle, row-major); gl: this lane's place in its
+// quad.  JP is a template argument so that every array index is static (kept in
+// registers).  Weights and features are taken relative to the largest term,
+// found in a pass of its own: a distribution that has shrunk to one point then
+// has a covariance of exactly zero, which ends the fit (with the rounding of w / w
+// in its place moments that no distribution has take all FIT_MAXIT steps: a
+// 30-mode device's sectors 5.7 ms instead of 0.3), and on a short support, where
+// four features are nearly dependent, the covariance E2 - E E' loses least.
+// SEQ (cut supports, v0 > 0, of up to FIT_SEQ points): every lane adds up the whole support in
+// index order, f0 = 0.  There three or four moments determine the distribution
+// almost, the covariance is singular but for rounding, and whether the last
+// moment can be used hangs on the last bits of these sums (split over the quad,
+// 3 of 300 devices' distributions moved by up to 5e-4 at order 4).
+#define FIT_SEQ 10
+template <int JP, bool SEQ>
 __device__ __forceinline__ void fit_eval(int n, int v0, LdsTab phi, int gl, const double *c, double &lse,
-                                         double *E, double *E2)
+                                         double *f0, double *E, double *E2)
 {
-    double zref = 0.0;
+    double zmax = -1e300, s = 0.0, e[JP], e2[JP * (JP + 1) / 2];
+    int vm = v0;
+    for (int v = v0 + (SEQ ? 0 : gl); v < n; v += SEQ ? 1 : FIT_G) {
+        double z = 0.0;
 #pragma unroll
-    for (int t = 0; t < JP; ++t) zref -= c[t] * phi[4 * v0 + t];
-    for (int pass = 0;; ++pass) {
-        double s = 0.0, e[JP], e2[JP * (JP + 1) / 2], mx = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < JP; ++t) e[t] = 0.0;
-#pragma unroll
-        for (int t = 0; t < JP * (JP + 1) / 2; ++t) e2[t] = 0.0;
-        for (int v = v0 + gl; v < n; v += FIT_G) {
-            double f[JP], z = 0.0;
-#pragma unroll
-            for (int t = 0; t < JP; ++t) {
-                f[t] = phi[4 * v + t];
-                z -= c[t] * f[t];
-            }
-            mx = fmax(mx, z);
-            const double w = exp(z - zref);
-            s += w;
-            int k = 0;
-#pragma unroll
-            for (int t = 0; t < JP; ++t) {
-                const double wf = w * f[t];
-                e[t] += wf;
-#pragma unroll
-                for (int u = t; u < JP; ++u) e2[k++] += wf * f[u];
-            }
+        for (int t = 0; t < JP; ++t) z -= c[t] * phi[4 * v + t];
+        if (z > zmax) {
+            zmax = z;
+            vm = v;
         }
-        mx = quad_max(mx);
-        if (pass == 0 && mx - zref > 600.0) {
-            zref = mx;  // (no exponent is above it: once is enough)
-            continue;
+    }
+    if (!SEQ) {
+        const double zq = quad_max(zmax);
+        vm = (int)quad_max(zmax == zq ? (double)vm : (double)v0);
+        zmax = zq;
+    }
+#pragma unroll
+    for (int t = 0; t < JP; ++t) {
+        e[t] = 0.0;
+        f0[t] = SEQ ? 0.0 : phi[4 * vm + t];
+    }
+#pragma unroll
+    for (int t = 0; t < JP * (JP + 1) / 2; ++t) e2[t] = 0.0;
+    for (int v = v0 + (SEQ ? 0 : gl); v < n; v += SEQ ? 1 : FIT_G) {
+        double f[JP], z = 0.0;
+#pragma unroll
+        for (int t = 0; t < JP; ++t) {
+            f[t] = phi[4 * v + t];
+            z -= c[t] * f[t];
+            if (!SEQ) f[t] -= f0[t];
         }
-        s = quad_sum(s);
-        lse = zref + log(s);
-        const double is = rcp_nr(s);
+        const double w = exp(z - zmax);
+        s += w;
+        int k = 0;
 #pragma unroll
-        for (int t = 0; t < JP; ++t) E[t] = quad_sum(e[t]) * is;
+        for (int t = 0; t < JP; ++t) {
+            const double wf = w * f[t];
+            e[t] += wf;
 #pragma unroll
-        for (int k = 0; k < JP * (JP + 1) / 2; ++k) E2[k] = quad_sum(e2[k]) * is;
+            for (int u = t; u < JP; ++u) e2[k++] += wf * f[u];
+        }
+    }
+    if (SEQ) {
+        lse = zmax + log(s);
+#pragma unroll
+        for (int t = 0; t < JP; ++t) E[t] = e[t] / s;
+#pragma unroll
+        for (int k = 0; k < JP * (JP + 1) / 2; ++k) E2[k] = e2[k] / s;
         return;
     }
+    s = quad_sum(s);
+    lse = zmax + log(s);
+    const double is = rcp_nr(s);
+#pragma unroll
+    for (int t = 0; t < JP; ++t) E[t] = quad_sum(e[t]) * is;
+#pragma unroll
+    for (int k = 0; k < JP * (JP + 1) / 2; ++k) E2[k] = quad_sum(e2[k]) * is;
 }
 
-// L D L^T solve of the JP x JP system H x = r (H from E, E2 as the covariance
-// of the features, damped by 1e-14 of its trace); false if H is not positive.
-template <int JP>
+// Solve of the JP x JP system H x = r (H from E, E2 as the covariance of the
+// features, damped by 1e-14 of its trace) by L D L^T, or L L^T with SEQ; false if
+// H is not positive.
+template <int JP, bool SEQ>
 __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, const double *r, double *x)
 {
-    double H[JP][JP], L[JP][JP], id[JP], tr = 0.0;
+    double H[JP][JP], L[JP][JP], tr = 0.0;
     int k = 0;
 #pragma unroll
     for (int t = 0; t < JP; ++t)
@@ -568,6 +637,39 @@ __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, con
     if (!(tr > 0.0)) return false;
 #pragma unroll
     for (int t = 0; t < JP; ++t) H[t][t] += 1e-14 * tr;
+    if (SEQ) {
+#pragma unroll
+        for (int j = 0; j < JP; ++j) {
+            double d = H[j][j];
+#pragma unroll
+            for (int l = 0; l < j; ++l) d -= L[j][l] * L[j][l];
+            if (!(d > 0.0)) return false;
+            L[j][j] = sqrt(d);
+#pragma unroll
+            for (int i = j + 1; i < JP; ++i) {
+                double v = H[i][j];
+#pragma unroll
+                for (int l = 0; l < j; ++l) v -= L[i][l] * L[j][l];
+                L[i][j] = v / L[j][j];
+            }
+        }
+        double y[JP];
+#pragma unroll
+        for (int i = 0; i < JP; ++i) {
+            double v = r[i];
+#pragma unroll
+            for (int l = 0; l < i; ++l) v -= L[i][l] * y[l];
+            y[i] = v / L[i][i];
+        }
+#pragma unroll
+        for (int i = JP - 1; i >= 0; --i) {
+            double v = y[i];
+#pragma unroll
+            for (int l = i + 1; l < JP; ++l) v -= L[l][i] * x[l];
+            x[i] = v / L[i][i];
+        }
+        return true;
+    }
     // column j: H[i][j] <- L_ij d_j, L[i][j] = L_ij
 #pragma unroll
     for (int j = 0; j < JP; ++j) {
@@ -576,9 +678,8 @@ __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, con
 #pragma unroll
             for (int i = j; i < JP; ++i) H[i][j] -= L[j][l] * H[i][l];
         if (!(H[j][j] > 0.0)) return false;
-        id[j] = rcp_nr(H[j][j]);
 #pragma unroll
-        for (int i = j + 1; i < JP; ++i) L[i][j] = H[i][j] * id[j];
+        for (int i = j + 1; i < JP; ++i) L[i][j] = H[i][j] / H[j][j];
     }
 #pragma unroll
     for (int i = 0; i < JP; ++i) {
@@ -588,7 +689,7 @@ __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, con
     }
 #pragma unroll
     for (int i = JP - 1; i >= 0; --i) {
-        x[i] *= id[i];
+        x[i] /= H[i][i];  // (of a distribution near one point, down to 1e-308)
 #pragma unroll
         for (int l = i + 1; l < JP; ++l) x[i] -= L[l][i] * x[l];
     }
@@ -597,34 +698,34 @@ __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, con
 
 // Max-entropy fit on n' = 1..n - v0 (v = n - n' empty modes, v >= v0) of the JP
 // moments m[] by Newton's method on the convex dual, from the parameters c;
-// returns 1 if a Hessian is singular, 2 after FIT_MAXIT steps, else 0, minus the log-partition sum (log q(n) when v0 = 0), the parameters
-// in c and the sensitivity u = H^{-1} m (H the covariance of the basis under
+// returns 1 if a Hessian is singular, 2 after FIT_MAXIT steps, else 0, minus
+// the log-partition sum (log q(n) when v0 = 0), the parameters in c and the sensitivity u = H^{-1} m (H the covariance of the basis under
 // the fit; 1e300 where H is singular) on success.
-template <int JP>
+template <int JP, bool SEQ>
 __device__ __forceinline__ int fit_newton(int n, int v0, LdsTab phi, int gl, const double *m, double *c,
                                           double &logq, double *u)
 {
-    double lse, E[JP], E2[JP * (JP + 1) / 2];
-    fit_eval<JP>(n, v0, phi, gl, c, lse, E, E2);
+    double lse, f0[JP], E[JP], E2[JP * (JP + 1) / 2];
+    fit_eval<JP, SEQ>(n, v0, phi, gl, c, lse, f0, E, E2);
     for (int it = 0; it <= FIT_MAXIT; ++it) {
         double mg[JP], slope = 0.0, L0 = lse;
         bool conv = true;
 #pragma unroll
         for (int t = 0; t < JP; ++t) {
-            mg[t] = E[t] - m[t];
+            mg[t] = (f0[t] - m[t]) + E[t];
             L0 += c[t] * m[t];
             if (!(fabs(mg[t]) <= 1e-15 + 1e-12 * fabs(m[t]))) conv = false;
         }
         // Newton step H x = -g, g = m - E, H the covariance of the features
         double x[JP], cn[JP];
-        if (!fit_solve<JP>(E, E2, mg, x)) return 1;
+        if (!fit_solve<JP, SEQ>(E, E2, mg, x)) return 1;
 #pragma unroll
         for (int t = 0; t < JP; ++t) slope -= mg[t] * x[t];
         double st = 1.0;
         for (;;) {
 #pragma unroll
             for (int t = 0; t < JP; ++t) cn[t] = c[t] + st * x[t];
-            fit_eval<JP>(n, v0, phi, gl, cn, lse, E, E2);
+            fit_eval<JP, SEQ>(n, v0, phi, gl, cn, lse, f0, E, E2);
             // (Armijo, while the predicted decrease is above the rounding of the
             // objective; one polishing step after convergence)
             if (conv || !(-slope > 1e-13 * fmax(1.0, fabs(L0)))) break;
@@ -637,8 +738,9 @@ __device__ __forceinline__ int fit_newton(int n, int v0, LdsTab phi, int gl, con
 #pragma unroll
         for (int t = 0; t < JP; ++t) c[t] = cn[t];
         if (conv) {
+            if (!(fabs(lse) < INFINITY)) return 1;
             logq = -lse;
-            if (!fit_solve<JP>(E, E2, m, u))
+            if (!fit_solve<JP, SEQ>(E, E2, m, u))
 #pragma unroll
                 for (int t = 0; t < JP; ++t) u[t] = 1e300;
             return 0;
@@ -712,8 +814,8 @@ __device__ __forceinline__ cplx dft_tw(const cplx *W, int K, int e)
 }
 // In-place forward DFT of X[0..K) in LDS, input placed by dft_pos, output in
 // natural order.  All threads of the block (at least DFT_MINT) take part; in
-// the r-point combines each thread takes outputs o = tid, tid + nt, ...:
-// X[o] = sum_j W^{j o} F_j[o mod L], held until every input has been read.
+// the r-point combines each thread takes outputs o = tid, tid + nt, ..., held
+// until every input has been read.
 #define DFT_MINT 256
 __device__ void dft_lds(cplx *X, const cplx *W, const DftShape &d)
 {
@@ -734,19 +836,26 @@ __device__ void dft_lds(cplx *X, const cplx *W, const DftShape &d)
         __syncthreads();
     }
     if (d.r > 1) {
+        // twiddles in place, then the r-point sums (each of their roots W^{e}, e
+        // a multiple of L, is a root of unity of order r)
+        for (int o = tid + L; o < K; o += nt) {
+            const int j = o >> d.lgL, m = o & (L - 1);
+            X[o] = cmul(dft_tw(W, K, j * m), X[o]);
+        }
+        __syncthreads();
         cplx out[GBS_KMAX / DFT_MINT];
 #pragma unroll
         for (int i = 0; i < GBS_KMAX / DFT_MINT; ++i) {
             const int o = tid + i * nt;
             if (o >= K) continue;
-            const int m = o & (L - 1);
+            const int m = o & (L - 1), step = o - m;
             cplx acc = X[m];
-            int e = 0;  // j o mod K
+            int e = 0;  // (j o / L mod r) L
 #pragma unroll 4
             for (int j = 1; j < d.r; ++j) {
-                e += o;
+                e += step;
                 if (e >= K) e -= K;
-                acc = cfma(dft_tw(W, K, e), X[j * L + m], acc);
+                acc = cadd(acc, cmul(dft_tw(W, K, e), X[j * L + m]));
             }
             out[i] = acc;
         }
@@ -769,6 +878,18 @@ struct SectorFitT {
     int jr, bad;
 };
 
+template <int JM, bool SEQ>
+__device__ __forceinline__ int fit_moments(int jr, int n, int v0, LdsTab phi, int gl, const double *m, double *c,
+                                           double &logq, double *u)
+{
+    switch (jr) {
+    case 1: return fit_newton<1, SEQ>(n, v0, phi, gl, m, c, logq, u);
+    case 2: return fit_newton<2, SEQ>(n, v0, phi, gl, m, c, logq, u);
+    case 3: return fit_newton<3, SEQ>(n, v0, phi, gl, m, c, logq, u);
+    default: return fit_newton<JM >= 4 ? 4 : 1, SEQ>(n, v0, phi, gl, m, c, logq, u);
+    }
+}
+
 // Fit one sector by a quad from its tilted moments t0..t4 (t0 > 0; moments past
 // JM are ignored) on n' = 1..n - v0 (v0 > 0: a sector with fewer photons than
 // modes): the moments m_t = tau_t / (tau_0 C(n-1,t)) are used up to the
@@ -782,9 +903,11 @@ struct SectorFitT {
 // moment (its limit for a long support), and again from c = 0 where a Hessian
 // on the way was singular: the dual is convex, so the start only sets the
 // number of steps (measured with orders 2 / 3: 11 / 14 from c = 0, 7 / 12 from
-// the geometric one, 4 from a neighbour's).  The moments arrive by value and the fit runs out of line, so
-// that callers index nothing at run time.
-template <int JM>
+// the geometric one, 4 from a neighbour's).  js < 0, or a cut support (CUT: v0
+// may be positive) of up to FIT_SEQ points: from c = 0 alone.  The moments
+// arrive by value and the fit runs out of line, so that callers index nothing
+// at run time.
+template <int JM, bool CUT>
 __device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, LdsTab phi, int gl, double t0,
                                                   double t1, double t2, double t3, double t4, int js, double c1,
                                                   double c2, double c3, double c4)
@@ -811,22 +934,21 @@ __device__ __noinline__ SectorFitT<JM> fit_sector(int n, int v0, int jp, LdsTab 
         r.bad = 0;
         return r;
     }
+    const bool seq = CUT && v0 > 0 && n - v0 <= FIT_SEQ;
     int bad = 1;
     while (jr >= 1 && bad) {
         // starts: 2 a neighbour's, 1 geometric, 0 zero
         const double mu = r.m[0] * (n - 1.0);
         bad = 1;
-        for (int start = js == jr ? 2 : 1; start >= 0 && bad == 1; --start) {
+        for (int start = seq || js < 0 ? 0 : js == jr ? 2 : 1; start >= 0 && bad == 1; --start) {
             if (start == 1 && (v0 > 0 || !(mu < 0.5 * (n - 1.0)))) continue;
 #pragma unroll
             for (int t = 0; t < JM; ++t) r.c[t] = start == 2 && t < jr ? cs[t] : 0.0;
             if (start == 1) r.c[0] = (n - 1.0) * log1p(1.0 / mu);
-            switch (jr) {
-            case 1: bad = fit_newton<1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
-            case 2: bad = fit_newton<JM >= 2 ? 2 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
-            case 3: bad = fit_newton<JM >= 3 ? 3 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
-            default: bad = fit_newton<JM >= 4 ? 4 : 1>(n, v0, phi, gl, r.m, r.c, r.lq, r.u); break;
-            }
+            if (CUT && seq)
+                bad = fit_moments<JM, true>(jr, n, v0, phi, gl, r.m, r.c, r.lq, r.u);
+            else
+                bad = fit_moments<JM, false>(jr, n, v0, phi, gl, r.m, r.c, r.lq, r.u);
         }
         if (bad) --jr;
     }

@@ -148,6 +148,334 @@ __device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, in
     }
 }
 
+// ---------------------------------------------------------------------------
+// eig_ordered: rows of up to EIG_TINY clicks, by one wavefront of k_eig, and
+// whole devices of up to GBS_NSMALL modes (k_eig_whole).
+// Lossless rows hold sectors whose last moments, or whose weights, lie at the
+// transform's rounding: there a fit takes one moment more or less by the sign of
+// an error, and the row's estimate moves by up to 1e-5.  In batches of large
+// rows such sectors carry nothing; short rows (16 of 2-6 clicks: the estimates of
+// 39 of 300 such batches moved by more than 1e-9) and a distribution's outer
+// sectors show them.  So here every value has one rounding that no split over
+// lanes changes: sums run in index order or by one tree over the index, the
+// rotations' quotients and roots are correctly rounded, and the radius comes from
+// the halvings of [0, 0.98 R_b], six at a time: the lanes evaluate the 63
+// midpoints that six halvings can meet.
+// The matrix, then the factor, are in LDS; lanes take columns, then the factor's
+// rows; the wavefronts share the rank-2 update's rows, and those after the first
+// apply a step's rotations while the first chases the next.
+// 16 rows of 2-6 clicks 73 us (115 with a thread per column and the matrix
+// in memory; 55 with the sums split), a device of 30 modes 415 us (1030; 285).
+// ---------------------------------------------------------------------------
+#define EIG_TINY 8
+#define EIG_ORDERED_LDS(N) ((10 * (N) + 2 * (N) * ((N) + 1)) * 8)
+
+// c = x/r, sn = z/r, r = (x^2 + z^2)^{1/2}, each rounded to nearest: a root by
+// coupled Newton steps from the estimate of 1/r, quotients by 1/r with one
+// correction.
+__device__ __forceinline__ void rotation(double x, double z, double &c, double &sn, double &r)
+{
+    const double r2 = fma(x, x, z * z), ax = fabs(x), az = fabs(z);
+    const bool in = r2 > 1e-200 && r2 < 1e200 && (ax > 1e-200 || ax == 0.0) && (az > 1e-200 || az == 0.0);
+    if (in) {
+        const double y0 = __builtin_amdgcn_rsq(r2);
+        double g = r2 * y0, h = 0.5 * y0;
+        const double e = fma(-h, g, 0.5);
+        g = fma(g, e, g);
+        h = fma(h, e, h);
+        g = fma(fma(-g, g, r2), h, g);
+        r = fma(fma(-g, g, r2), h, g);
+        double y = h + h;
+        y = fma(y, fma(-r, y, 1.0), y);
+        const double qx = x * y, qz = z * y;
+        c = fma(fma(-r, qx, x), y, qx);
+        sn = fma(fma(-r, qz, z), y, qz);
+    } else {
+        r = sqrt(r2);
+        c = 1.0;
+        sn = 0.0;
+        if (r != 0.0) {
+            c = x / r;
+            sn = z / r;
+        }
+    }
+}
+
+// chase with these rotations
+__device__ __forceinline__ void chase_ordered(double *dg, double *ed, int lo, int hi, int lane, double2 *rot)
+{
+    const double e = ed[hi - 1];
+    const double dd = 0.5 * (dg[hi - 1] - dg[hi]);
+    const double den = dd + copysign(sqrt(fma(dd, dd, e * e)), dd);
+    const double mu = den != 0.0 ? dg[hi] - e * e / den : dg[hi];
+    double a = dg[lo], b = ed[lo];
+    double x = a - mu, z = b;
+    for (int cb = lo; cb < hi; cb += 64) {
+        const int k0 = cb + lane, len = min(64, hi - cb);
+        const double dv = k0 < hi ? dg[k0 + 1] : 0.0, ev = k0 + 1 < hi ? ed[k0 + 1] : 0.0;
+        double nd = 0.0, nr = 0.0, nc = 1.0, ns = 0.0;
+        for (int k = 0; k < len; ++k) {
+            const double d = lane_value(dv, k), en = lane_value(ev, k);
+            double c, sn, r;
+            rotation(x, z, c, sn, r);
+            const double cs = c * sn, c2 = c * c, s2 = sn * sn;
+            const double dk = c2 * a + 2.0 * cs * b + s2 * d;
+            const double dn = s2 * a - 2.0 * cs * b + c2 * d;
+            const double ek = cs * (d - a) + (c2 - s2) * b;
+            const bool me = lane == k;
+            nd = me ? dk : nd;
+            nr = me ? r : nr;
+            nc = me ? c : nc;
+            ns = me ? sn : ns;
+            x = ek;
+            z = sn * en;
+            b = c * en;
+            a = dn;
+        }
+        if (lane < len) {
+            dg[k0] = nd;
+            rot[k0] = make_double2(nc, ns);
+            if (k0 > lo) ed[k0 - 1] = nr;  // the bulge is gone
+        }
+    }
+    if (lane == 0) {
+        dg[hi] = a;
+        ed[hi - 1] = x;
+    }
+}
+
+// NT threads take part (64: the others of the workgroup have left); N <= 128
+template <int NT>
+__device__ __forceinline__ void eig_ordered(int M, const double *__restrict__ qi, const double *__restrict__ scal,
+                                            const int *__restrict__ modes, int n, double *__restrict__ alpha_out,
+                                            double *__restrict__ Qf, RowPlan *__restrict__ row, int frozen,
+                                            double *sh)
+{
+    constexpr int NW = NT / 64, NJ = NT > 64 ? 2 : 1;  // wavefronts, columns per lane
+    __shared__ int s_lo[2], s_hi[2];
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = 2 * n, D = 2 * M, LD = N + 1;
+    double2 *rot = (double2 *)sh;  // two steps', N each
+    double *v = sh + 4 * N, *w = v + N, *dg = w + N, *ed = dg + N, *tau = ed + N, *red = tau + N;
+    double *W = red + N, *Q = W + N * LD;
+    auto sync = [] {
+        if (NT > 64) {
+            __syncthreads();
+        } else {
+            // LDS of one wavefront: its accesses keep their order
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    // a tree over the index, 64 and above onto 0.. first
+    auto tree = [&](const double *x) {
+        double s = x[0];
+        if (NJ > 1) s += x[NJ - 1];
+        for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
+        return s;
+    };
+    for (int idx = tid; idx < N * N; idx += NT) {
+        const int i = idx / N, j = idx - i * N;
+        const int ri = i < n ? modes[i] : modes[i - n] + M;
+        const int rj = j < n ? modes[j] : modes[j - n] + M;
+        W[i * LD + j] = qi[(long)ri * D + rj];
+    }
+    sync();
+    for (int k = 0; k + 2 < N; ++k) {
+        const int m = N - k - 1;
+        double *Wk = W + k * LD + k + 1, *W2 = Wk + LD;
+        double x[NJ], q[NJ];
+#pragma unroll
+        for (int u = 0; u < NJ; ++u) {
+            const int i = lane + 64 * u;
+            x[u] = i < m ? Wk[i] : 0.0;
+            q[u] = i > 0 ? fma(x[u], x[u], 0.0) : 0.0;  // (rounded before the tree)
+        }
+        const double sg = tree(q);
+        const double x0 = lane_value(x[0], 0);
+        double tk = 0.0, al = x0;
+        if (sg != 0.0) {
+            al = -copysign(sqrt(x0 * x0 + sg), x0);
+            const double v0 = x0 - al;
+            tk = 2.0 / (v0 * v0 + sg);
+            if (lane == 0) x[0] = v0;
+        }
+#pragma unroll
+        for (int u = 0; u < NJ; ++u)
+            if (wid == 0 && lane + 64 * u < m) v[lane + 64 * u] = x[u];
+        if (wid == 0 && lane == 0) {
+            dg[k] = W[k * LD + k];
+            ed[k] = al;
+            tau[k] = tk;
+        }
+        sync();
+        if (wid == 0)
+            for (int i = lane; i < m; i += 64) Wk[i] = v[i];
+        if (tk != 0.0) {
+            // column sums in index order, a column per thread of the workgroup
+            if (tid < m) {
+                double s = 0.0;
+#pragma unroll 8
+                for (int i = 0; i < m; ++i) s = fma(W2[i * LD + tid], v[i], s);
+                w[tid] = tk * s;
+            }
+            sync();
+            double pj[NJ];
+#pragma unroll
+            for (int u = 0; u < NJ; ++u) {
+                const int j = lane + 64 * u;
+                pj[u] = j < m ? w[j] : 0.0;
+                q[u] = fma(pj[u], x[u], 0.0);
+            }
+            const double kk = 0.5 * tk * tree(q);
+            sync();
+#pragma unroll
+            for (int u = 0; u < NJ; ++u) {
+                const int j = lane + 64 * u;
+                pj[u] -= kk * x[u];
+                if (wid == 0 && j < m) w[j] = pj[u];
+            }
+            sync();
+#pragma unroll
+            for (int u = 0; u < NJ; ++u) {
+                const int j = lane + 64 * u;
+                if (j >= m) continue;
+#pragma unroll 4
+                for (int i = wid; i < m; i += NW) W2[i * LD + j] -= v[i] * pj[u] + w[i] * x[u];
+            }
+        }
+        sync();
+    }
+    if (tid == 0) {
+        if (N >= 2) {
+            dg[N - 2] = W[(N - 2) * LD + N - 2];
+            ed[N - 2] = W[(N - 2) * LD + N - 1];
+        }
+        if (N >= 1) {
+            dg[N - 1] = W[(N - 1) * LD + N - 1];
+            ed[N - 1] = 0.0;
+        }
+    }
+    // the factor, column-major: Q[c * LD + r]
+    for (int idx = tid; idx < N * N; idx += NT) {
+        const int c = idx / N, r = idx - c * N;
+        Q[c * LD + r] = r == c ? 1.0 : 0.0;
+    }
+    sync();
+    for (int k = N - 3; k >= 0; --k) {
+        const double tk = tau[k];
+        if (tk == 0.0) continue;
+        const int m = N - k - 1;
+        const double *vk = W + k * LD + k + 1;
+        double *Q2 = Q + (k + 1) * LD + k + 1;
+        if (tid < m) {
+            const double *col = Q2 + tid * LD;
+            double s = 0.0;
+#pragma unroll 8
+            for (int i = 0; i < m; ++i) s = fma(col[i], vk[i], s);
+            w[tid] = tk * s;
+        }
+        sync();
+#pragma unroll
+        for (int u = 0; u < NJ; ++u) {
+            const int i = lane + 64 * u;
+            if (i >= m) continue;
+            const double vi = vk[i];
+#pragma unroll 4
+            for (int j = wid; j < m; j += NW) Q2[j * LD + i] -= vi * w[j];
+        }
+        sync();
+    }
+    bool fail = false;
+    int top = N - 1;
+    for (int t = 0;; ++t) {
+        const int b = t & 1;
+        int lo = 0, hi = 0;
+        if (wid == 0) {
+            if (t < 60 * N + 60)
+                active_block(dg, ed, top, lane, lo, hi);
+            else
+                fail = top > 0;
+            lo = __builtin_amdgcn_readfirstlane(lo);
+            hi = __builtin_amdgcn_readfirstlane(hi);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (hi > 0) chase_ordered(dg, ed, lo, hi, lane, rot + b * N);
+            top = hi;
+            if (NT > 64 && lane == 0) {
+                s_lo[b] = lo;
+                s_hi[b] = hi;
+            }
+        }
+        // this step's rotations (one wavefront), or the step before's
+        const bool apply = NT > 64 ? wid > 0 && t > 0 : hi > 0;
+        if (NT == 64) sync();
+        if (apply) {
+            const int p = NT > 64 ? b ^ 1 : b;
+            if (NT > 64) {
+                lo = s_lo[p];
+                hi = s_hi[p];
+            }
+            const double2 *g = rot + p * N;
+            for (int r = NT > 64 ? tid - 64 : tid; r < N; r += NT > 64 ? NT - 64 : 64) {
+                double qk = Q[lo * LD + r];
+#pragma unroll 4
+                for (int k = lo; k < hi; ++k) {
+                    const double qn = Q[(k + 1) * LD + r];
+                    const double c = g[k].x, sn = g[k].y;
+                    Q[k * LD + r] = c * qk + sn * qn;
+                    qk = c * qn - sn * qk;
+                }
+                Q[hi * LD + r] = qk;
+            }
+        }
+        sync();
+        if ((NT > 64 ? s_hi[b] : top) == 0) break;
+    }
+    for (int idx = tid; idx < N * N; idx += NT) {
+        const int c = idx / N, r = idx - c * N;
+        Qf[idx] = Q[c * LD + r];
+    }
+    if (wid != 0) return;
+    double lg[NJ], amin = 1e300, dev = 0.0;
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) {
+        const int i = lane + 64 * u;
+        lg[u] = 0.0;
+        if (i >= N) continue;
+        const double a = dg[i];
+        alpha_out[i] = a;
+        lg[u] = log(a);
+        amin = fmin(amin, a);
+        dev = fmax(dev, fabs(a - 1.0));
+    }
+    const double logdetA = tree(lg);
+    amin = -wave_max(-amin);
+    dev = wave_max(dev);
+    RowPlan rp = *row;
+    row_plan<true>(rp, n, dg, lane, scal[0], logdetA, amin, dev, scal[3] != 0.0 || fail, frozen & 1,
+                   (frozen & 2) != 0);
+    if (lane == 0) *row = rp;
+}
+
+__device__ __noinline__ void eig_tiny(int M, const double *__restrict__ qi, const double *__restrict__ scal,
+                                      const int *__restrict__ modes, int n, double *__restrict__ alpha_out,
+                                      double *__restrict__ Qf, RowPlan *__restrict__ row, int frozen, double *sh)
+{
+    eig_ordered<64>(M, qi, scal, modes, n, alpha_out, Qf, row, frozen, sh);
+}
+
+// one row: every mode
+__global__ __launch_bounds__(256) void k_eig_whole(int M, const double *__restrict__ qi,
+                                                   const double *__restrict__ scal,
+                                                   const int *__restrict__ offsets, const int *__restrict__ modes,
+                                                   double *__restrict__ alpha_out, double *__restrict__ vt_out,
+                                                   RowPlan *__restrict__ rows, int frozen)
+{
+    extern __shared__ __attribute__((aligned(16))) double sh[];
+    eig_ordered<256>(M, qi, scal, modes, offsets[1] - offsets[0], alpha_out, vt_out, rows, frozen, sh);
+}
+
 // MAT: the matrix in LDS, row-major with odd stride N + 1 (rows of up to
 // GBS_NSMALL clicks); else in wbuf (row-major, stride N), and the factor in
 // place in vt_out from step 3 on.
@@ -166,6 +494,11 @@ __global__ __launch_bounds__(THREADS) void k_eig(
     const int o = offsets[p], n = offsets[p + 1] - o, N = 2 * n;
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long long vo = voff[p];
+    if (MAT && n <= EIG_TINY) {
+        if (wid == 0)
+            eig_tiny(M, qi, scal, modes + o, n, alpha_out + 2 * o, vt_out + vo, rows + p, frozen, sh);
+        return;
+    }
     static_assert(NW >= 2, "two steps' rotations fit the reduction's arrays");
     double *part = sh;                       // NW x N partial sums
     double *v = part + NW * N, *w = v + N;   // the reflector, its partner in the rank-2
@@ -428,7 +761,7 @@ __global__ __launch_bounds__(THREADS) void k_eig(
     amin = -wave_max(-amin);
     dev = wave_max(dev);
     RowPlan rp = rows[p];
-    row_plan(rp, n, dg, lane, scal[0], logdetA, amin, dev, scal[3] != 0.0 || fail, frozen & 1, (frozen & 2) != 0);
+    row_plan<false>(rp, n, dg, lane, scal[0], logdetA, amin, dev, scal[3] != 0.0 || fail, frozen & 1, (frozen & 2) != 0);
     if (lane == 0) rows[p] = rp;
 }
 
@@ -438,6 +771,14 @@ int eig_rows(gbs_ctx *ctx, gbs_plan *pl)
 {
     if (pl->P == 0) return 0;
     const int fz = (pl->frozen ? 1 : 0) | (pl->whole ? 2 : 0);
+    if (pl->whole && pl->nbig == 0) {
+        const int lds = EIG_ORDERED_LDS(2 * pl->max_n);
+        if (int rc = func_lds_limit(ctx, (const void *)k_eig_whole, lds)) return rc;
+        hipLaunchKernelGGL(k_eig_whole, dim3(1), dim3(256), lds, ctx->stream, ctx->model.M, ctx->model.qi_hi,
+                           ctx->model.scal, pl->d_offsets, pl->d_modes, pl->d_alpha, pl->d_v, pl->d_rows, fz);
+        HIP_TRY(ctx, hipGetLastError());
+        return 0;
+    }
     // (rows by decreasing click count; the larger ones are perm[0..nbig))
     if (pl->nbig > 0) {
         const void *fn = (const void *)k_eig<false, 512>;
@@ -451,15 +792,15 @@ int eig_rows(gbs_ctx *ctx, gbs_plan *pl)
     // run at a time one per class of click counts, so that each class's LDS lets
     // as many of its workgroups as possible share a compute unit (2 above 36
     // clicks, then 3, 4 and 6).
-    constexpr int tops[] = {GBS_NSMALL, 36, 31, 25};
+    constexpr int tops[] = {GBS_NSMALL, 36, 31, 25, EIG_TINY, -1};
     const bool classes = pl->P - pl->nbig > 4 * ctx->num_cu;
     for (int i = pl->nbig, c = 0; i < pl->P; ++c) {
-        const int below = classes && c < 3 ? tops[c + 1] : -1, n0 = pl->h_n[pl->h_perm[i]];
+        if (!classes && c == 0) c = 3;
+        const int below = tops[c + 1], n0 = pl->h_n[pl->h_perm[i]];
         int e = i;
-        if (below < 0) e = pl->P;
         while (e < pl->P && pl->h_n[pl->h_perm[e]] > below) ++e;
         if (e == i) continue;
-        const int lds = eig_lds(2 * n0, 4, true);
+        const int lds = std::max(eig_lds(2 * n0, 4, true), EIG_ORDERED_LDS(2 * EIG_TINY));
         if (int rc = func_lds_limit(ctx, (const void *)k_eig<true, 256>, lds)) return rc;
         hipLaunchKernelGGL((k_eig<true, 256>), dim3(e - i), dim3(256), lds, ctx->stream, ctx->model.M,
                            ctx->model.qi_hi, ctx->model.scal, pl->d_offsets, pl->d_modes, pl->d_perm + i,

@@ -795,8 +795,7 @@ int eig_rows(gbs_ctx *ctx, gbs_plan *pl)
     constexpr int tops[] = {GBS_NSMALL, 36, 31, 25, EIG_TINY, -1};
     const bool classes = pl->P - pl->nbig > 4 * ctx->num_cu;
     for (int i = pl->nbig, c = 0; i < pl->P; ++c) {
-        if (!classes && c == 0) c = 3;
-        const int below = tops[c + 1], n0 = pl->h_n[pl->h_perm[i]];
+        const int below = classes ? tops[c + 1] : -1, n0 = pl->h_n[pl->h_perm[i]];
         int e = i;
         while (e < pl->P && pl->h_n[pl->h_perm[e]] > below) ++e;
         if (e == i) continue;

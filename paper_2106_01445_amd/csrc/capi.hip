@@ -114,14 +114,12 @@ int check_csr(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
 
 void plan_free_dev(gbs_plan *pl)
 {
-    void *ptrs[] = {pl->d_offsets, pl->d_modes, pl->d_perm, pl->d_voff, pl->d_alpha,
-                    pl->d_v, pl->d_rows, pl->d_sw, pl->d_items, pl->d_counter,
-                    pl->d_cluster_items, pl->d_cluster_off, pl->d_logp, pl->d_status,
+    void *ptrs[] = {pl->own_units ? pl->d_cluster_items : nullptr, pl->own_units ? pl->d_cluster_off : nullptr,
                     pl->d_asw, pl->d_aitems, pl->d_roff, pl->d_ritem0, pl->d_axq, pl->d_rscr,
-                    pl->d_qibar, pl->d_qitmp, pl->d_grad, pl->d_dl, pl->d_wbig, pl->d_mscr,
-                    pl->d_ascr, pl->d_da, pl->d_da_x, pl->d_det};
+                    pl->d_qibar, pl->d_qitmp, pl->d_ascr, pl->d_da, pl->d_da_x, pl->d_det};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    if (pl->block) pl->pool->give(pl->block, pl->block_bytes);
 }
 
 // Cluster work units for rows with n clicks (orders 2 and 3), one packed int
@@ -202,27 +200,79 @@ int dev_alloc(gbs_ctx *ctx, T **p, size_t count)
 
 }  // namespace
 
-// (Re)build the cluster work units of a plan for its segment lengths: the
-// forward list, the adjoint list, then (order 4) the quadruple list; offsets
-// [n] -> (offset, count) for the forward at d_cluster_off, for the adjoint at
-// d_cluster_off + 2 (max_n + 1), for the quadruples at d_cluster_off +
-// 4 (max_n + 1).
-int plan_units(gbs_ctx *ctx, gbs_plan *pl)
+void *BlockPool::take(size_t bytes, size_t *got)
+{
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (spare && spare_bytes >= bytes) {
+            void *p = spare;
+            *got = spare_bytes;
+            spare = nullptr;
+            return p;
+        }
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    *got = bytes;
+    return p;
+}
+
+void BlockPool::give(void *p, size_t bytes)
+{
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (!closed && bytes <= KEEP && (!spare || bytes > spare_bytes)) {
+            std::swap(p, spare);
+            spare_bytes = bytes;
+        }
+    }
+    if (p) (void)hipFree(p);
+}
+
+void BlockPool::close()
+{
+    std::lock_guard<std::mutex> lk(mu);
+    closed = true;
+    if (spare) (void)hipFree(spare);
+    spare = nullptr;
+}
+
+namespace {
+// The cluster work units of a plan for its segment lengths, for the click counts
+// of its rows: the forward list, the adjoint list, then (order 4) the quadruple
+// list; offsets [n] -> (offset, count) for the forward at 0, for the adjoint at
+// 2 (max_n + 1), for the quadruples at 4 (max_n + 1).
+void unit_lists(const gbs_plan *pl, std::vector<int32_t> &citems, std::vector<int32_t> &coff)
 {
     const int nm = pl->max_n;
-    std::vector<int32_t> citems, coff(6 * (nm + 1), 0);
+    std::vector<char> present(nm + 1, 0);
+    for (int n : pl->h_n) present[n] = 1;
+    coff.assign(6 * (nm + 1), 0);
     for (int pass = 0; pass < 3; ++pass)
         for (int n = 0; n <= nm; ++n) {
             int32_t *o = coff.data() + 2 * (nm + 1) * pass + 2 * n;
             o[0] = (int32_t)citems.size();
+            if (!present[n]) continue;
             if (pass < 2 && pl->order >= 2)
                 cluster_units(n, pl->order, pass ? pl->seg_adj : pl->seg_fwd, pass == 1, citems);
             if (pass == 2 && pl->order >= 4) quad_units(n, pl->seg_fwd, citems);
             o[1] = (int32_t)citems.size() - o[0];
         }
-    pl->n_cluster_items = (int)citems.size();
-    if (pl->d_cluster_items) (void)hipFree(pl->d_cluster_items);
-    if (pl->d_cluster_off) (void)hipFree(pl->d_cluster_off);
+}
+}  // namespace
+
+// Rebuild the cluster work units of a plan after its segment lengths changed.
+int plan_units(gbs_ctx *ctx, gbs_plan *pl)
+{
+    std::vector<int32_t> citems, coff;
+    unit_lists(pl, citems, coff);
+    // (launches that still read the old lists come before the wait)
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    if (pl->own_units) {
+        (void)hipFree(pl->d_cluster_items);
+        (void)hipFree(pl->d_cluster_off);
+    }
+    pl->own_units = true;
     pl->d_cluster_items = nullptr;
     pl->d_cluster_off = nullptr;
     int e = dev_alloc(ctx, &pl->d_cluster_items, citems.size());
@@ -313,6 +363,8 @@ int gbs_create(gbs_ctx **out, int hip_device, void *hip_stream)
         optin > ctx->lds_per_block)
         ctx->lds_per_block = optin;
     if (ctx->num_cu <= 0) ctx->num_cu = 256;
+    ctx->pool = std::make_shared<BlockPool>();
+    ctx->pool->device = hip_device;
     // the device address of the fixed scratch of gbs_prob_exact_dev_noalloc
     // (once per device; this device is current)
     if (exact_scratch_init(hip_device) != 0) {
@@ -335,6 +387,7 @@ int gbs_destroy(gbs_ctx *ctx)
     }
     for (hipEvent_t e : ctx->event_pool) (void)hipEventDestroy(e);
     if (ctx->ex_part) (void)hipFree(ctx->ex_part);
+    ctx->pool->close();
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
     return GBS_OK;
@@ -364,10 +417,14 @@ int gbs_set_model(gbs_ctx *ctx, int M, const double *U_re, const double *U_im, c
     if (rc) return rc;
     DevModel &m = ctx->model;
     size_t MM = (size_t)M * M;
-    HIP_TRY(ctx, hipMemcpyAsync(m.params, U_re, MM * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + MM, U_im, MM * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM, r, M * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(m.params + 2 * MM + M, eta, M * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+    // (one upload; the build below waits for it)
+    ctx->stage.resize((2 * MM + 2 * M) * sizeof(double));
+    double *sg = (double *)ctx->stage.data();
+    std::copy(U_re, U_re + MM, sg);
+    std::copy(U_im, U_im + MM, sg + MM);
+    std::copy(r, r + M, sg + 2 * MM);
+    std::copy(eta, eta + M, sg + 2 * MM + M);
+    HIP_TRY(ctx, hipMemcpyAsync(m.params, sg, ctx->stage.size(), hipMemcpyHostToDevice, ctx->stream));
     m.from_params = true;
     return model_build_dev(ctx, m.params, m.params + MM, m.params + 2 * MM, m.params + 2 * MM + M, nullptr, true);
 }
@@ -459,8 +516,10 @@ int gbs_get_model(gbs_ctx *ctx, double *q_inv, double *logdet_q)
     return GBS_OK;
 }
 
-int gbs_plan_create(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order,
-                    int prec, gbs_plan **out)
+}  // extern "C"
+
+int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec, size_t extra,
+              gbs_plan **out)
 {
     if (!ctx || !out) return GBS_E_INVAL;
     *out = nullptr;
@@ -503,64 +562,100 @@ int gbs_plan_create(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *
                      [&](int a, int b) { return pl->h_n[a] > pl->h_n[b]; });
     long long max_items = (long long)P * ((GBS_QCAP + GBS_QCHUNK_MIN - 1) / GBS_QCHUNK_MIN);
     pl->max_items = (int)max_items;
-    int e = 0;
-    e = e ? e : dev_alloc(ctx, &pl->d_offsets, P + 1);
-    e = e ? e : dev_alloc(ctx, &pl->d_modes, nnz);
-    e = e ? e : dev_alloc(ctx, &pl->d_perm, P);
-    e = e ? e : dev_alloc(ctx, &pl->d_voff, P);
-    e = e ? e : dev_alloc(ctx, &pl->d_alpha, 2 * (size_t)nnz);
-    e = e ? e : dev_alloc(ctx, &pl->d_v, pl->v_total);
-    e = e ? e : dev_alloc(ctx, &pl->d_rows, P);
-    e = e ? e : dev_alloc(ctx, &pl->d_sw, (size_t)P * (order + 1) * GBS_QCAP);
-    e = e ? e : dev_alloc(ctx, &pl->d_items, 2 * (size_t)max_items);
-    e = e ? e : dev_alloc(ctx, &pl->d_counter, GBS_NCOUNTER);
-    e = e ? e : dev_alloc(ctx, &pl->d_wbig, 2 * pl->v_total);
-    if (pl->nbig > 0) {
-        // M(w) of rows whose blocks do not fit in LDS: one copy per workgroup
-        const long long ms = 2LL * pl->max_n * pl->max_n + 5LL * pl->max_n;
-        if (16 * ms + 16 * 64 > (long long)ctx->lds_per_block - 8 * 1024) {
-            pl->mscr_blocks = 2 * ctx->num_cu;
-            e = e ? e : dev_alloc(ctx, &pl->d_mscr, (size_t)pl->mscr_blocks * ms);
-        }
-    }
-    e = e ? e : dev_alloc(ctx, &pl->d_logp, P);
-    e = e ? e : dev_alloc(ctx, &pl->d_status, P);
-    if (e) {
-        plan_free_dev(pl);
-        delete pl;
-        return e;
-    }
-    hipStream_t st = ctx->stream;
-    auto cp = [&](void *dst, const void *src, size_t bytes) {
-        return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
+    std::vector<int32_t> citems, coff;
+    unit_lists(pl, citems, coff);
+    // the block: first what is uploaded (rows start unplanned, K = 0: a frozen
+    // plan re-plans a row that never got a contour), then the work arrays, each
+    // at a multiple of 256 bytes
+    size_t at = 0;
+    auto put = [&](size_t bytes) {
+        const size_t here = at;
+        at += (std::max(bytes, (size_t)1) + 255) & ~(size_t)255;
+        return here;
     };
-    hipError_t he = hipSuccess;
-    if (he == hipSuccess) he = cp(pl->d_offsets, pl->h_offsets.data(), (P + 1) * sizeof(int32_t));
-    if (he == hipSuccess) he = cp(pl->d_modes, pl->h_modes.data(), nnz * sizeof(int32_t));
-    if (he == hipSuccess) he = cp(pl->d_perm, pl->h_perm.data(), P * sizeof(int32_t));
-    if (he == hipSuccess) he = cp(pl->d_voff, voff.data(), P * sizeof(long long));
-    // (rows start unplanned, K = 0: a frozen plan re-plans a row that never got
-    // a contour)
-    if (he == hipSuccess && P > 0) he = hipMemsetAsync(pl->d_rows, 0, P * sizeof(RowPlan), st);
-    if (he == hipSuccess) he = hipStreamSynchronize(st);
+    const size_t o_off = put((P + 1) * sizeof(int32_t)), o_mod = put(nnz * sizeof(int32_t)),
+                 o_perm = put(P * sizeof(int32_t)), o_voff = put(P * sizeof(long long)),
+                 o_ci = put(citems.size() * sizeof(int32_t)), o_co = put(coff.size() * sizeof(int32_t)),
+                 o_rows = put(P * sizeof(RowPlan)), image = at;
+    const size_t o_alpha = put(2 * (size_t)nnz * sizeof(double)), o_v = put(pl->v_total * sizeof(double)),
+                 o_sw = put((size_t)P * (order + 1) * GBS_QCAP * sizeof(cplx)),
+                 o_items = put(2 * (size_t)max_items * sizeof(int32_t)), o_cnt = put(GBS_NCOUNTER * sizeof(int32_t)),
+                 o_wbig = put(2 * pl->v_total * sizeof(double));
+    // M(w) of rows whose blocks do not fit in LDS: one copy per workgroup
+    const long long ms = 2LL * pl->max_n * pl->max_n + 5LL * pl->max_n;
+    if (pl->nbig > 0 && 16 * ms + 16 * 64 > (long long)ctx->lds_per_block - 8 * 1024) pl->mscr_blocks = 2 * ctx->num_cu;
+    const size_t o_mscr = put((size_t)pl->mscr_blocks * ms * sizeof(cplx)),
+                 // (log p and the status next to each other: one copy back)
+                 o_logp = put(P * (sizeof(double) + sizeof(int32_t))), o_extra = put(extra);
+    pl->pool = ctx->pool;
+    pl->block = ctx->pool->take(at, &pl->block_bytes);
+    if (!pl->block) {
+        delete pl;
+        return set_err(ctx, GBS_E_NOMEM, "device allocation of " + std::to_string(at) + " bytes failed");
+    }
+    char *base = (char *)pl->block;
+    pl->d_offsets = (int32_t *)(base + o_off);
+    pl->d_modes = (int32_t *)(base + o_mod);
+    pl->d_perm = (int32_t *)(base + o_perm);
+    pl->d_voff = (long long *)(base + o_voff);
+    pl->d_cluster_items = (int32_t *)(base + o_ci);
+    pl->d_cluster_off = (int32_t *)(base + o_co);
+    pl->d_rows = (RowPlan *)(base + o_rows);
+    pl->d_alpha = (double *)(base + o_alpha);
+    pl->d_v = (double *)(base + o_v);
+    pl->d_sw = (cplx *)(base + o_sw);
+    pl->d_items = (int32_t *)(base + o_items);
+    pl->d_counter = (int32_t *)(base + o_cnt);
+    pl->d_wbig = (double *)(base + o_wbig);
+    if (pl->mscr_blocks > 0) pl->d_mscr = (cplx *)(base + o_mscr);
+    pl->d_logp = (double *)(base + o_logp);
+    pl->d_status = (int32_t *)(pl->d_logp + P);
+    pl->d_extra = base + o_extra;
+    pl->h_image.assign(image, 0);
+    auto fill = [&](size_t o, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(pl->h_image.data() + o, src, bytes);
+    };
+    fill(o_off, pl->h_offsets.data(), (P + 1) * sizeof(int32_t));
+    fill(o_mod, pl->h_modes.data(), nnz * sizeof(int32_t));
+    fill(o_perm, pl->h_perm.data(), P * sizeof(int32_t));
+    fill(o_voff, voff.data(), P * sizeof(long long));
+    fill(o_ci, citems.data(), citems.size() * sizeof(int32_t));
+    fill(o_co, coff.data(), coff.size() * sizeof(int32_t));
+    const hipError_t he = hipMemcpyAsync(base, pl->h_image.data(), image, hipMemcpyHostToDevice, ctx->stream);
     if (he != hipSuccess) {
         plan_free_dev(pl);
         delete pl;
         return set_err(ctx, GBS_E_HIP, hipGetErrorString(he));
     }
-    if ((rc = plan_units(ctx, pl))) {
-        plan_free_dev(pl);
-        delete pl;
-        return rc;
-    }
     *out = pl;
+    return GBS_OK;
+}
+
+extern "C" {
+
+int gbs_plan_create(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec,
+                    gbs_plan **out)
+{
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, out);
+    if (rc) return rc;
+    // (the upload's host copy is not needed any longer)
+    const hipError_t he = hipStreamSynchronize(ctx->stream);
+    if (he != hipSuccess) {
+        gbs_plan_destroy(*out);
+        *out = nullptr;
+        return set_err(ctx, GBS_E_HIP, hipGetErrorString(he));
+    }
+    std::vector<char>().swap((*out)->h_image);
     return GBS_OK;
 }
 
 int gbs_plan_destroy(gbs_plan *pl)
 {
     if (!pl) return GBS_E_INVAL;
-    if (pl->ctx) (void)hipSetDevice(pl->ctx->device);
+    (void)hipSetDevice(pl->pool->device);
+    // (the block goes on to the context's next call: what may still use it on
+    // other streams, a recorded step's replay, comes first)
+    (void)hipDeviceSynchronize();
     plan_free_dev(pl);
     delete pl;
     return GBS_OK;
@@ -588,23 +683,45 @@ int gbs_prob_approx_dev(gbs_ctx *ctx, gbs_plan *pl, double *logp_dev, int32_t *s
     return rc;
 }
 
+}  // extern "C"
+
+namespace {
+// a host call's results: log p (nullable) and the status of every row, in one copy
+int rows_back(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
+{
+    const size_t P = pl->P;
+    if (P == 0) return 0;
+    ctx->stage.resize(P * (sizeof(double) + sizeof(int32_t)));
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->stage.data(), pl->d_logp, ctx->stage.size(), hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    const char *s = ctx->stage.data();
+    if (logp) std::memcpy(logp, s, P * sizeof(double));
+    std::memcpy(status, s + P * sizeof(double), P * sizeof(int32_t));
+    return 0;
+}
+// the end of a host call on its own plan: nothing of the plan is in use when its
+// block and its host image go back, also after an error
+void call_done(gbs_ctx *ctx, gbs_plan *pl)
+{
+    (void)hipStreamSynchronize(ctx->stream);
+    plan_free_dev(pl);
+    delete pl;
+}
+}  // namespace
+
+extern "C" {
+
 int gbs_prob_approx(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order,
                     int prec, double *logp, int32_t *status)
 {
     if (!ctx) return GBS_E_INVAL;
     if (P > 0 && (!logp || !status)) return set_err(ctx, GBS_E_INVAL, "NULL output array");
     gbs_plan *pl = nullptr;
-    int rc = gbs_plan_create(ctx, P, offsets, modes, order, prec, &pl);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, &pl);
     if (rc) return rc;
     rc = gbs_prob_approx_dev(ctx, pl, pl->d_logp, pl->d_status);
-    if (rc == 0 && P > 0) {
-        hipError_t e = hipMemcpyAsync(logp, pl->d_logp, P * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(status, pl->d_status, P * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) rc = set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
-    }
-    gbs_plan_destroy(pl);
+    if (rc == 0) rc = rows_back(ctx, pl, logp, status);
+    call_done(ctx, pl);
     if (rc) return rc;
     for (int p = 0; p < P; ++p)
         if (status[p] != 0) return GBS_W_PATTERN;
@@ -617,21 +734,15 @@ int gbs_prob_approx_plain(gbs_ctx *ctx, int P, const int32_t *offsets, const int
     if (!ctx) return GBS_E_INVAL;
     if (P > 0 && (!logp || !status)) return set_err(ctx, GBS_E_INVAL, "NULL output array");
     gbs_plan *pl = nullptr;
-    int rc = gbs_plan_create(ctx, P, offsets, modes, order, prec, &pl);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, &pl);
     if (rc) return rc;
     rc = pl->max_n > GBS_NSMALL
              ? set_err(ctx, GBS_E_INVAL, "the plain kernel takes rows of at most 40 clicks")
          : prec != GBS_PREC_FP64
              ? set_err(ctx, GBS_E_INVAL, "the plain kernel runs in fp64 only")
              : approx_forward_plain(ctx, pl, pl->d_logp, pl->d_status);
-    if (rc == 0 && P > 0) {
-        hipError_t e = hipMemcpyAsync(logp, pl->d_logp, P * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(status, pl->d_status, P * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (e != hipSuccess) rc = set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
-    }
-    gbs_plan_destroy(pl);
+    if (rc == 0) rc = rows_back(ctx, pl, logp, status);
+    call_done(ctx, pl);
     if (rc) return rc;
     for (int p = 0; p < P; ++p)
         if (status[p] != 0) return GBS_W_PATTERN;
@@ -968,34 +1079,31 @@ int gbs_click_distribution(gbs_ctx *ctx, int order, int nk, const int32_t *ks, d
     std::vector<int32_t> off = {0, M}, mod(M);
     std::iota(mod.begin(), mod.end(), 0);
     gbs_plan *pl = nullptr;
-    int rc = gbs_plan_create(ctx, 1, off.data(), mod.data(), order, GBS_PREC_FP64, &pl);
+    // (device side: p_n, p_k, the status, then ks)
+    const size_t nout = (size_t)(nk + 1) * (M + 1), back = nout * sizeof(double) + sizeof(int32_t);
+    int rc = plan_make(ctx, 1, off.data(), mod.data(), order, GBS_PREC_FP64, back + nk * sizeof(int32_t), &pl);
     if (rc) return rc;
     pl->whole = true;
-    int *dks = nullptr;
-    double *dpn = nullptr, *dpk = nullptr;
-    int32_t *dst = nullptr;
-    rc = dev_alloc(ctx, &dks, nk > 0 ? nk : 1);
-    if (!rc) rc = dev_alloc(ctx, &dpn, M + 1);
-    if (!rc) rc = dev_alloc(ctx, &dpk, nk > 0 ? (size_t)nk * (M + 1) : 1);
-    if (!rc) rc = dev_alloc(ctx, &dst, 1);
+    double *dpn = (double *)pl->d_extra, *dpk = dpn + M + 1;
+    int32_t *dst = (int32_t *)(dpn + nout), *dks = dst + 1;
     hipStream_t st = ctx->stream;
-    if (!rc && nk > 0 &&
-        hipMemcpyAsync(dks, ks, nk * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess)
+    if (nk > 0 && hipMemcpyAsync(dks, ks, nk * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = set_err(ctx, GBS_E_HIP, "copy of ks failed");
     if (!rc) rc = click_distribution_run(ctx, pl, nk, dks, dpn, dpk, dst);
     if (!rc) {
-        hipError_t e = hipMemcpyAsync(p_n, dpn, (M + 1) * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && nk > 0)
-            e = hipMemcpyAsync(p_k, dpk, (size_t)nk * (M + 1) * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(status, dst, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+        ctx->stage.resize(back);
+        const char *sg = ctx->stage.data();
+        hipError_t e = hipMemcpyAsync(ctx->stage.data(), dpn, back, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) rc = set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
+        if (e != hipSuccess) {
+            rc = set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
+        } else {
+            std::memcpy(p_n, sg, (M + 1) * sizeof(double));
+            if (nk > 0) std::memcpy(p_k, sg + (M + 1) * sizeof(double), (size_t)nk * (M + 1) * sizeof(double));
+            std::memcpy(status, sg + nout * sizeof(double), sizeof(int32_t));
+        }
     }
-    if (dks) (void)hipFree(dks);
-    if (dpn) (void)hipFree(dpn);
-    if (dpk) (void)hipFree(dpk);
-    if (dst) (void)hipFree(dst);
-    gbs_plan_destroy(pl);
+    call_done(ctx, pl);
     if (rc) return rc;
     return *status != 0 ? GBS_W_PATTERN : GBS_OK;
 }
@@ -1009,28 +1117,27 @@ int gbs_grad(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, 
     if (!ctx->model.have || !ctx->model.from_params)
         return set_err(ctx, GBS_E_STATE, "gradient needs a model set by gbs_set_model");
     gbs_plan *pl = nullptr;
-    int rc = gbs_plan_create(ctx, P, offsets, modes, order, prec, &pl);
-    if (rc) return rc;
     int M = ctx->model.M;
-    rc = dev_alloc(ctx, &pl->d_dl, P > 0 ? P : 1);
-    if (!rc) rc = dev_alloc(ctx, &pl->d_grad, 2 * (size_t)M);
+    // (device side: the gradients, then the rows' weights)
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, (2 * (size_t)M + std::max(P, 0)) * sizeof(double), &pl);
+    if (rc) return rc;
+    double *dg = (double *)pl->d_extra, *ddl = dg + 2 * M;
     hipStream_t st = ctx->stream;
-    if (!rc && P > 0 &&
-        hipMemcpyAsync(pl->d_dl, dL_dlogp, P * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess)
+    if (P > 0 && hipMemcpyAsync(ddl, dL_dlogp, P * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = set_err(ctx, GBS_E_HIP, "copy of dL_dlogp failed");
-    if (!rc) rc = gbs_grad_dev(ctx, pl, pl->d_dl, pl->d_logp, pl->d_grad, pl->d_grad + M, pl->d_status);
+    if (!rc) rc = gbs_grad_dev(ctx, pl, ddl, pl->d_logp, dg, dg + M, pl->d_status);
     if (!rc) {
-        hipError_t e = hipMemcpyAsync(grad_r, pl->d_grad, M * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(grad_eta, pl->d_grad + M, M * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && logp && P > 0)
-            e = hipMemcpyAsync(logp, pl->d_logp, P * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess && P > 0)
-            e = hipMemcpyAsync(status, pl->d_status, P * sizeof(int32_t), hipMemcpyDeviceToHost, st);
+        std::vector<double> g(2 * (size_t)M);
+        hipError_t e = hipMemcpyAsync(g.data(), dg, g.size() * sizeof(double), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) rc = set_err(ctx, GBS_E_HIP, hipGetErrorString(e));
+        if (!rc) rc = rows_back(ctx, pl, logp, status);
+        if (!rc) {
+            std::copy(g.begin(), g.begin() + M, grad_r);
+            std::copy(g.begin() + M, g.end(), grad_eta);
+        }
     }
-    gbs_plan_destroy(pl);
+    call_done(ctx, pl);
     if (rc) return rc;
     for (int i = 0; i < P; ++i)
         if (status[i] != 0) return GBS_W_PATTERN;

@@ -33,6 +33,7 @@
 // wavefronts per compute unit): one row of 30 clicks 502 -> 31.6 ms (3.4e10
 // subsets/s), 4096 rows of 6-14 clicks at 20 modes 8.60 -> 0.62 ms.
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 
 #include "internal.h"
@@ -592,7 +593,8 @@ double *exact_scratch(int device)
     return scratch_ptr[device];
 }
 
-// Host CSR (already checked): copies in, one launch, copies out.
+// Host CSR (already checked): one copy in, one launch, one copy out, in a block
+// of the context's pool.
 int exact_run(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, double *p,
               double *logp, double *kappa, int32_t *status)
 {
@@ -601,43 +603,33 @@ int exact_run(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
     int maxn = 0;
     for (int r = 0; r < P; ++r) maxn = std::max(maxn, offsets[r + 1] - offsets[r]);
     const long long nitems = (long long)P << exact_lgs(maxn);
-    const int nnz = offsets[P];
-    int32_t *d_off = nullptr, *d_modes = nullptr, *d_st = nullptr;
-    double *d_part = nullptr, *d_out = nullptr;
-    auto cleanup = [&]() {
-        void *ptrs[] = {d_off, d_modes, d_st, d_part, d_out};
-        for (void *q : ptrs)
-            if (q) (void)hipFree(q);
-    };
-    if (hipMalloc((void **)&d_off, (P + 1) * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc((void **)&d_modes, std::max(nnz, 1) * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc((void **)&d_st, P * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc((void **)&d_part, std::max(nitems, 1LL) * 3 * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&d_out, (size_t)P * 3 * sizeof(double)) != hipSuccess) {
-        cleanup();
-        return set_err(ctx, GBS_E_NOMEM, "exact: device allocation failed");
-    }
-    hipError_t e = hipMemcpyAsync(d_off, offsets, (P + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && nnz)
-        e = hipMemcpyAsync(d_modes, modes, nnz * sizeof(int32_t), hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) {
-        cleanup();
-        return set_err(ctx, GBS_E_HIP, std::string("exact: ") + hipGetErrorString(e));
-    }
-    int rc = exact_launch(ctx, P, d_off, d_modes, maxn, d_part, d_out, d_out + P, d_out + 2 * P, d_st);
-    std::vector<double> out((size_t)P * 3);
-    if (!rc) {
-        e = hipMemcpyAsync(out.data(), d_out, out.size() * sizeof(double), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(status, d_st, P * sizeof(int32_t), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) rc = set_err(ctx, GBS_E_HIP, std::string("exact: ") + hipGetErrorString(e));
-    }
-    cleanup();
+    const size_t nnz = offsets[P], n = P;
+    // the block: p, log p, kappa and status of every row; the rows; the partial sums
+    const size_t back = n * (3 * sizeof(double) + sizeof(int32_t)), in = (n + 1 + nnz) * sizeof(int32_t);
+    const size_t o_part = (back + in + 15) & ~(size_t)15;
+    size_t got = 0;
+    char *blk = (char *)ctx->pool->take(o_part + std::max(nitems, 1LL) * 3 * sizeof(double), &got);
+    if (!blk) return set_err(ctx, GBS_E_NOMEM, "exact: device allocation failed");
+    double *d_out = (double *)blk;
+    int32_t *d_st = (int32_t *)(d_out + 3 * n), *d_off = d_st + n, *d_modes = d_off + n + 1;
+    ctx->stage.resize(std::max(in, back));
+    std::memcpy(ctx->stage.data(), offsets, (n + 1) * sizeof(int32_t));
+    if (nnz) std::memcpy(ctx->stage.data() + (n + 1) * sizeof(int32_t), modes, nnz * sizeof(int32_t));
+    int rc = 0;
+    hipError_t e = hipMemcpyAsync(d_off, ctx->stage.data(), in, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+        rc = exact_launch(ctx, P, d_off, d_modes, maxn, (double *)(blk + o_part), d_out, d_out + n, d_out + 2 * n, d_st);
+    // (the upload is done before its host copy takes the results)
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (!rc && e == hipSuccess) e = hipMemcpyAsync(ctx->stage.data(), blk, back, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    ctx->pool->give(blk, got);
+    if (e != hipSuccess) return set_err(ctx, GBS_E_HIP, std::string("exact: ") + hipGetErrorString(e));
     if (rc) return rc;
-    for (int r = 0; r < P; ++r) {
-        p[r] = out[r];
-        if (logp) logp[r] = out[P + r];
-        if (kappa) kappa[r] = out[2 * (size_t)P + r];
-    }
+    const double *out = (const double *)ctx->stage.data();
+    std::copy(out, out + n, p);
+    if (logp) std::copy(out + n, out + 2 * n, logp);
+    if (kappa) std::copy(out + 2 * n, out + 3 * n, kappa);
+    std::memcpy(status, out + 3 * n, n * sizeof(int32_t));
     return 0;
 }

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <map>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -52,6 +54,26 @@ struct DevModel {
     double *expd = nullptr;         // e^{-2r}, e^{2r} as dd (4M doubles) and sqrt(eta) dd (4M)
 };
 
+// Device memory of the short-lived objects of a context (plans, one call's
+// buffers), a block each.  The pool keeps the block given back last, up to
+// 64 MiB, for the next one that fits in it: a call on host arrays then pays for
+// no hipMalloc and hipFree (10 to 50 us each, and a wait for the whole device).
+// A kept block is only reused by work on the context's stream, which comes after
+// everything that used it before.  Plans share the pool's ownership: those that
+// outlive the context free their blocks themselves.
+struct BlockPool {
+    static constexpr size_t KEEP = 64u << 20;
+    int device = 0;
+    std::mutex mu;
+    bool closed = false;
+    void *spare = nullptr;
+    size_t spare_bytes = 0;
+    // a block of at least `bytes` (its size in *got), or null
+    void *take(size_t bytes, size_t *got);
+    void give(void *p, size_t bytes);
+    void close();
+};
+
 struct TimedLaunch {
     int group;
     hipEvent_t a, b;
@@ -73,6 +95,8 @@ struct gbs_ctx {
     // the kernel itself, so a step can be recorded into a HIP graph
     std::map<const void *, int> lds_limit, lds_static;
     std::map<std::pair<const void *, int>, int> occupancy;
+    std::shared_ptr<BlockPool> pool;
+    std::vector<char> stage;  // host side of the model's and the exact path's copies
     // partial sums of gbs_prob_exact_dev (grown on demand, freed with the context)
     double *ex_part = nullptr;
     long long ex_part_items = 0;
@@ -122,7 +146,14 @@ struct gbs_plan {
     bool whole = false;                   // one row of every mode: contour at rho = 1 (click distribution)
     bool have_run = false;
     std::vector<int32_t> h_offsets, h_modes, h_perm, h_n;
-    // device
+    // device: one block of the context's pool holds the arrays from here to
+    // d_status, with the cluster units the plan was made with and the caller's
+    // extra bytes; its uploaded part is a copy of h_image
+    std::shared_ptr<BlockPool> pool;
+    void *block = nullptr, *d_extra = nullptr;
+    size_t block_bytes = 0;
+    std::vector<char> h_image;
+    bool own_units = false;               // d_cluster_* are allocations of their own (plan_units)
     int32_t *d_offsets = nullptr, *d_modes = nullptr, *d_perm = nullptr;
     long long *d_voff = nullptr;          // offset of row p's eigenvectors in d_v
     double *d_alpha = nullptr;            // 2n per row, offset 2*offsets[p]
@@ -150,7 +181,6 @@ struct gbs_plan {
     int32_t *d_status = nullptr;          // P
     size_t v_total = 0;
     int max_items = 0;
-    int n_cluster_items = 0;
     // gradient workspace (allocated by the first gradient call)
     bool have_adj = false;
     cplx *d_asw = nullptr;                // cotangents of the cluster sums, like d_sw
@@ -161,8 +191,6 @@ struct gbs_plan {
     double *d_rscr = nullptr;             // per item: upper triangle of R
     double *d_qibar = nullptr;            // (2M)^2: Psi (adjoint of Q^{-1}), then sigma_bar
     double *d_qitmp = nullptr;            // (2M)^2 scratch
-    double *d_grad = nullptr;             // 2M: grad r, grad eta (gbs_grad's own)
-    double *d_dl = nullptr;               // P
     cplx *d_ascr = nullptr;               // per-workgroup adjoint scratch of the larger rows
     int ascr_blocks = 0;
     long long ascr_stride = 0;            // complex entries per workgroup
@@ -201,3 +229,6 @@ int click_distribution_run(gbs_ctx *ctx, gbs_plan *pl, int nk, const int *ks_dev
                            int32_t *status_dev);
 int approx_forward_plain(gbs_ctx *ctx, gbs_plan *plan, double *logp_dev, int32_t *status_dev);
 int plan_units(gbs_ctx *ctx, gbs_plan *plan);
+// gbs_plan_create with `extra` more bytes of device memory (pl->d_extra)
+int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec, size_t extra,
+              gbs_plan **out);

@@ -42,6 +42,18 @@
 
 #define ADJ_QCHUNK GBS_ADJ_CHUNK
 static_assert(GBS_ADJ_CHUNK_BIG <= ADJ_QCHUNK, "one pass of points per item fits s_wq");
+// Contour points per item of a row of up to GBS_NSMALL clicks with Qn points.
+// Where such rows are fewer than the compute units (fine), an item per 64 points
+// leaves most units without one: an item is then 1/17 of the row (the items the
+// lists and the R slots have room for at the largest contour), but not under 8
+// points, below which staging V and writing R weigh more than the points (64
+// rows at 20 modes, order 2: 431 us with 64, 373 so).
+#define ADJ_QMIN 8
+#define ADJ_ITEMS ((GBS_QCAP + ADJ_QCHUNK - 1) / ADJ_QCHUNK)
+__device__ __forceinline__ int adj_chunk(int Qn, int fine)
+{
+    return fine ? min(ADJ_QCHUNK, max(ADJ_QMIN, (Qn + ADJ_ITEMS - 1) / ADJ_ITEMS)) : ADJ_QCHUNK;
+}
 
 namespace {
 
@@ -188,7 +200,7 @@ __global__ __launch_bounds__(CONT_THREADS) void k_adj_contour(
     int *__restrict__ q_head, const int *__restrict__ units, const int *__restrict__ unit_off,
     const int *__restrict__ unit4_off,
     const cplx *__restrict__ asw, const long long *__restrict__ roff, double *__restrict__ rscr,
-    cplx *__restrict__ ascr, long long ascr_stride, const int *__restrict__ xq)
+    cplx *__restrict__ ascr, long long ascr_stride, const int *__restrict__ xq, int fine)
 {
     extern __shared__ __attribute__((aligned(16))) double sh[];
     __shared__ int s_item;
@@ -330,7 +342,7 @@ __global__ __launch_bounds__(CONT_THREADS) void k_adj_contour(
         auto zo = [&](int k, int q, cplx v) { zadd(zoff + k * ostr + q, v, true); };
         for (int i = tid; i < N; i += CONT_THREADS) al[i] = alpha[2 * o + i];
         const int Qn = rp.K / 2 + 1;
-        constexpr int QCH = BIG ? GBS_ADJ_CHUNK_BIG : ADJ_QCHUNK;
+        const int QCH = BIG ? GBS_ADJ_CHUNK_BIG : adj_chunk(Qn, fine);
         const int q0 = ch * QCH, q1 = min(q0 + QCH, Qn);
         const int T = (N + 15) >> 4, KS = (N + 3) >> 2;
         // rows up to 40 clicks: this wavefront's share of R (its column unit's
@@ -1581,7 +1593,7 @@ __global__ __launch_bounds__(CONT_THREADS) void k_adj_pairs_big(
 }
 
 // ---------------------------------------------------------------------------
-// k_adj_items: backward work items (row, chunk of ADJ_QCHUNK points) and the
+// k_adj_items: backward work items (row, chunk of adj_chunk points) and the
 // offsets of their R scratch
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_adj_items(int P, int nbig, const int *__restrict__ offsets,
@@ -1589,7 +1601,7 @@ __global__ __launch_bounds__(1024) void k_adj_items(int P, int nbig, const int *
                                                     const RowPlan *__restrict__ rows,
                                                     int *__restrict__ items, long long *__restrict__ roff,
                                                     int *__restrict__ row_item0, int *__restrict__ counter,
-                                                    int *__restrict__ xq)
+                                                    int *__restrict__ xq, int fine)
 {
     __shared__ int part[1024];
     __shared__ long long lpart[1024];
@@ -1601,7 +1613,7 @@ __global__ __launch_bounds__(1024) void k_adj_items(int P, int nbig, const int *
         const int n = offsets[p + 1] - offsets[p];
         const RowPlan &rp = rows[p];
         if (n == 0 || rp.status != 0 || rp.K <= 0) return 0;
-        const int qc = n > GBS_NSMALL ? GBS_ADJ_CHUNK_BIG : ADJ_QCHUNK;
+        const int qc = n > GBS_NSMALL ? GBS_ADJ_CHUNK_BIG : adj_chunk(rp.K / 2 + 1, fine);
         return (rp.K / 2 + 1 + qc - 1) / qc;
     };
     auto rsz = [&](int i) {
@@ -1745,7 +1757,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce(int M, const int *__restrict
                                                     const long long *__restrict__ roff,
                                                     const double *__restrict__ rscr,
                                                     double *__restrict__ psi, int mode,
-                                                    unsigned long long *__restrict__ det)
+                                                    unsigned long long *__restrict__ det, int fine)
 {
     extern __shared__ __attribute__((aligned(16))) double sh[];
     const int p = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
@@ -1755,7 +1767,7 @@ __global__ __launch_bounds__(256) void k_adj_reduce(int M, const int *__restrict
     if (n == 0 || n > GBS_NSMALL) return;
     const int it0 = row_item0[p];
     if (it0 < 0 || rp.status != 0 || (status[p] & GBS_PS_FAILED) || !isfinite(dl[p]) || dl[p] == 0.0) return;
-    const int nit = (rp.K / 2 + 1 + ADJ_QCHUNK - 1) / ADJ_QCHUNK;
+    const int qc = adj_chunk(rp.K / 2 + 1, fine), nit = (rp.K / 2 + qc) / qc;
     double *V = sh;            // V[i][k] row-major
     double *R = V + N * N;     // full symmetric
     double *T = R + N * N;
@@ -2020,9 +2032,10 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
     hipStream_t st = ctx->stream;
     DevModel &m = ctx->model;
     const int P = pl->P, nmax = pl->max_n, M = m.M;
+    const int fine = P - pl->nbig <= ctx->num_cu;
     int ts = timer_begin(ctx, TG_ADJ_CLUSTER);
     hipLaunchKernelGGL(k_adj_items, dim3(1), dim3(1024), 0, st, P, pl->nbig, pl->d_offsets, pl->d_perm,
-                       pl->d_rows, pl->d_aitems, pl->d_roff, pl->d_ritem0, pl->d_counter, pl->d_axq);
+                       pl->d_rows, pl->d_aitems, pl->d_roff, pl->d_ritem0, pl->d_counter, pl->d_axq, fine);
     if constexpr (ORDER == 2) {
         if (pl->nbig > 0) {
             // larger rows at order 2: M(w) never stored, the pair blocks of Z(w) in
@@ -2069,7 +2082,7 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
                            pl->d_counter + 8 + GBS_NXCD, pl->d_counter + 8,
                            pl->d_cluster_items, pl->d_cluster_off + 2 * (pl->max_n + 1),
                            pl->order >= 4 ? pl->d_cluster_off + 4 * (pl->max_n + 1) : nullptr, pl->d_asw,
-                           pl->d_roff, pl->d_rscr, pl->d_ascr, pl->ascr_stride, pl->d_axq);
+                           pl->d_roff, pl->d_rscr, pl->d_ascr, pl->ascr_stride, pl->d_axq, fine);
     }
     const int ns = pl->max_n_small;
     if (pl->nbig < P) {
@@ -2092,7 +2105,7 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
                            pl->d_aitems, pl->d_counter + 2, pl->d_counter + 3,
                            pl->d_cluster_items, pl->d_cluster_off + 2 * (pl->max_n + 1),
                            pl->order >= 4 ? pl->d_cluster_off + 4 * (pl->max_n + 1) : nullptr, pl->d_asw,
-                           pl->d_roff, pl->d_rscr, (cplx *)nullptr, 0LL, (const int *)nullptr);
+                           pl->d_roff, pl->d_rscr, (cplx *)nullptr, 0LL, (const int *)nullptr, fine);
     }
     timer_end(ctx, ts);
     ts = timer_begin(ctx, TG_ADJ_ROWS);
@@ -2110,7 +2123,7 @@ int backward_order(gbs_ctx *ctx, gbs_plan *pl, const double *dl, const int32_t *
             if (int rc = func_lds_limit(ctx, (const void *)k_adj_reduce, (int)lds_r)) return rc;
             hipLaunchKernelGGL(k_adj_reduce, dim3(P), dim3(256), lds_r, st, M, pl->d_offsets, pl->d_modes,
                                pl->d_voff, pl->d_alpha, pl->d_v, pl->d_rows, dl, status, pl->d_ritem0,
-                               pl->d_roff, pl->d_rscr, pl->d_qibar, mode, pl->d_det);
+                               pl->d_roff, pl->d_rscr, pl->d_qibar, mode, pl->d_det, fine);
         }
         if (pl->nbig > 0)
             hipLaunchKernelGGL(k_adj_reduce_big, dim3(pl->nbig), dim3(512), 0, st, M, pl->d_offsets,

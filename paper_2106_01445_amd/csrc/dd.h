@@ -102,32 +102,33 @@ __host__ __device__ __forceinline__ dd dd_sqrt(dd x)
 }
 
 // 1/sqrt(x) for x > 0: the fp64 value y and the next terms of its series in
-// e = 1 - x y^2 (|e| of the order of 1e-16): y + y e (1/2 + 3 e / 8), with e
-// formed from error-free products (1 - x.hi y^2 cancels exactly).
+// e = 1 - x y^2 (|e| of the order of 1e-16): y + y (e/2 + 3 e^2 / 8).  1 - x.hi y^2
+// cancels exactly but for the products' low parts s; e is below that difference's
+// own grid, so the rounding r of e is kept too.
 __device__ __forceinline__ dd dd_rsqrt(dd x)
 {
 #pragma clang fp contract(off)
     const double y = rsqrt(x.hi);
     const dd h = two_prod(y, y);
     const dd q = two_prod(x.hi, h.hi);
-    double e = (1.0 - q.hi) - q.lo;
-    e = fma(-x.hi, h.lo, e);
-    e = fma(-x.lo, h.hi, e);
-    return quick_two_sum(y, y * e * fma(0.375, e, 0.5));
+    const double a = 1.0 - q.hi;
+    const double s = fma(x.lo, h.hi, fma(x.hi, h.lo, q.lo));
+    const double e = a - s, r = (a - e) - s;
+    const double w = 0.5 * y;
+    return quick_two_sum(y, fma(w, e, w * fma(0.75 * e, e, r)));
 }
 
 // a - p q and a - p q - r s: error-free leading products and sums, what is
-// below them in one fp64 sum (errors of a few 2^-106 of the largest term, as
-// dd_mul and dd_add leave)
+// below them in fp64 sums (about five roundings of up to 2^-106 of the largest
+// term, where dd_mul and dd_sub leave six).  The first adds its low parts as a
+// short tree: it forms the pivots, whose errors reach every later entry.
 __device__ __forceinline__ dd dd_fms(dd a, dd p, dd q)
 {
 #pragma clang fp contract(off)
     const dd t = two_prod(p.hi, q.hi);
     const dd u = two_sum(a.hi, -t.hi);
-    double lo = fma(-p.hi, q.lo, a.lo);
-    lo = fma(-p.lo, q.hi, lo);
-    lo += u.lo - t.lo;
-    return quick_two_sum(u.hi, lo);
+    const double c = fma(p.hi, q.lo, p.lo * q.hi);
+    return quick_two_sum(u.hi, (a.lo - t.lo) + (u.lo - c));
 }
 __device__ __forceinline__ dd dd_fms2(dd a, dd p, dd q, dd r, dd s)
 {

@@ -20,18 +20,23 @@
 //   - the last S + 1 modes: one lane per node and choice of the first of them
 //     (lanes 0..31 without it, 32..63 with it), which then walks the tree of
 //     the other S modes in registers.
-// Signed sums are double-double, reduced in a fixed order; kappa =
-// sum|terms| / |sum| is returned.
+// A lane's signed sum is kept in three words, the lanes' and parts' sums in
+// double-double, in a fixed order; kappa = sum|terms| / |sum| is returned.
+// Against binary128 the rms error at 3 / 6 / 8 / 10 / 11 clicks and kappa of
+// 1e18 is 0.183 / 0.070 / 0.037 / 0.018 / 0.013 kappa 2^-106; with sums in two
+// words and inverse roots off by a few units it was 0.258 / 0.099 / 0.050 /
+// 0.035 / 0.023, with full double-double operations at every step of a Schur
+// complement by inverse blocks 0.206 / 0.106 / 0.053 / 0.026 / 0.019.
 //
-// What bounds it: the fp64 vector ALUs (about 390 operations per subset, the
+// What bounds it: the fp64 vector ALUs (about 410 operations per subset, the
 // Schur complements 7 entries of them at 27 each, and as many again for the
 // levels' redundant factors and the lanes that carry an excluded mode).  The
 // breadth-first levels of 64 lanes' nodes take 39 KB of LDS, so that one
 // wavefront sits on each SIMD with 512 registers, and the independent entries
 // of a step keep it busy.  Against levels that end with three modes per node,
 // copy excluded children and pay 122 operations per entry (43 KB, three
-// wavefronts per compute unit): one row of 30 clicks 502 -> 31.6 ms (3.4e10
-// subsets/s), 4096 rows of 6-14 clicks at 20 modes 8.60 -> 0.62 ms.
+// wavefronts per compute unit): one row of 30 clicks 502 -> 32.5 ms (3.3e10
+// subsets/s), 4096 rows of 6-14 clicks at 20 modes 8.60 -> 0.64 ms.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -86,12 +91,26 @@ __device__ __forceinline__ Piv factor(dd a, dd b, dd d)
 }
 __device__ __forceinline__ dd rdet(dd a, dd b, dd d) { return dd_rsqrt(dd_fms(dd_mul(a, d), b, b)); }
 
-__device__ __forceinline__ void add_term(dd v, dd &tot, double &ab)
+// A lane's signed sum in three words, hi + mid + lo: the terms cancel by up to
+// 1e20, and every rounding of the sum counts in full.  Adding a term loses
+// nothing above 2^-159 of the sum, for the operations of one dd_add.
+struct Sum {
+    double hi, mid, lo, ab;  // ab: the sum of the terms' moduli
+};
+__device__ __forceinline__ void add_term(dd v, Sum &s)
 {
-    const dd s = two_sum(tot.hi, v.hi);
-    tot.lo += s.lo + v.lo;
-    tot.hi = s.hi;
-    ab += fabs(v.hi);
+    const dd a = two_sum(s.hi, v.hi);
+    const dd b = two_sum(s.mid, a.lo);
+    const dd c = two_sum(b.hi, v.lo);
+    s.hi = a.hi;
+    s.mid = c.hi;
+    s.lo += b.lo + c.lo;
+    s.ab += fabs(v.hi);
+}
+__device__ __forceinline__ dd sum_dd(const Sum &s)
+{
+    const dd a = two_sum(s.hi, s.mid);
+    return quick_two_sum(a.hi, a.lo + s.lo);
 }
 
 // The first of K modes held in registers (packed, last mode first) taken out of
@@ -130,18 +149,18 @@ __device__ __forceinline__ dd step(const dd (&A)[ex_e(K)], dd (&B)[ex_e(K - 1)])
 // The subsets of K modes held in registers; acc: the product of the inverse
 // roots so far with the subset's sign.
 template <int K>
-__device__ __forceinline__ void walk(const dd (&A)[ex_e(K)], dd acc, dd &tot, double &ab)
+__device__ __forceinline__ void walk(const dd (&A)[ex_e(K)], dd acc, Sum &sum)
 {
     if constexpr (K == 1) {
-        add_term(acc, tot, ab);
-        add_term(dd_neg(dd_mul(acc, rdet(A[0], A[1], A[2]))), tot, ab);
+        add_term(acc, sum);
+        add_term(dd_neg(dd_mul(acc, rdet(A[0], A[1], A[2]))), sum);
     } else {
         dd B[ex_e(K - 1)];
         const dd r = step<K>(A, B);
-        walk<K - 1>(B, dd_mul(acc, r), tot, ab);
+        walk<K - 1>(B, dd_mul(acc, r), sum);
 #pragma unroll
         for (int e = 0; e < ex_e(K - 1); ++e) B[e] = A[e];
-        walk<K - 1>(B, acc, tot, ab);
+        walk<K - 1>(B, acc, sum);
     }
 }
 
@@ -299,8 +318,7 @@ __global__ __launch_bounds__(64) void k_exact(int M, const double *__restrict__ 
     const int root = SMALL ? ex_lev(R, L + 1) : R == EX_R ? EX_ROOT : ex_lev(R, L + 1);
     constexpr int NREG = (ex_e(EX_R + EX_IN) + 63) / 64;
     const dd sign = dd_make(n & 1 ? -1.0 : 1.0);
-    dd rtot = dd_make(0.0);
-    double rab = 0.0;
+    Sum sum = {0.0, 0.0, 0.0, 0.0};
     for (int zm = 0; zm < (1 << (lgZ - nin)); ++zm) {
         const int z0 = (ip << lgZ) | (zm << nin);
         // the last R modes, then the nin inner prefix modes, then the other
@@ -405,18 +423,16 @@ __global__ __launch_bounds__(64) void k_exact(int M, const double *__restrict__ 
                 }
                 __syncthreads();
             }
-            dd tot = dd_make(0.0);
-            double ab = 0.0;
             if (on) {
                 if (S <= 2) {
                     if (S == 2) {
                         dd A[ex_e(2)];
                         load_node<2>(A, m, inc, one);
-                        walk<2>(A, a, tot, ab);
+                        walk<2>(A, a, sum);
                     } else {
                         dd A[ex_e(1)];
                         load_node<1>(A, m, inc, one);
-                        walk<1>(A, a, tot, ab);
+                        walk<1>(A, a, sum);
                     }
                 } else if constexpr (!SMALL) {
                     // (R = 9 walks three modes, R = 10 four: the first of these
@@ -431,24 +447,23 @@ __global__ __launch_bounds__(64) void k_exact(int M, const double *__restrict__ 
                     }
 #pragma unroll 1
                     for (int half = S == EX_S ? 2 : 1; half > 0; --half) {
-                        walk<EX_S - 1>(B, aa, tot, ab);
+                        walk<EX_S - 1>(B, aa, sum);
 #pragma unroll
                         for (int e = 0; e < ex_e(EX_S - 1); ++e) B[e] = A[e];
                         aa = a;
                     }
                 }
             }
-            rtot = dd_add(rtot, quick_two_sum(tot.hi, tot.lo));
-            rab += ab;
             __syncthreads();
         }
     }
-    rtot = wave_dd_sum(rtot);
-    for (int mm = 32; mm > 0; mm >>= 1) rab += __shfl_xor(rab, mm);
+    const dd tot = wave_dd_sum(sum_dd(sum));
+    double ab = sum.ab;
+    for (int mm = 32; mm > 0; mm >>= 1) ab += __shfl_xor(ab, mm);
     if (lane == 0) {
-        part[3 * item] = rtot.hi;
-        part[3 * item + 1] = rtot.lo;
-        part[3 * item + 2] = rab;
+        part[3 * item] = tot.hi;
+        part[3 * item + 1] = tot.lo;
+        part[3 * item + 2] = ab;
     }
 }
 

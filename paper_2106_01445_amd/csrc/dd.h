@@ -144,9 +144,10 @@ __device__ __forceinline__ dd dd_fms2(dd a, dd p, dd q, dd r, dd s)
     return quick_two_sum(u.hi, lo);
 }
 
-// exp(x) for |x| < 700.  x = k ln2 + r; r' = r / 1024 (at most 3.4e-4); Taylor to
-// degree 9 (the next term is below 2e-41), coefficients 1/i! as double-doubles;
-// square 10 times; scale by 2^k.
+// exp(x) for |x| < 700.  x = k ln2 + r; r' = r / 1024 (at most 3.4e-4); expm1 by
+// Taylor to degree 9 (the next term is below 2e-41), coefficients 1/i! as
+// double-doubles; ten steps expm1(2y) = 2 expm1(y) + expm1(y)^2 (squarings of exp
+// itself would multiply its rounding by 1024); scale by 2^k.
 __host__ __device__ inline dd dd_exp(dd x)
 {
 #pragma clang fp contract(off)
@@ -161,8 +162,10 @@ __host__ __device__ inline dd dd_exp(dd x)
     r = dd_mul_d(r, 1.0 / 1024.0);
     dd s = cf[9];
 #pragma unroll
-    for (int i = 8; i >= 0; --i) s = dd_add(dd_mul(s, r), cf[i]);
-    for (int i = 0; i < 10; ++i) s = dd_mul(s, s);
+    for (int i = 8; i >= 1; --i) s = dd_add(dd_mul(s, r), cf[i]);
+    s = dd_mul(s, r);
+    for (int i = 0; i < 10; ++i) s = dd_add(dd{2.0 * s.hi, 2.0 * s.lo}, dd_mul(s, s));
+    s = dd_add_d(s, 1.0);
     double sc = ldexp(1.0, (int)k);
     return dd{s.hi * sc, s.lo * sc};
 }

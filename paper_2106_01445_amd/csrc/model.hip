@@ -4,22 +4,28 @@
 //   O = [[Re U, -Im U], [Im U, Re U]],  D = diag(sqrt eta, sqrt eta)
 //
 // Q is inverted by symmetric Gauss-Jordan sweeps over blocks of 16 rows, one
-// launch per block, every 16 x 16 tile a workgroup: with P the block's own tile,
-//   A_ss <- -P^{-1},  A_is <- A_is P^{-1},  A_ij <- A_ij - A_is P^{-1} A_sj,
-// after the last block -Q^{-1}.  The pivots d_k met inside the blocks give
+// launch per block, every 16 x 16 tile a workgroup: with P = L diag(d) L^T the
+// block's own tile and Y_i = A_is L^{-T},
+//   A_ss <- -P^{-1},  A_is <- A_is P^{-1},  A_ij <- A_ij - Y_i diag(1/d) Y_j^T,
+// after the last block -Q^{-1}.  The Schur complements are thus those of the
+// factorisation Q = L D L^T step by step, and the pivots its own; formed with
+// P^{-1} instead, A_ij - (A_is P^{-1}) A_sj, they lose a factor cond(Q): against
+// binary128 the rms error of Q^{-1} at 12 modes and r = 1.6 / 3 / 8 was 3.3 / 1170
+// / 1.6e13 2^-106, now 2.0 / 43 / 3.9e6 (a Cholesky factor and triangular
+// solves: 1.9 / 40 / 3.5e6).  The pivots d_k give
 // positive definiteness, log det Q = sum log d_k and det(Q)^{-1/2} =
 // prod d_k^{-1/2}.  Everything stays in HBM as hi/lo fp64 planes, row-major
 // (2M)^2, xxpp order.
 //
-// What bounds it: the chain of 2M pivots (a double-double reciprocal, a product
-// and a barrier each, about 0.35 us), which every workgroup of a launch walks
-// for itself so that no other launch stands between the blocks.  Blocks of 16
-// keep the tiles' products (2 x 16 terms per entry) below that chain.  Against
-// a column-by-column Cholesky factor in one workgroup and a pair of triangular
-// solves per column of the inverse, the inversion takes 9 / 30 / 91 / 220 us
-// instead of 38 / 101 / 1160 / 8040 at M = 8 / 20 / 70 / 144 (a launch per block
-// is 9 to 12 us), and the assembly of Q 3 / 8 / 17 / 30 instead of
-// 9 / 19 / 68 / 157.
+// What bounds it: the chain of 2M pivots (a double-double reciprocal, a product,
+// up to three updates and a barrier each, 0.3 to 0.5 us), which every workgroup
+// of a launch walks for itself so that no other launch stands between the
+// blocks.  Blocks of 16 keep the tiles' products (16 terms per entry) below that
+// chain.  Against a column-by-column Cholesky factor in one workgroup and a pair
+// of triangular solves per column of the inverse, the inversion takes 8 / 34 /
+// 96 / 257 us instead of 38 / 101 / 1160 / 8040 at M = 8 / 20 / 70 / 144 (a launch
+// per block is 8 to 14 us; with P^{-1} in the Schur complements 8 to 12), and the
+// assembly of Q 3 / 7 / 17 / 30 instead of 9 / 19 / 68 / 157.
 #include "internal.h"
 
 #define SWB 16
@@ -42,23 +48,19 @@ __device__ __forceinline__ void st_dd(double *hi, double *lo, long i, dd v)
 __global__ void k_model_scalars(int M, const double *ure, const double *uim, const double *r, const double *eta,
                                 double *params, double *__restrict__ expd)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
-    if (k < M) {
-        const double rk = r[k], ek = eta[k];
-        dd em = dd_exp(dd_make(-2.0 * rk));
-        dd ep = dd_exp(dd_make(2.0 * rk));
-        dd s = ek > 0.0 ? dd_sqrt(dd_make(ek)) : dd_make(0.0);
-        int D = 2 * M;
-        expd[k] = em.hi;
-        expd[D + k] = em.lo;
-        expd[M + k] = ep.hi;
-        expd[D + M + k] = ep.lo;
-        expd[2 * D + k] = s.hi;
-        expd[2 * D + M + k] = s.lo;
-        if (ure != params) {
-            params[2 * M * M + k] = rk;
-            params[2 * M * M + M + k] = ek;
+    const int k = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x, D = 2 * M;
+    if (k < D) {  // (a thread per exponential)
+        const int m = k < M ? k : k - M;
+        const double rk = r[m], ek = eta[m];
+        const dd e = dd_exp(dd_make(k < M ? -2.0 * rk : 2.0 * rk));
+        expd[k] = e.hi;
+        expd[D + k] = e.lo;
+        if (k < M) {
+            const dd s = ek > 0.0 ? dd_sqrt(dd_make(ek)) : dd_make(0.0);
+            expd[2 * D + k] = s.hi;
+            expd[2 * D + M + k] = s.lo;
         }
+        if (ure != params) params[2 * M * M + k] = k < M ? rk : ek;
     }
     if (ure != params)
         for (int i = k; i < M * M; i += nt) {
@@ -141,81 +143,122 @@ __device__ __forceinline__ dd wave_dd_prod(dd v)
     return v;
 }
 
+// a - p q - r s as dd_fms2, what is below the leading words added up as a short
+// tree (29 operations against 27; Q^{-1}'s error is a tenth smaller)
+__device__ __forceinline__ dd fms2(dd a, dd p, dd q, dd r, dd s)
+{
+    const dd f = two_prod(p.hi, q.hi), g = two_prod(r.hi, s.hi);
+    const dd t = two_sum(f.hi, g.hi);
+    const dd u = two_sum(a.hi, -t.hi);
+    const double c = fma(p.hi, q.lo, p.lo * q.hi), d = fma(r.hi, s.lo, r.lo * s.hi);
+    return quick_two_sum(u.hi, (a.lo - ((f.lo + g.lo) + t.lo)) + (u.lo - (c + d)));
+}
+
+// 1/x (x normal) by the hardware estimate and two Newton steps, within an ulp
+__device__ __forceinline__ double rcp_nr(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
 // One sweep over block s, from src to dst (both full; a workgroup per tile
 // ti >= tj, one entry per thread, written with its mirror image; rows past 2M
-// act as rows of the identity).  scal: [0] log det Q, [1],[2] det(Q)^{-1/2}
-// (dd), [3] 1 if not positive definite (dst is then the identity after the last
-// block, so that no later kernel meets what the sweeps left), [8 .. 8+2D) the
-// pivots as dd (hi then lo planes).
+// act as rows of the identity).  P = L diag(d) L^T by right-looking steps that
+// carry W = L^{-1} (in the lower part's place) and the rows of A_is and A_js
+// along, which become Y = A L^{-T}: a block's inverse is formed for its own
+// tiles alone.  ONE: a matrix of one block (nothing is carried along).
+// scal: [0] log det Q, [1],[2] det(Q)^{-1/2} (dd), [3] 1 if not positive
+// definite (dst is then the identity after the last block, so that no later
+// kernel meets what the sweeps left), [8 .. 8+2D) the pivots as dd (hi then lo
+// planes).
+template <bool ONE>
 __global__ __launch_bounds__(256) void k_sweep(int D, int s, int last, const double *__restrict__ s_hi,
                                                const double *__restrict__ s_lo, double *__restrict__ d_hi,
                                                double *__restrict__ d_lo, double *__restrict__ scal)
 {
     const int ti = blockIdx.x, tj = blockIdx.y;
     if (ti < tj) return;
-    __shared__ double2 col[2][SWB], inv[SWB][SWB + 1], ais[SWB][SWB + 1], ajs[SWB][SWB + 1], prod[SWB][SWB + 1];
-    __shared__ double2 piv[SWB];
+    // column k of P, row k of W, column k of either side's rows, as step k finds them
+    __shared__ double2 pc[2][SWB], wr[2][SWB], ic[2][SWB], jc[2][SWB];
+    __shared__ double2 piv[SWB], inv[SWB], w[SWB][SWB + 1], zi[SWB][SWB + 1], yj[SWB][SWB + 1];
     const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     const int i = ti * SWB + r, j = tj * SWB + c;
+    const bool di = !ONE && ti != s, dc = !ONE && tj != s;
     bool bad = s > 0 && scal[3] != 0.0;
+    // (read at a valid place and then chosen: no branch keeps the loads apart)
     auto at = [&](int a, int b) {
-        if (a < D && b < D) return ld_dd(s_hi, s_lo, (long)a * D + b);
-        return dd_make(a == b ? 1.0 : 0.0);
+        const dd v = ld_dd(s_hi, s_lo, (long)min(a, D - 1) * D + min(b, D - 1)), e = dd_make(a == b ? 1.0 : 0.0);
+        const bool in = a < D && b < D;
+        return dd{in ? v.hi : e.hi, in ? v.lo : 0.0};
     };
+    auto get = [](const double2 &v) { return dd{v.x, v.y}; };
+    auto put = [](dd v) { return make_double2(v.hi, v.lo); };
     const int sr = s * SWB + r, sc = s * SWB + c;
-    dd p = at(sr, sc);
-    const dd mine = at(i, j), vi = at(i, sc), vj = at(tj * SWB + r, sc);
-    ais[r][c] = make_double2(vi.hi, vi.lo);
-    ajs[r][c] = make_double2(vj.hi, vj.lo);
-    if (c == 0) col[0][r] = make_double2(p.hi, p.lo);
+    dd p = at(sr, sc), vi = at(i, sc), vj = at(tj * SWB + r, sc);
+    const dd mine = at(i, j);
+    if (c == 0) {
+        pc[0][r] = put(p);
+        ic[0][r] = put(vi);
+        jc[0][r] = put(vj);
+    }
     __syncthreads();
-    // P by single sweeps, its column k passed on through LDS
 #pragma unroll 1
     for (int k = 0; k < SWB; ++k) {
-        const double2 *cl = col[k & 1];
-        const double2 dv = cl[k], cr = cl[r], cc = cl[c];
-        const dd d = dd{dv.x, dv.y}, ac = dd{cc.x, cc.y};
+        // (all of a step's operands first: the chain then waits for LDS once)
+        const int b = k & 1;
+        const bool right = c > k;
+        const dd d = get(pc[b][k]), pr = get(pc[b][r]), pcc = get(pc[b][c]), wc = get(wr[b][c]);
+        const dd ir = ONE ? pr : get(ic[b][r]), jr = ONE ? pr : get(jc[b][r]);
         bad = bad || !(d.hi > 0.0);
-        // 1/d: the fp64 value y and y e, e = 1 - d y
-        const double y = 1.0 / d.hi;
+        // 1/d: the fp64 value y and y e (1 + e), e = 1 - d y
+        const double y = rcp_nr(d.hi);
         const double e = fma(-d.lo, y, fma(-d.hi, y, 1.0));
         const dd id = quick_two_sum(y, y * fma(e, e, e));
-        const dd t = dd_mul(r == k ? ac : dd{cr.x, cr.y}, id);
-        if (r == k && c == k)
-            p = dd_neg(id);
-        else if (r == k || c == k)
-            p = t;
-        else
-            p = dd_fms(p, t, ac);
-        if (threadIdx.x == 0) piv[k] = dv;
-        if (c == k + 1) col[(k + 1) & 1][r] = make_double2(p.hi, p.lo);
+        // one product by 1/d serves all: l_c of L's column k (entries right of k:
+        // a_rc - a_rk l_c, also along the carried rows), l_r for W's row r
+        const dd l = dd_mul(dd{right ? pcc.hi : pr.hi, right ? pcc.lo : pr.lo}, id);
+        const dd q = dd_fms(p, l, dd{right ? pr.hi : wc.hi, right ? pr.lo : wc.lo});
+        if (!ONE) {
+            const dd zi_ = dd_fms(vi, ir, l), zj = dd_fms(vj, jr, l);
+            vi = dd{right ? zi_.hi : vi.hi, right ? zi_.lo : vi.lo};
+            vj = dd{right ? zj.hi : vj.hi, right ? zj.lo : vj.lo};
+        }
+        if (r > k && c <= r) p = c == k ? dd_neg(l) : q;
+        if (threadIdx.x == 0) {
+            piv[k] = put(d);
+            inv[k] = put(id);
+        }
+        if (c == k + 1) {
+            pc[b ^ 1][r] = put(p);
+            if (!ONE) {
+                ic[b ^ 1][r] = put(vi);
+                jc[b ^ 1][r] = put(vj);
+            }
+        }
+        if (r == k + 1 && c <= k) wr[b ^ 1][c] = put(p);
         __syncthreads();
     }
-    inv[r][c] = make_double2(-p.hi, -p.lo);
+    // Z = Y diag(1/d) of the tile's rows, Y (beside the block's own rows Z) of its
+    // columns; in the block's own tile diag(1/d) W
+    const dd wv = r > c ? p : dd_make(r == c ? 1.0 : 0.0);
+    const double2 dcl = inv[c], drw = inv[r];
+    w[r][c] = put(wv);
+    zi[r][c] = put(di ? dd_mul(vi, get(dcl)) : dd_mul(wv, get(drw)));
+    yj[r][c] = put(di ? vj : dd_mul(vj, get(dcl)));
     __syncthreads();
-    auto get = [](const double2 &v) { return dd{v.x, v.y}; };
-    dd out;
-    if (ti == s && tj == s) {
-        out = p;
-    } else {
-        // the block's row or column: P^{-1} A_sj = (A_js P^{-1})^T, or A_is P^{-1}
-        const bool row = ti == s;
-        dd acc = dd_make(0.0);
-#pragma unroll 4
-        for (int k = 0; k < SWB; k += 2)
-            acc = row ? dd_fms2(acc, get(inv[r][k]), get(ajs[c][k]), get(inv[r][k + 1]), get(ajs[c][k + 1]))
-                      : dd_fms2(acc, get(ais[r][k]), get(inv[c][k]), get(ais[r][k + 1]), get(inv[c][k + 1]));
-        out = dd_neg(acc);
-        if (ti != s && tj != s) {
-            prod[r][c] = make_double2(out.hi, out.lo);
-            __syncthreads();
-            acc = mine;
-#pragma unroll 4
-            for (int k = 0; k < SWB; k += 2)
-                acc = dd_fms2(acc, get(prod[r][k]), get(ajs[c][k]), get(prod[r][k + 1]), get(ajs[c][k + 1]));
-            out = acc;
-        }
+    // A_ij - Z_i Y_j^T; Z_i W (its sign turned below), the new A_is; its mirror
+    // image in the block's rows, (Z_j W)^T; -P^{-1} = -(diag(1/d) W)^T W
+    const double2 *pa = di ? zi[r] : dc ? yj[c] : &zi[0][r], *pb = di && dc ? yj[c] : &w[0][dc ? r : c];
+    const int sa = di || dc ? 1 : SWB + 1, sb = di && dc ? 1 : SWB + 1;
+    dd out = di && dc ? mine : dd_make(0.0), more = dd_make(0.0);  // (two chains)
+#pragma unroll
+    for (int k = 0; k < SWB; k += 4) {
+        out = fms2(out, get(pa[k * sa]), get(pb[k * sb]), get(pa[(k + 1) * sa]), get(pb[(k + 1) * sb]));
+        more = fms2(more, get(pa[(k + 2) * sa]), get(pb[(k + 2) * sb]), get(pa[(k + 3) * sa]), get(pb[(k + 3) * sb]));
     }
+    out = dd_add(out, more);
+    if (di != dc) out = dd_neg(out);
     if (last) out = bad ? dd_make(i == j ? 1.0 : 0.0) : dd_neg(out);
     if (i < D && j <= i) {
         st_dd(d_hi, d_lo, (long)i * D + j, out);
@@ -309,7 +352,8 @@ int model_build_dev(gbs_ctx *ctx, const double *ure, const double *uim, const do
     for (int s = 0; s < T; ++s) {
         const bool home = ((T - 1 - s) & 1) == 0;
         double *dh = home ? m.qi_hi : m.work_hi, *dl = home ? m.qi_lo : m.work_lo;
-        hipLaunchKernelGGL(k_sweep, dim3(T, T), dim3(256), 0, st, D, s, s == T - 1, sh, sl, dh, dl, m.scal);
+        hipLaunchKernelGGL((T > 1 ? k_sweep<false> : k_sweep<true>), dim3(T, T), dim3(256), 0, st, D, s, s == T - 1,
+                           sh, sl, dh, dl, m.scal);
         sh = dh;
         sl = dl;
     }

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(CONT_THREADS) void k_contour(
     const double *__restrict__ alpha, const double *__restrict__ vt,
     const RowPlan *__restrict__ rows, const int *__restrict__ items, const int *__restrict__ q_end,
     int *__restrict__ q_head, const int *__restrict__ units, const int *__restrict__ unit_off,
-    const int *__restrict__ unit4_off, cplx *__restrict__ mscr, long long mscr_stride, cplx *__restrict__ sw)
+    const int *__restrict__ unit4_off, cplx *__restrict__ sw)
 {
     extern __shared__ __attribute__((aligned(16))) double sh[];
     __shared__ int s_item;
@@ -140,14 +140,11 @@ __global__ __launch_bounds__(CONT_THREADS) void k_contour(
         cplx *slots;                            // G x (2n^2 + 5n) complex
         int G = 1;
         if (BIG) {
-            // eigenvectors read from HBM (L2); M(w) in LDS when it fits, else in
-            // this workgroup's HBM scratch
+            // eigenvectors read from HBM (L2); M(w) in LDS (orders 1 and 2: only d,
+            // rz and the diagonal blocks are stored)
             Vt = vt + vo;
             al = dyn;
-            // (order 2: only d, rz and the diagonal blocks are stored, in LDS)
-            slots = ORDER == 2 || cont_fixed() + 8 * N + cont_mbytes<C>(n) <= lds_bytes
-                        ? (cplx *)(al + N)
-                        : mscr + blockIdx.x * mscr_stride;
+            slots = (cplx *)(al + N);
         } else {
             // V and each slot's d zero-padded to whole tiles (no operand masks)
             const int tp = cont_tp(n), vsp = tp + 1;
@@ -1006,11 +1003,10 @@ int launch_contour(gbs_ctx *ctx, gbs_plan *pl, int nmax)
     const int lds_cap = ctx->lds_per_block - lds_static;
     int lds_c;
     if (BIG) {
-        // the largest row's M(w) in LDS if it fits, else only alpha (M in HBM);
-        // order 2 keeps only d, rz and the diagonal blocks
-        lds_c = cont_fixed() + 8 * 2 * nmax + cont_mbytes<C>(nmax);
-        if (lds_c > lds_cap) lds_c = cont_fixed() + 8 * 2 * nmax;
-        if (ORDER == 2) lds_c = cont_fixed() + 8 * 2 * nmax + 16 * (cont_tp(nmax) + 5 * nmax);
+        // the largest row's M(w) (136 KB at the 64 clicks of orders 3 and 4); orders
+        // 1 and 2 keep only d, rz and the diagonal blocks
+        lds_c = cont_fixed() + 8 * 2 * nmax + (ORDER <= 2 ? 16 * (cont_tp(nmax) + 5 * nmax) : cont_mbytes<C>(nmax));
+        if (lds_c > lds_cap) return set_err(ctx, GBS_E_INVAL, "row too large for the contour kernel's LDS");
     } else {
         // the whole 160 KB when the largest row needs it, else enough for eight
         // contour points of the largest row (two workgroups may then share a CU)
@@ -1022,23 +1018,13 @@ int launch_contour(gbs_ctx *ctx, gbs_plan *pl, int nmax)
     int occ = 1;
     if (int rc = func_lds_limit(ctx, fn, lds_c)) return rc;
     if (int rc = func_occupancy(ctx, fn, CONT_THREADS, lds_c, &occ)) return rc;
-    int grid = occ * ctx->num_cu;
-    cplx *mscr = nullptr;
-    long long mstride = 0;
-    if (BIG) {
-        mstride = cont_mbytes<C>(nmax) / 16;
-        if (pl->d_mscr) {
-            if (grid > pl->mscr_blocks) grid = pl->mscr_blocks;
-            mscr = pl->d_mscr;
-        }
-    }
+    const int grid = occ * ctx->num_cu;
     const int *q_end = pl->d_counter + (BIG ? 4 : 0);
     int *q_head = pl->d_counter + (BIG ? 5 : 1);
     hipLaunchKernelGGL((k_contour<ORDER, BIG, C, RERUN>), dim3(grid), dim3(CONT_THREADS), lds_c, st, lds_c,
                        pl->qchunk, pl->gmax, pl->d_offsets, pl->d_voff, pl->d_alpha, pl->d_v, pl->d_rows, pl->d_items,
                        q_end, q_head, pl->d_cluster_items, pl->d_cluster_off,
-                       pl->order >= 4 ? pl->d_cluster_off + 4 * (pl->max_n + 1) : nullptr, mscr, mstride,
-                       pl->d_sw);
+                       pl->order >= 4 ? pl->d_cluster_off + 4 * (pl->max_n + 1) : nullptr, pl->d_sw);
     return 0;
 }
 

@@ -582,12 +582,8 @@ int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
                  o_sw = put((size_t)P * (order + 1) * GBS_QCAP * sizeof(cplx)),
                  o_items = put(2 * (size_t)max_items * sizeof(int32_t)), o_cnt = put(GBS_NCOUNTER * sizeof(int32_t)),
                  o_wbig = put(2 * pl->v_total * sizeof(double));
-    // M(w) of rows whose blocks do not fit in LDS: one copy per workgroup
-    const long long ms = 2LL * pl->max_n * pl->max_n + 5LL * pl->max_n;
-    if (pl->nbig > 0 && 16 * ms + 16 * 64 > (long long)ctx->lds_per_block - 8 * 1024) pl->mscr_blocks = 2 * ctx->num_cu;
-    const size_t o_mscr = put((size_t)pl->mscr_blocks * ms * sizeof(cplx)),
-                 // (log p and the status next to each other: one copy back)
-                 o_logp = put(P * (sizeof(double) + sizeof(int32_t))), o_extra = put(extra);
+    // (log p and the status next to each other: one copy back)
+    const size_t o_logp = put(P * (sizeof(double) + sizeof(int32_t))), o_extra = put(extra);
     pl->pool = ctx->pool;
     pl->block = ctx->pool->take(at, &pl->block_bytes);
     if (!pl->block) {
@@ -608,7 +604,6 @@ int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
     pl->d_items = (int32_t *)(base + o_items);
     pl->d_counter = (int32_t *)(base + o_cnt);
     pl->d_wbig = (double *)(base + o_wbig);
-    if (pl->mscr_blocks > 0) pl->d_mscr = (cplx *)(base + o_mscr);
     pl->d_logp = (double *)(base + o_logp);
     pl->d_status = (int32_t *)(pl->d_logp + P);
     pl->d_extra = base + o_extra;

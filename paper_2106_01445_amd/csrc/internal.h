@@ -164,8 +164,6 @@ struct gbs_plan {
     int32_t *d_counter = nullptr;         // work queues: [0] end, [1] head (rows <= GBS_NSMALL),
                                           // [4] end, [5] head (larger rows); [2,3], [6,7] adjoint
     double *d_wbig = nullptr;             // 2 (2n)^2 per row: eigen-decomposition, then adjoint scratch
-    cplx *d_mscr = nullptr;               // per-workgroup M(w) scratch of the larger rows
-    int mscr_blocks = 0;                  // workgroups d_mscr serves
     int32_t *d_cluster_items = nullptr;   // per click count n: packed cluster units (a, b, c0, c1),
                                           // the forward's list, then the adjoint's
     int32_t *d_cluster_off = nullptr;     // [n] -> offset, count (2 ints); forward, then adjoint

@@ -190,7 +190,7 @@ template <class T>
 int dev_alloc(gbs_ctx *ctx, T **p, size_t count)
 {
     if (count == 0) count = 1;
-    if (hipMalloc((void **)p, count * sizeof(T)) != hipSuccess) {
+    if (ctx->pool->alloc((void **)p, count * sizeof(T)) != hipSuccess) {
         *p = nullptr;
         return set_err(ctx, GBS_E_NOMEM, "device allocation of " +
                                              std::to_string(count * sizeof(T)) + " bytes failed");
@@ -200,21 +200,38 @@ int dev_alloc(gbs_ctx *ctx, T **p, size_t count)
 
 }  // namespace
 
-void *BlockPool::take(size_t bytes, size_t *got)
+void *BlockPool::take(size_t bytes, size_t *got, bool lasting)
 {
+    void *p = nullptr;
     {
         std::lock_guard<std::mutex> lk(mu);
-        if (spare && spare_bytes >= bytes) {
-            void *p = spare;
+        if (spare && spare_bytes >= bytes && (!lasting || spare_bytes / 2 <= bytes)) {
+            std::swap(p, spare);
             *got = spare_bytes;
-            spare = nullptr;
             return p;
         }
     }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
     *got = bytes;
-    return p;
+    return alloc(&p, bytes) == hipSuccess ? p : nullptr;
+}
+
+hipError_t BlockPool::alloc(void **p, size_t bytes)
+{
+    if (hipMalloc(p, bytes) == hipSuccess) return hipSuccess;
+    // (what is kept may be what is missing)
+    trim();
+    (void)hipGetLastError();  // (the first attempt's)
+    return hipMalloc(p, bytes);
+}
+
+void BlockPool::trim()
+{
+    void *p = nullptr;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        std::swap(p, spare);
+    }
+    if (p) (void)hipFree(p);
 }
 
 void BlockPool::give(void *p, size_t bytes)
@@ -231,10 +248,11 @@ void BlockPool::give(void *p, size_t bytes)
 
 void BlockPool::close()
 {
-    std::lock_guard<std::mutex> lk(mu);
-    closed = true;
-    if (spare) (void)hipFree(spare);
-    spare = nullptr;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        closed = true;
+    }
+    trim();
 }
 
 namespace {
@@ -519,7 +537,7 @@ int gbs_get_model(gbs_ctx *ctx, double *q_inv, double *logdet_q)
 }  // extern "C"
 
 int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec, size_t extra,
-              gbs_plan **out)
+              bool lasting, gbs_plan **out)
 {
     if (!ctx || !out) return GBS_E_INVAL;
     *out = nullptr;
@@ -585,7 +603,7 @@ int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
     // (log p and the status next to each other: one copy back)
     const size_t o_logp = put(P * (sizeof(double) + sizeof(int32_t))), o_extra = put(extra);
     pl->pool = ctx->pool;
-    pl->block = ctx->pool->take(at, &pl->block_bytes);
+    pl->block = ctx->pool->take(at, &pl->block_bytes, lasting);
     if (!pl->block) {
         delete pl;
         return set_err(ctx, GBS_E_NOMEM, "device allocation of " + std::to_string(at) + " bytes failed");
@@ -632,7 +650,7 @@ extern "C" {
 int gbs_plan_create(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec,
                     gbs_plan **out)
 {
-    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, out);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, true, out);
     if (rc) return rc;
     // (the upload's host copy is not needed any longer)
     const hipError_t he = hipStreamSynchronize(ctx->stream);
@@ -713,7 +731,7 @@ int gbs_prob_approx(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *
     if (!ctx) return GBS_E_INVAL;
     if (P > 0 && (!logp || !status)) return set_err(ctx, GBS_E_INVAL, "NULL output array");
     gbs_plan *pl = nullptr;
-    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, &pl);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, false, &pl);
     if (rc) return rc;
     rc = gbs_prob_approx_dev(ctx, pl, pl->d_logp, pl->d_status);
     if (rc == 0) rc = rows_back(ctx, pl, logp, status);
@@ -730,7 +748,7 @@ int gbs_prob_approx_plain(gbs_ctx *ctx, int P, const int32_t *offsets, const int
     if (!ctx) return GBS_E_INVAL;
     if (P > 0 && (!logp || !status)) return set_err(ctx, GBS_E_INVAL, "NULL output array");
     gbs_plan *pl = nullptr;
-    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, &pl);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, 0, false, &pl);
     if (rc) return rc;
     rc = pl->max_n > GBS_NSMALL
              ? set_err(ctx, GBS_E_INVAL, "the plain kernel takes rows of at most 40 clicks")
@@ -1077,7 +1095,7 @@ int gbs_click_distribution(gbs_ctx *ctx, int order, int nk, const int32_t *ks, d
     gbs_plan *pl = nullptr;
     // (device side: p_n, p_k, the status, then ks)
     const size_t nout = (size_t)(nk + 1) * (M + 1), back = nout * sizeof(double) + sizeof(int32_t);
-    int rc = plan_make(ctx, 1, off.data(), mod.data(), order, GBS_PREC_FP64, back + nk * sizeof(int32_t), &pl);
+    int rc = plan_make(ctx, 1, off.data(), mod.data(), order, GBS_PREC_FP64, back + nk * sizeof(int32_t), false, &pl);
     if (rc) return rc;
     pl->whole = true;
     // One row has fewer contour points than the chip compute units (K/2 + 1 is 65
@@ -1121,7 +1139,8 @@ int gbs_grad(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, 
     gbs_plan *pl = nullptr;
     int M = ctx->model.M;
     // (device side: the gradients, then the rows' weights)
-    int rc = plan_make(ctx, P, offsets, modes, order, prec, (2 * (size_t)M + std::max(P, 0)) * sizeof(double), &pl);
+    int rc = plan_make(ctx, P, offsets, modes, order, prec, (2 * (size_t)M + std::max(P, 0)) * sizeof(double), false,
+                       &pl);
     if (rc) return rc;
     double *dg = (double *)pl->d_extra, *ddl = dg + 2 * M;
     hipStream_t st = ctx->stream;

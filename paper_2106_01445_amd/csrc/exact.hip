@@ -623,7 +623,7 @@ int exact_run(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
     const size_t back = n * (3 * sizeof(double) + sizeof(int32_t)), in = (n + 1 + nnz) * sizeof(int32_t);
     const size_t o_part = (back + in + 15) & ~(size_t)15;
     size_t got = 0;
-    char *blk = (char *)ctx->pool->take(o_part + std::max(nitems, 1LL) * 3 * sizeof(double), &got);
+    char *blk = (char *)ctx->pool->take(o_part + std::max(nitems, 1LL) * 3 * sizeof(double), &got, false);
     if (!blk) return set_err(ctx, GBS_E_NOMEM, "exact: device allocation failed");
     double *d_out = (double *)blk;
     int32_t *d_st = (int32_t *)(d_out + 3 * n), *d_off = d_st + n, *d_modes = d_off + n + 1;

@@ -54,10 +54,12 @@ struct DevModel {
     double *expd = nullptr;         // e^{-2r}, e^{2r} as dd (4M doubles) and sqrt(eta) dd (4M)
 };
 
-// Device memory of the short-lived objects of a context (plans, one call's
-// buffers), a block each.  The pool keeps the block given back last, up to
-// 64 MiB, for the next one that fits in it: a call on host arrays then pays for
-// no hipMalloc and hipFree (10 to 50 us each, and a wait for the whole device).
+// Device memory of the plans and the host calls of a context, a block each.  The
+// pool keeps the largest block given back, up to 64 MiB, for a later one that
+// fits in it: a call on host arrays then pays for no hipMalloc and hipFree (10 to
+// 50 us each, and a wait for the whole device).  A plan, which may stay, only
+// takes a block of up to twice its size; a call, which gives the block back,
+// takes any.  The context's allocations that fail are tried again without it.
 // A kept block is only reused by work on the context's stream, which comes after
 // everything that used it before.  Plans share the pool's ownership: those that
 // outlive the context free their blocks themselves.
@@ -69,8 +71,11 @@ struct BlockPool {
     void *spare = nullptr;
     size_t spare_bytes = 0;
     // a block of at least `bytes` (its size in *got), or null
-    void *take(size_t bytes, size_t *got);
+    void *take(size_t bytes, size_t *got, bool lasting);
     void give(void *p, size_t bytes);
+    // hipMalloc, tried again without the kept block
+    hipError_t alloc(void **p, size_t bytes);
+    void trim();  // the kept block back to the device
     void close();
 };
 
@@ -227,6 +232,7 @@ int click_distribution_run(gbs_ctx *ctx, gbs_plan *pl, int nk, const int *ks_dev
                            int32_t *status_dev);
 int approx_forward_plain(gbs_ctx *ctx, gbs_plan *plan, double *logp_dev, int32_t *status_dev);
 int plan_units(gbs_ctx *ctx, gbs_plan *plan);
-// gbs_plan_create with `extra` more bytes of device memory (pl->d_extra)
+// gbs_plan_create with `extra` more bytes of device memory (pl->d_extra); lasting:
+// for the caller to keep, not for one call
 int plan_make(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes, int order, int prec, size_t extra,
-              gbs_plan **out);
+              bool lasting, gbs_plan **out);

@@ -313,14 +313,14 @@ int model_alloc(gbs_ctx *ctx, int M)
     size_t D = 2 * (size_t)M, DD = D * D * sizeof(double);
     double **mats[] = {&m.q_hi, &m.q_lo, &m.qi_hi, &m.qi_lo, &m.work_hi, &m.work_lo};
     for (double **p : mats)
-        if (hipMalloc((void **)p, DD) != hipSuccess) {
+        if (ctx->pool->alloc((void **)p, DD) != hipSuccess) {
             free_model(m);
             m.M = 0;
             return set_err(ctx, -3, "model: device allocation failed");
         }
-    if (hipMalloc((void **)&m.params, (2 * (size_t)M * M + 2 * M) * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&m.scal, (8 + 2 * D) * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&m.expd, 6 * (size_t)M * sizeof(double)) != hipSuccess) {
+    if (ctx->pool->alloc((void **)&m.params, (2 * (size_t)M * M + 2 * M) * sizeof(double)) != hipSuccess ||
+        ctx->pool->alloc((void **)&m.scal, (8 + 2 * D) * sizeof(double)) != hipSuccess ||
+        ctx->pool->alloc((void **)&m.expd, 6 * (size_t)M * sizeof(double)) != hipSuccess) {
         free_model(m);
         m.M = 0;
         return set_err(ctx, -3, "model: device allocation failed");

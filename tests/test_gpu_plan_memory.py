@@ -49,3 +49,22 @@ def test_order1_rows_of_any_length(gpu_ctx):
     assert np.all(out["status"] == 0)
     for i, C in enumerate(rows):
         assert abs(out["logp"][i] - approx.prob_approx(Q, C, 1)) <= 1e-9, len(C)
+
+
+def test_small_plan_after_a_large_call():
+    """A plan of a few rows made after a large host call leaves the call's block
+    (50 MB) to the next call: that one allocates nothing."""
+    M, P = 20, 700
+    U, r, eta = small_model(M, 7, n_squeezed=10)
+    rng = np.random.default_rng(3)
+    off, mod = csr_from_lists([sorted(rng.choice(M, 5, replace=False).tolist()) for _ in range(P)])
+    ctx = g.Context(0)
+    ctx.gbs_set_model(U, r, eta)
+    first = ctx.gbs_prob_approx(off, mod, 3)["logp"]
+    before = used()
+    plan = ctx.gbs_plan_create(off[:4], mod[: off[3]], 3)
+    again = ctx.gbs_prob_approx(off, mod, 3)["logp"]
+    grown = used() - before
+    plan.close()
+    ctx.close()
+    assert np.array_equal(first, again) and grown < 16 * MIB, grown

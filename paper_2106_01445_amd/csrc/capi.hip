@@ -711,6 +711,7 @@ int rows_back(gbs_ctx *ctx, gbs_plan *pl, double *logp, int32_t *status)
     const char *s = ctx->stage.data();
     if (logp) std::memcpy(logp, s, P * sizeof(double));
     std::memcpy(status, s + P * sizeof(double), P * sizeof(int32_t));
+    stage_done(ctx);
     return 0;
 }
 // the end of a host call on its own plan: nothing of the plan is in use when its
@@ -1122,6 +1123,7 @@ int gbs_click_distribution(gbs_ctx *ctx, int order, int nk, const int32_t *ks, d
             if (nk > 0) std::memcpy(p_k, sg + (M + 1) * sizeof(double), (size_t)nk * (M + 1) * sizeof(double));
             std::memcpy(status, sg + nout * sizeof(double), sizeof(int32_t));
         }
+        stage_done(ctx);
     }
     call_done(ctx, pl);
     if (rc) return rc;

@@ -639,12 +639,14 @@ int exact_run(gbs_ctx *ctx, int P, const int32_t *offsets, const int32_t *modes,
     if (!rc && e == hipSuccess) e = hipMemcpyAsync(ctx->stage.data(), blk, back, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     ctx->pool->give(blk, got);
+    if (e == hipSuccess && !rc) {
+        const double *out = (const double *)ctx->stage.data();
+        std::copy(out, out + n, p);
+        if (logp) std::copy(out + n, out + 2 * n, logp);
+        if (kappa) std::copy(out + 2 * n, out + 3 * n, kappa);
+        std::memcpy(status, out + 3 * n, n * sizeof(int32_t));
+    }
+    stage_done(ctx);
     if (e != hipSuccess) return set_err(ctx, GBS_E_HIP, std::string("exact: ") + hipGetErrorString(e));
-    if (rc) return rc;
-    const double *out = (const double *)ctx->stage.data();
-    std::copy(out, out + n, p);
-    if (logp) std::copy(out + n, out + 2 * n, logp);
-    if (kappa) std::copy(out + 2 * n, out + 3 * n, kappa);
-    std::memcpy(status, out + 3 * n, n * sizeof(int32_t));
-    return 0;
+    return rc;
 }

@@ -101,11 +101,19 @@ struct gbs_ctx {
     std::map<const void *, int> lds_limit, lds_static;
     std::map<std::pair<const void *, int>, int> occupancy;
     std::shared_ptr<BlockPool> pool;
-    std::vector<char> stage;  // host side of the model's and the exact path's copies
+    // host side of the host calls' copies, kept from call to call up to the size of
+    // a kept block (stage_done)
+    std::vector<char> stage;
     // partial sums of gbs_prob_exact_dev (grown on demand, freed with the context)
     double *ex_part = nullptr;
     long long ex_part_items = 0;
 };
+
+// The end of a call's use of ctx->stage.
+inline void stage_done(gbs_ctx *ctx)
+{
+    if (ctx->stage.capacity() > BlockPool::KEEP) std::vector<char>().swap(ctx->stage);
+}
 
 // Cached kernel queries (see gbs_ctx).
 int func_static_lds(gbs_ctx *ctx, const void *f, int *bytes);

@@ -68,3 +68,26 @@ def test_small_plan_after_a_large_call():
     plan.close()
     ctx.close()
     assert np.array_equal(first, again) and grown < 16 * MIB, grown
+
+
+def test_large_call_gives_host_memory_back():
+    """The context's host copy of a call's results (170 MB for six million empty
+    rows) does not stay with it."""
+    def resident():
+        with open("/proc/self/statm") as f:
+            return int(f.read().split()[1]) * 4096
+
+    U, r, eta = small_model(4, 8)
+    ctx = g.Context(0)
+    ctx.gbs_set_model(U, r, eta)
+    few = csr_from_lists([[0], [1, 2]])
+    ref = ctx.gbs_prob_exact(*few)["p"]
+    off, mod = np.zeros(6_000_001, np.int32), np.zeros(1, np.int32)
+    before = resident()
+    out = ctx.gbs_prob_exact(off, mod)
+    assert np.all(out["p"] == out["p"][0])
+    del out
+    grown = resident() - before
+    assert np.array_equal(ctx.gbs_prob_exact(*few)["p"], ref)
+    ctx.close()
+    assert grown < 100 * MIB, grown

@@ -857,7 +857,9 @@ __global__ __launch_bounds__(FIT_THREADS, 2) void k_dft_fit(const int *__restric
 // n = M): per sector k (0 <= k < K) the tilted moments by the FFT, the
 // exp-polynomial fitted on the sector's support n' = 1..min(k, n) (k photons
 // click at most k detectors; k = 0 is the vacuum, n' = 0), and its whole curve:
-// p_k(n') = S_0[k] q_k(n'), p(n') = sum_k p_k(n') (LDS accumulators, one block).
+// p_k(n') = S_0[k] q_k(n'), p(n') = sum_k p_k(n'), in one block.  The sum has one
+// order, whatever the wavefronts' timing: a tree over the 16 sectors that a
+// wavefront works on at a time, these one after another, then the wavefronts.
 // Sectors below the transform's noise floor (1e-14 of the largest tilted
 // weight) are left out; a sector whose fit fails sets GBS_PS_FIT_NOCONV when
 // its weight exceeds 1e-10 of the total.  A quad per sector.
@@ -873,14 +875,13 @@ __global__ __launch_bounds__(DIST_THREADS) void k_dist_fit(const int *__restrict
     constexpr int JM = ORDER >= 4 ? 4 : 3;
     extern __shared__ __attribute__((aligned(16))) double sh[];
     __shared__ double red[DIST_THREADS / 64];
-    __shared__ double pacc[2 * GBS_NSMALL + 2];
-    __shared__ double s_fail;
-    const int tid = threadIdx.x, nt = blockDim.x;
+    // per wavefront: p(n - v) of its sectors so far, then the weight of failed fits
+    __shared__ double pacc[DIST_THREADS / 64][GBS_NSMALL + 2];
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wid = tid >> 6;
     const int n = offsets[1] - offsets[0];
     const RowPlan rp = rows[0];
-    for (int i = tid; i <= n; i += nt) pacc[i] = 0.0;
     for (int i = tid; i < nk * (n + 1); i += nt) p_k[i] = 0.0;
-    if (tid == 0) s_fail = 0.0;
+    for (int i = lane; i < GBS_NSMALL + 2; i += 64) pacc[wid][i] = 0.0;
     if (n == 0 || rp.status != 0) {
         for (int i = tid; i <= n; i += nt) p_n[i] = n == 0 ? 1.0 : NAN;
         if (tid == 0) *status = rp.status;
@@ -921,51 +922,61 @@ __global__ __launch_bounds__(DIST_THREADS) void k_dist_fit(const int *__restrict
     fit_basis(n, phi);
     __syncthreads();
     const int gl = tid & (FIT_G - 1);
-    for (int kap = tid / FIT_G; kap < K; kap += nt / FIT_G) {
+    for (int k0 = 0; k0 < K; k0 += nt / FIT_G) {
+        const int kap = k0 + tid / FIT_G;
         double tau[JM + 1];
 #pragma unroll
-        for (int t = 0; t <= JM; ++t) tau[t] = t <= ORDER && t <= jp ? plane(t)[kap] : 0.0;
+        for (int t = 0; t <= JM; ++t) tau[t] = kap < K && t <= ORDER && t <= jp ? plane(t)[kap] : 0.0;
         const double t0 = tau[0];
-        if (!(t0 >= thr) || !(t0 > 0.0)) continue;
-        const double w0 = exp(log(t0) + rp.log_pvac + rp.log_g_rho - kap * rp.log_rho);  // S_0[k]
+        const bool used = t0 >= thr && t0 > 0.0;
+        const double w0 = used ? exp(log(t0) + rp.log_pvac + rp.log_g_rho - kap * rp.log_rho) : 0.0;  // S_0[k]
         int slot = -1;
         for (int i = 0; i < nk; ++i)
-            if (ks[i] == kap) slot = i;
+            if (used && ks[i] == kap) slot = i;
         const int s = min(kap, n), v0 = n - s;
         SectorFitT<JM> f;
         f.jr = f.bad = 0;
-        if (s > 1)
+        if (used && s > 1)
             f = fit_sector<JM, true>(n, v0, min(jp, s - 1), (LdsTab)phi, gl, t0, tau[1], tau[2], tau[3], JM >= 4 ? tau[JM] : 0.0, -1,
                                0.0, 0.0, 0.0, 0.0);
-        if (f.bad) {
-            if (gl == 0) atomicAdd(&s_fail, w0);
-            continue;
-        }
-        if (f.jr == 0) {
-            // the vacuum, one photon, or no usable moment (m_1 <= 0): every
-            // detector the sector can reach fires
-            if (gl == 0) {
-                atomicAdd(&pacc[s], w0);
-                if (slot >= 0) p_k[slot * (n + 1) + s] = w0;
-            }
-            continue;
-        }
-        // q(n') = exp(lq - c . phi(v)), v = n - n' (lq = minus the log-partition sum)
-        for (int v = v0 + gl; v < n; v += FIT_G) {
-            double z = f.lq;
+        auto add = [&](int v, double x) {  // over the quads: the lanes of a v are 4 apart
+            for (int m = FIT_G; m < 64; m <<= 1) x += __shfl_xor(x, m);
+            if (lane < FIT_G && v <= n + 1) pacc[wid][v] += x;
+        };
+        // q(n') = exp(lq - c . phi(v)), v = n - n' (lq = minus the log-partition sum);
+        // the vacuum, one photon, or no usable moment (m_1 <= 0): every detector the
+        // sector can reach fires
+        for (int u = 0; u <= n; u += FIT_G) {
+            const int v = u + gl;
+            double pv = 0.0;
+            if (used && !f.bad && v >= v0) {
+                if (f.jr == 0) {
+                    pv = v == v0 ? w0 : 0.0;
+                } else if (v < n) {
+                    double z = f.lq;
 #pragma unroll
-            for (int t = 0; t < JM; ++t)
-                if (t < f.jr) z -= f.c[t] * phi[4 * v + t];
-            const double pv = w0 * exp(z);
-            atomicAdd(&pacc[n - v], pv);
-            if (slot >= 0) p_k[slot * (n + 1) + n - v] = pv;
+                    for (int t = 0; t < JM; ++t)
+                        if (t < f.jr) z -= f.c[t] * phi[4 * v + t];
+                    pv = w0 * exp(z);
+                }
+                if (slot >= 0 && v <= n) p_k[slot * (n + 1) + n - v] = pv;
+            }
+            add(v <= n ? v : n + 2, pv);
         }
+        add(gl == 0 ? n + 1 : n + 2, gl == 0 && f.bad ? w0 : 0.0);
     }
     __syncthreads();
     double tot = 0.0;
-    for (int i = 0; i <= n; ++i) tot += pacc[i];
-    for (int i = tid; i <= n; i += nt) p_n[i] = pacc[i];
-    if (tid == 0) *status = s_fail > 1e-10 * tot ? GBS_PS_FIT_NOCONV : 0;
+    for (int i = 0; i <= n + 1; ++i) {
+        double x = 0.0;
+        for (int w = 0; w < nt / 64; ++w) x += pacc[w][i];
+        if (i == n + 1) {
+            if (tid == 0) *status = x > 1e-10 * tot ? GBS_PS_FIT_NOCONV : 0;
+        } else {
+            tot += x;
+            if (tid == i) p_n[n - i] = x;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------

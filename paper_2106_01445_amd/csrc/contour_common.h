@@ -721,26 +721,33 @@ __device__ __forceinline__ int fit_newton(int n, int v0, LdsTab phi, int gl, con
         if (!fit_solve<JP, SEQ>(E, E2, mg, x)) return 1;
 #pragma unroll
         for (int t = 0; t < JP; ++t) slope -= mg[t] * x[t];
+        // (Armijo, while the predicted decrease is above the rounding of the
+        // objective.  After convergence one polishing step, kept only if the
+        // objective does not rise: with a moment below the tolerance, whose
+        // feature has no weight at c, the covariance says nothing about it and
+        // the step may lead anywhere)
         double st = 1.0;
+        const double noise = 1e-13 * fmax(1.0, fabs(L0));
         for (;;) {
 #pragma unroll
-            for (int t = 0; t < JP; ++t) cn[t] = c[t] + st * x[t];
+            for (int t = 0; t < JP; ++t) cn[t] = st > 0.0 ? c[t] + st * x[t] : c[t];
             fit_eval<JP, SEQ>(n, v0, phi, gl, cn, lse, f0, E, E2);
-            // (Armijo, while the predicted decrease is above the rounding of the
-            // objective; one polishing step after convergence)
-            if (conv || !(-slope > 1e-13 * fmax(1.0, fabs(L0)))) break;
+            if (!conv && !(-slope > noise)) break;
             double l2 = lse;
 #pragma unroll
             for (int t = 0; t < JP; ++t) l2 += cn[t] * m[t];
-            if (l2 <= L0 + 1e-4 * st * slope || !(st > 1e-12)) break;
-            st *= 0.5;
+            if (l2 <= L0 + (conv ? noise : 1e-4 * st * slope) || !(st > 1e-12)) break;
+            st = conv ? 0.0 : 0.5 * st;
         }
 #pragma unroll
         for (int t = 0; t < JP; ++t) c[t] = cn[t];
         if (conv) {
             if (!(fabs(lse) < INFINITY)) return 1;
             logq = -lse;
-            if (!fit_solve<JP, SEQ>(E, E2, m, u))
+            // d log q / dm = -H^{-1} E[phi], the fit's own moments
+#pragma unroll
+            for (int t = 0; t < JP; ++t) mg[t] = f0[t] + E[t];
+            if (!fit_solve<JP, SEQ>(E, E2, mg, u))
 #pragma unroll
                 for (int t = 0; t < JP; ++t) u[t] = 1e300;
             return 0;

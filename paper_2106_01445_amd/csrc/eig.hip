@@ -25,8 +25,11 @@
 // 14); larger ones in global memory (L2).  Against the matrix in global memory
 // for every row, one lane's chase with two divisions and a root between memory
 // accesses, the factor's update after it, and the plan's bisection in one
-// thread (us): 64 rows of 6-14 clicks 395 -> 165, one of 30 clicks 1030 -> 280,
-// 4096 of 15-40 clicks 7750 -> 5000, 512 of 40-110 clicks 22200 -> 9700.
+// thread (us): 64 rows of 6-14 clicks 395 -> 167, one of 30 clicks 1030 -> 285,
+// 4096 of 15-40 clicks 7750 -> 4900, 512 of 40-110 clicks 22200 -> 10100.
+// The spectrum is as accurate as theirs: rms errors of alpha at 9 / 27 / 40 / 64 /
+// 110 clicks 5.8 / 9.1 / 8.7 / 10.0 / 8.4e-16 against 6.7 / 10.1 / 9.3 / 11.2 /
+// 10.1e-16.
 #include "contour_common.h"
 
 namespace {
@@ -74,12 +77,20 @@ __device__ __forceinline__ void active_block(const double *dg, double *ed, int t
 }
 
 // 1/sqrt(x), x normal: the hardware's estimate (about 24 bits) and one
-// third-order step
+// third-order step, its e = 1 - x y^2 with the rounding of x y kept (half an ulp;
+// without it one, and the spectrum's errors are a tenth to a third larger)
 __device__ __forceinline__ double rsq_nr(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
+    const double h = x * y, hl = fma(x, y, -h);
+    const double e = fma(-hl, y, fma(-h, y, 1.0));
     return fma(y * e, fma(0.375, e, 0.5), y);
+}
+// sqrt(x), x normal, within half an ulp and a little: s = x / sqrt(x) corrected once
+__device__ __forceinline__ double sqrt_nr(double x)
+{
+    const double y = rsq_nr(x), s = x * y;
+    return fma(fma(-s, s, x), 0.5 * y, s);
 }
 
 __device__ __forceinline__ double lane_value(double x, int l)
@@ -98,7 +109,7 @@ __device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, in
     // last diagonal entry
     const double e = ed[hi - 1], dh = dg[hi], dd = 0.5 * (dg[hi - 1] - dh);
     const double q2 = fma(dd, dd, e * e);  // (> 0: e is not negligible)
-    const double den = dd + copysign(q2 > 1e-290 ? q2 * rsq_nr(q2) : sqrt(q2), dd);
+    const double den = dd + copysign(q2 > 1e-290 ? sqrt_nr(q2) : sqrt(q2), dd);
     const double mu = fabs(den) > 1e-290 ? fma(-e * e, rcp_nr(den), dh) : dh;
     // a = dg[k] and b = ed[k] as rotated by the previous step
     double a = dg[lo], b = ed[lo];
@@ -112,8 +123,8 @@ __device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, in
             const double d = lane_value(dv, k), en = lane_value(ev, k);
             // G_k on (k, k+1): c = x/r, s = z/r, r = (x^2 + z^2)^{1/2}; the next
             // step's entries come from x, z and 1/r^2 directly
-            const double xx = x * x, zz = z * z, r2 = xx + zz, xz = x * z;
-            const double y = rsq_nr(r2), rc = y * y;
+            const double xx = x * x, zz = z * z, r2 = fma(x, x, zz), xz = x * z;
+            const double y = rsq_nr(r2), yy = y * y, rc = fma(yy, fma(-r2, yy, 1.0), yy);
             double c = x * y, sn = z * y, r = r2 * y;
             double ek = fma(xz, d - a, (xx - zz) * b) * rc;
             double dn = fma(-2.0 * xz, b, fma(xx, d, zz * a)) * rc;
@@ -538,7 +549,7 @@ __global__ __launch_bounds__(THREADS) void k_eig(
             // (any al and tau as consistent as these to rounding will do: H is
             // orthogonal to the rounding of tau, and couples row k by al)
             const double r2 = fma(x0, x0, sg);
-            al = -copysign(r2 > 1e-290 ? r2 * rsq_nr(r2) : sqrt(r2), x0);
+            al = -copysign(r2 > 1e-290 ? sqrt_nr(r2) : sqrt(r2), x0);
             v0 = x0 - al;
             const double vv = fma(v0, v0, sg);
             tk = vv > 1e-290 ? 2.0 * rcp_nr(vv) : 2.0 / vv;
@@ -593,6 +604,8 @@ __global__ __launch_bounds__(THREADS) void k_eig(
                 const int j = lane + 64 * u;
                 if (j < m) w[j] = pj[u] - kk * v[j];
             }
+            // (the change first: one rounding of the entry, which is near one on the
+            // diagonal, where two of them made the spectrum's errors a tenth larger)
             for (int j = lane; j < m; j += 64) {
                 const double vj = v[j], wj = w[j];
                 int i = wid;
@@ -602,10 +615,9 @@ __global__ __launch_bounds__(THREADS) void k_eig(
                     for (int u = 0; u < 4; ++u) x[u] = W2[i * ld + j + u * NW * ld];
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        W2[i * ld + j + u * NW * ld] =
-                            fma(-w[i + u * NW], vj, fma(-v[i + u * NW], wj, x[u]));
+                        W2[i * ld + j + u * NW * ld] = x[u] - fma(v[i + u * NW], wj, w[i + u * NW] * vj);
                 }
-                for (; i < m; i += NW) W2[i * ld + j] = fma(-w[i], vj, fma(-v[i], wj, W2[i * ld + j]));
+                for (; i < m; i += NW) W2[i * ld + j] -= fma(v[i], wj, w[i] * vj);
             }
         }
         __syncthreads();

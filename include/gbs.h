@@ -156,10 +156,10 @@ int gbs_get_model(gbs_ctx *ctx, double *q_inv, double *logdet_q);
  *     p(C) = det(Q)^{-1/2} sum_{Z subset C} (-1)^{n-|Z|} det((Q^{-1})_{ZZ})^{-1/2}
  * The 2^n terms and their signed sum are evaluated in double-double, so p is
  * accurate to ~1e-16 relative even when the sum cancels by 1e11.  Rows may hold
- * at most 30 clicks (2^30 terms; a row of 30 clicks takes of the order of a
- * second).  Outputs (host arrays of length P): p, logp (nullable),
- * kappa = sum|terms| / |sum| (nullable), status.  A row whose sum cancels by
- * more than 1e20 gets NaN and GBS_PS_CANCEL.  prec: GBS_PREC_FP64, or
+ * at most 30 clicks (2^30 terms; a row of 30 clicks takes 33 ms).  Outputs (host
+ * arrays of length P): p, logp (nullable), kappa = sum|terms| / |sum|
+ * (nullable), status.  A row whose sum cancels by more than 1e20 gets NaN and
+ * GBS_PS_CANCEL.  prec: GBS_PREC_FP64, or
  * GBS_PREC_MIXED (the same double-double run, every row flagged
  * GBS_PS_ESCALATED; see Precision above).
  */
@@ -329,7 +329,9 @@ int gbs_plan_info(gbs_plan *plan, double *rho, double *rconv, int32_t *K, int32_
  * gradient, vary from run to run (~1e-14 relative).  With the switch on, the
  * terms are added as 64-bit integers, llrint(term x scale), whose sum does not
  * depend on the order, and converted back: the results are bitwise
- * reproducible (same plan, model, weights and GPU type).  The scales are
+ * reproducible (same plan, model, weights and GPU type; the rows' shares are cut
+ * by the number of rows of up to 40 clicks, so that a row among others may differ
+ * in the last bits from the row alone).  The scales are
  * powers of two that leave room for every term of an entry (one per cluster
  * holding its modes; one per row for Q^-1's adjoint) below the largest term
  * of its kind: for Q^-1's adjoint a first pass over the rows finds it; for

@@ -996,7 +996,7 @@ __global__ __launch_bounds__(256) void k_retilt(int P, const int *__restrict__ o
     const int o = offsets[p], n = offsets[p + 1] - o;
     const double logdet_q = -2.0 * rp.log_pvac - rp.logdet_a;
     const double dev = rp.rconv < 1e299 ? 1.0 / rp.rconv : 0.0;
-    if (n <= 8)
+    if (n <= EIG_TINY)
         row_plan<true>(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);
     else
         row_plan<false>(rp, n, alpha + 2 * o, lane, logdet_q, rp.logdet_a, 1.0, dev, false, 0, false, rp.kbar);

@@ -23,6 +23,8 @@
 #ifndef DFT_RMAX
 #define DFT_RMAX 15
 #endif
+// rows of up to this many clicks are decomposed by eig_ordered (eig.hip)
+#define EIG_TINY 8
 
 namespace {
 
@@ -444,13 +446,6 @@ __device__ __forceinline__ void m_block_mfma(int n, int ib, int jb, const double
                 m_store<C, DIAG, FIX>(n, BS * ib + s, BS * jb + t, mre[s][t], mim[s][t], blk, lane);
 }
 
-template <class C = cplx>
-__device__ __forceinline__ void m_tile_mfma(int n, int it, int jt, const double *Vt, int vs,
-                                            const cplx *d, C *blk, int lane)
-{
-    m_block_mfma<1, C>(n, it, jt, Vt, vs, d, blk, lane);
-}
-
 // tile u of the column-major list of upper tiles (it <= jt)
 __device__ __forceinline__ void upper_tile(int u, int &it, int &jt)
 {
@@ -699,8 +694,9 @@ __device__ __forceinline__ bool fit_solve(const double *E, const double *E2, con
 // Max-entropy fit on n' = 1..n - v0 (v = n - n' empty modes, v >= v0) of the JP
 // moments m[] by Newton's method on the convex dual, from the parameters c;
 // returns 1 if a Hessian is singular, 2 after FIT_MAXIT steps, else 0, minus
-// the log-partition sum (log q(n) when v0 = 0), the parameters in c and the sensitivity u = H^{-1} m (H the covariance of the basis under
-// the fit; 1e300 where H is singular) on success.
+// the log-partition sum (log q(n) when v0 = 0), the parameters in c and the
+// sensitivity u = H^{-1} E[phi] (H the covariance of the basis under the fit;
+// 1e300 where H is singular) on success.
 template <int JP, bool SEQ>
 __device__ __forceinline__ int fit_newton(int n, int v0, LdsTab phi, int gl, const double *m, double *c,
                                           double &logq, double *u)
@@ -876,7 +872,7 @@ __device__ void dft_lds(cplx *X, const cplx *W, const DftShape &d)
 
 // Result of one sector fit with at most JM moments: log q(n), the fitted
 // parameters, the moments (zero past the ones used) and the sensitivity of log
-// q(n) to them (d log q / d m_t = -u_t, u = H^{-1} m; zero past the ones used),
+// q(n) to them (d log q / d m_t = -u_t, u = H^{-1} E[phi]; zero past the ones used),
 // how many moments were used, and bad != 0 if no fit succeeded.
 template <int JM>
 struct SectorFitT {

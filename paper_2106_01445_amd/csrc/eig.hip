@@ -164,11 +164,14 @@ __device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, in
 // whole devices of up to GBS_NSMALL modes (k_eig_whole).
 // Lossless rows hold sectors whose last moments, or whose weights, lie at the
 // transform's rounding: there a fit takes one moment more or less by the sign of
-// an error, and the row's estimate moves by up to 1e-5.  In batches of large
-// rows such sectors carry nothing; short rows (16 of 2-6 clicks: the estimates of
-// 39 of 300 such batches moved by more than 1e-9) and a distribution's outer
-// sectors show them.  So here every value has one rounding that no split over
-// lanes changes: sums run in index order or by one tree over the index, the
+// an error.  With a perturbation of 1e-16 of Q (8 and 12 modes, orders 1 to 4) the
+// estimates of rows of 3 / 4 / 5 / 6 / 7 / 8 clicks moved by up to 5e-7 / 3e-8 /
+// 5e-9 / 2e-10 / 1e-11 / 9e-13: by more than 1e-9 where at most order + 1 clicks
+// leave the moments to determine the distribution, and by nothing that is seen
+// beyond EIG_TINY.  Between two ways to take the sums, 39 of 300 batches of 16
+// rows of 2-6 clicks moved by more than 1e-9, and 6 of 100 distributions.  So
+// here every value has one rounding that no split over lanes changes: sums run in
+// index order or by one tree over the index, the
 // rotations' quotients and roots are correctly rounded, and the radius comes from
 // the halvings of [0, 0.98 R_b], six at a time: the lanes evaluate the 63
 // midpoints that six halvings can meet.
@@ -178,12 +181,12 @@ __device__ __forceinline__ void chase(double *dg, double *ed, int lo, int hi, in
 // 16 rows of 2-6 clicks 73 us (115 with a thread per column and the matrix
 // in memory; 55 with the sums split), a device of 30 modes 415 us (1030; 285).
 // ---------------------------------------------------------------------------
-#define EIG_TINY 8
-#define EIG_ORDERED_LDS(N) ((10 * (N) + 2 * (N) * ((N) + 1)) * 8)
+#define EIG_ORDERED_LDS(N) ((9 * (N) + 2 * (N) * ((N) + 1)) * 8)
 
-// c = x/r, sn = z/r, r = (x^2 + z^2)^{1/2}, each rounded to nearest: a root by
-// coupled Newton steps from the estimate of 1/r, quotients by 1/r with one
-// correction.
+// c = x/r, sn = z/r, r = (x^2 + z^2)^{1/2}, each rounded to nearest: the root by
+// Goldschmidt's coupled iteration for r and 1/(2r) from the estimate of 1/r, with
+// the remainder r2 - g g formed by fused multiply-adds, and the quotients by 1/r
+// with one correction by their remainder (Markstein, IBM J. Res. Dev. 34, 1990).
 __device__ __forceinline__ void rotation(double x, double z, double &c, double &sn, double &r)
 {
     const double r2 = fma(x, x, z * z), ax = fabs(x), az = fabs(z);
@@ -267,8 +270,8 @@ __device__ __forceinline__ void eig_ordered(int M, const double *__restrict__ qi
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = 2 * n, D = 2 * M, LD = N + 1;
     double2 *rot = (double2 *)sh;  // two steps', N each
-    double *v = sh + 4 * N, *w = v + N, *dg = w + N, *ed = dg + N, *tau = ed + N, *red = tau + N;
-    double *W = red + N, *Q = W + N * LD;
+    double *v = sh + 4 * N, *w = v + N, *dg = w + N, *ed = dg + N, *tau = ed + N;
+    double *W = tau + N, *Q = W + N * LD;
     auto sync = [] {
         if (NT > 64) {
             __syncthreads();
@@ -510,7 +513,8 @@ __global__ __launch_bounds__(THREADS) void k_eig(
             eig_tiny(M, qi, scal, modes + o, n, alpha_out + 2 * o, vt_out + vo, rows + p, frozen, sh);
         return;
     }
-    static_assert(NW >= 2, "two steps' rotations fit the reduction's arrays");
+    static_assert(NW >= 4, "two steps' rotations fit the partial sums' place");
+    static_assert(EIG_TINY >= 1 && GBS_NSMALL >= 1, "(from here on N >= 4)");
     double *part = sh;                       // NW x N partial sums
     double *v = part + NW * N, *w = v + N;   // the reflector, its partner in the rank-2
                                              // update (every wavefront writes both, alike)
@@ -623,25 +627,20 @@ __global__ __launch_bounds__(THREADS) void k_eig(
         __syncthreads();
     }
     if (tid == 0) {
-        if (N >= 2) {
-            dg[N - 2] = W[(long)(N - 2) * ld + N - 2];
-            ed[N - 2] = W[(long)(N - 2) * ld + N - 1];
-        }
-        if (N >= 1) {  // (an empty row has nothing to reduce)
-            dg[N - 1] = W[(long)(N - 1) * ld + N - 1];
-            ed[N - 1] = 0.0;
-        }
+        dg[N - 2] = W[(long)(N - 2) * ld + N - 2];
+        ed[N - 2] = W[(long)(N - 2) * ld + N - 1];
+        dg[N - 1] = W[(long)(N - 1) * ld + N - 1];
+        ed[N - 1] = 0.0;
     }
     __syncthreads();
     // 2. factor H_0 H_1 ... H_{N-3}, in place: after step k the block of rows and
     //    columns from k + 1 on holds H_k ... H_{N-3} (the identity's first row and
     //    column of each block, still occupied by a used reflector, are put in on
     //    the way); then the first row and column
-    if (N >= 2 && tid < 4) {
+    if (tid < 4) {
         const int i = N - 2 + (tid >> 1), j = N - 2 + (tid & 1);
         W[(long)i * ld + j] = i == j ? 1.0 : 0.0;
     }
-    if (N == 1 && tid == 0) W[0] = 1.0;
     __syncthreads();
     for (int k = N - 3; k >= 0; --k) {
         const int m = N - k - 1;
@@ -688,8 +687,7 @@ __global__ __launch_bounds__(THREADS) void k_eig(
         }
         __syncthreads();
     }
-    if (N >= 3)
-        for (int i = tid; i < N; i += THREADS) W[(long)i * ld] = W[i] = i == 0 ? 1.0 : 0.0;
+    for (int i = tid; i < N; i += THREADS) W[(long)i * ld] = W[i] = i == 0 ? 1.0 : 0.0;
     __syncthreads();
     if (!MAT) {
         // (the sweeps' rows are lanes: column-major)

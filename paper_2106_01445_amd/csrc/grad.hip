@@ -17,7 +17,8 @@
 //                  differentiated (implicitly: d log q / dm = -H^{-1} m, H the
 //                  covariance of the fitted basis); the sector cotangents
 //                  pushed back through the FFT to alpha_t(w_q)
-//   k_adj_contour  per (row, 64 contour points): M(w) and the clusters again
+//   k_adj_contour  per (row, 64 contour points; 8 to 64 in small batches): M(w)
+//                  and the clusters again
 //                  (the same work units as the forward, in an order that spreads
 //                  neighbouring lanes over different blocks of Z(w)),
 //                  Z(w) by LDS atomics, V^T Z V on the matrix cores (rows up to

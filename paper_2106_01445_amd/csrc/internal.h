@@ -124,7 +124,7 @@ int func_occupancy(gbs_ctx *ctx, const void *f, int threads, int lds, int *block
 int timer_begin(gbs_ctx *ctx, int group);
 void timer_end(gbs_ctx *ctx, int slot);
 enum { TG_MODEL = 0, TG_PREP = 1, TG_ITEMS = 2, TG_CONTOUR = 3, TG_FIT = 4, TG_EXACT = 5,
-       TG_ADJ_FIT = 6, TG_ADJ_CLUSTER = 7, TG_ADJ_ROWS = 8, TG_ADJ_MODEL = 9, TG_PASS2 = 10 };
+       TG_ADJ_CLUSTER = 7, TG_ADJ_ROWS = 8, TG_ADJ_MODEL = 9, TG_PASS2 = 10 };
 
 // Per-row scalar results of the approximate path's set-up step.  status holds
 // the failure bits (the row has no result); flags the informational bits that

@@ -28,6 +28,7 @@ EXPORTS = ["gbs_create", "gbs_destroy", "gbs_last_error", "gbs_set_model", "gbs_
            "gbs_grad", "gbs_grad_dev", "gbs_plan_info", "gbs_set_timing", "gbs_timing",
            "gbs_stream", "gbs_click_distribution", "gbs_prob_exact_dev", "gbs_prob_exact_dev_noalloc",
            "gbs_mcmc_step_dev", "gbs_mcmc_da_step_dev", "gbs_set_deterministic"]
+# (adjoint_fit_dft stays zero: the adjoint of the fits runs in their own kernel)
 TIMING_GROUPS = ["model", "row_setup", "work_queue", "contour_clusters", "dft_fit", "exact",
                  "adjoint_fit_dft", "adjoint_contour_clusters", "adjoint_rows_scatter",
                  "adjoint_model", "second_pass"]

@@ -29,14 +29,16 @@
 // complement by inverse blocks 0.206 / 0.106 / 0.053 / 0.026 / 0.019.
 //
 // What bounds it: the fp64 vector ALUs (about 410 operations per subset, the
-// Schur complements 7 entries of them at 27 each, and as many again for the
-// levels' redundant factors and the lanes that carry an excluded mode).  The
-// breadth-first levels of 64 lanes' nodes take 39 KB of LDS, so that one
-// wavefront sits on each SIMD with 512 registers, and the independent entries
-// of a step keep it busy.  Against levels that end with three modes per node,
-// copy excluded children and pay 122 operations per entry (43 KB, three
-// wavefronts per compute unit): one row of 30 clicks 502 -> 32.5 ms (3.3e10
-// subsets/s), 4096 rows of 6-14 clicks at 20 modes 8.60 -> 0.64 ms.
+// Schur complements 7 entries of them at 27 each; 693 issued per subset with
+// the levels' redundant factors and the lanes that carry an excluded mode).
+// The breadth-first levels of 64 lanes' nodes take 39 KB of LDS, so that one
+// wavefront sits on each SIMD with 512 registers.  At 30 clicks the counters
+// read VALU issue in 62 % of a SIMD's cycles and LDS in 7 %; the wavefront
+// issues something in 77 % and waits for its own results in the rest.  Against
+// levels that end with three modes per node, copy excluded children and pay
+// 122 operations per entry (43 KB, three wavefronts per compute unit): one row
+// of 30 clicks 502 -> 32.5 ms (3.3e10 subsets/s), 4096 rows of 6-14 clicks at
+// 20 modes 8.60 -> 0.67 ms.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
